@@ -157,11 +157,11 @@ int stag_arena_usage(const stag_ctx *ctx, size_t *used, size_t *total);
  * links: complex128 [V][4][3][3] (layout above), on the host
  * (links_on_device = 0; copied, the caller keeps ownership) or on the
  * device (1; read once, the caller keeps ownership).  The library folds the
- * staggered phases, the 1/2 and the t-boundary sign into its own copy,
- * builds the daggered backward links (the paper's `ud`) stored at the site
- * that uses them, reorders everything into a checkerboard
- * structure-of-arrays layout, and keeps FP64, FP32 and FP16 copies plus the
- * iup/idn neighbour tables resident in the arena.  When every link is
+ * staggered phases, the 1/2 and the t-boundary sign into its own copy (a
+ * backward hop daggers the neighbour's forward link: the paper's `ud` is not
+ * stored), reorders everything into a checkerboard structure-of-arrays
+ * layout, and keeps FP64, FP32 and FP16 copies, the iup/idn neighbour tables
+ * and the workspace of one solve at a time resident in the arena.  When every link is
  * special unitary (each stored matrix then has row 2 = conj(row 0 x row 1)
  * divided by its folded factor, to within 1e-14 absolute), only two rows
  * are kept and the kernels rebuild the third; otherwise all three rows are
@@ -475,8 +475,7 @@ int stag_cg_tune_info(stag_ctx *ctx, int32_t gauge_id, int32_t precision, int32_
  */
 
 /* Register links for the Wilson operator (same input layout and ownership as
- * stag_set_gauge).  The t-boundary sign is folded in, the backward links
- * U(x-mu)^dagger are stored at the site that uses them, and special unitary
+ * stag_set_gauge).  The t-boundary sign is folded in, and special unitary
  * fields keep two rows (as for stag_set_gauge; STAG_LINK_ROWS=3 keeps three).
  * The id is usable only with the stag_wilson_* calls (the staggered calls
  * return EINVAL for it, and the Wilson calls for a staggered id).

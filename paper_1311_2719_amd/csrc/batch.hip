@@ -38,15 +38,19 @@ Batch::~Batch()
         (void)hipEventDestroy(stage_ev_);
     if (stage_ && !external_)
         (void)hipHostFree(stage_);
-    if (mem_ && !external_)
-        ctx_->arena.release(mem_);
+    if (mem_ && !external_) {
+        if (field_mem_)
+            f_->work_taken.store(0);
+        else
+            ctx_->arena.release(mem_);
+    }
 }
 
 size_t Batch::workspace_bytes(const Geom &g, int prec, int slots, int pstride)
 {
     const size_t nsys = 2 * (size_t)slots, Vh = g.Vh;
     size_t b = 0;
-    b += align256(nsys * Vh * spinor_bytes_of(prec)) * 3;       // p (two buffers), ap
+    b += align256(nsys * Vh * spinor_bytes_of(prec)) * (prec == STAG_FP16_RU ? 3 : 2);  // p (FP16: two buffers), ap
     b += align256(nsys * 3 * Vh * (prec == 0 ? 16 : 8));         // r
     b += prec == 0 ? 0 : align256(nsys * 3 * Vh * 8);            // x_lo
     b += align256(nsys * 3 * Vh * 16);                           // tmp
@@ -54,7 +58,6 @@ size_t Batch::workspace_bytes(const Geom &g, int prec, int slots, int pstride)
     b += align256(nsys * sizeof(SysState)) * 2;                  // two state buffers
     b += align256(nsys * sizeof(int));                           // tile order
     b += align256(2 * nsys * 3 * (size_t)pstride * sizeof(double));  // partials
-    b += align256(2 * nsys * 3 * sizeof(double));                    // their totals
     return b;
 }
 
@@ -67,7 +70,7 @@ static int blocks_needed(const Geom &g, const KernelCfg &c)
 
 // Largest grid row of a register-tile shape with a reduction kernel; the
 // shared-link shapes may use the whole partial-sum slot.
-constexpr int kTileGridCap = 2048;
+constexpr int kTileGridCap = 8192;
 
 // Blocks per tile row of shape c: enough to cover the sites once (the
 // kernels stride over the sites when capped).  Without a reduction kernel the
@@ -114,25 +117,91 @@ bool cg_tuned_shape(Ctx *ctx, const GaugeField *f, int prec, int slots, KernelCf
 }
 
 namespace {
-// Total of the per-block partials [0, nblk) of slot slot0 + blockIdx.y of
-// partial buffer buf, system blockIdx.x, in a fixed order, into that slot's
-// entry of `totals` ([2 buffers][nsys][3 slots]).  Partials are only read, so
-// running it again over unchanged partials gives the same totals.
-__global__ void __launch_bounds__(256) k_cg_reduce(const double *partials, double *totals, int nsys, int pstride,
-                                                   int buf, int slot0, int nblk)
+
+// What k_cg_scalars does with the sums of system blockIdx.x.
+enum ScalarsKind : int { kAfterK1 = 0, kAfterK2 = 1, kAfterInit = 2, kSumOnly = 3 };
+
+// The scalars of one step, once per system instead of in every block of the
+// next kernel: totals of the partials [0, nblk) of the slots the last kernel
+// wrote (fixed order), then after K1 (state buffer cur = ver ^ 1) alpha, kept
+// in that state with <u',u'> (FP16: and <p',p'>); after K2 the state of the
+// next step, from buffer cur into buffer ver; after the initialisation the
+// first step's state, from buffer 0 into 1, for systems still in M_INIT.
+// kSumOnly forms the sums and leaves the states alone (timing runs).  Running it again
+// over unchanged partials and states gives the same result.  A block reads
+// up to 8192 partials per slot, 8 per thread and slot in flight.
+template <bool REC>
+__global__ void __launch_bounds__(1024) k_cg_scalars(CgArgs a, int ver, int kind, int nblk)
 {
-    __shared__ double lds[4];
-    const size_t k = ((size_t)buf * nsys + blockIdx.x) * 3 + slot0 + blockIdx.y;
-    const double t = reduce_partials(partials + k * pstride, nblk, lds);
-    if (threadIdx.x == 0)
-        totals[k] = t;
+    constexpr int U = 8, K1S = REC ? 1 : 2;  // slots K1 writes: [0, K1S); K2 the rest
+    __shared__ double lds[3 * 16];
+    const int j = blockIdx.x, cur = kind == kAfterInit ? 0 : ver ^ 1;
+    SysState st = a.st[cur][j];
+    const bool live = kind == kAfterInit ? st.mode == M_INIT : st.mode != M_IDLE && st.mode != M_DONE;
+    if (!live && kind != kAfterK2)
+        return;
+    double t[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const bool mine = kind == kAfterInit ? k == 2 : kind == kAfterK2 ? k >= K1S : k < K1S;
+        if (!mine || !live)
+            continue;
+        const double *p = partial_slot(a, cur, j, k);
+        double v = 0.0;
+        for (int i0 = threadIdx.x; i0 < nblk; i0 += U * blockDim.x) {
+            double b[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int i = i0 + u * blockDim.x;
+                const double q = p[i < nblk ? i : 0];
+                b[u] = i < nblk ? q : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                v += b[u];
+        }
+        v = wave_sum(v);
+        if ((threadIdx.x & 63) == 0)
+            lds[k * 16 + (threadIdx.x >> 6)] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x != 0)
+        return;
+    for (int k = 0; k < 3; ++k)
+        for (int w = 0; w < (int)(blockDim.x >> 6); ++w)
+            t[k] += (kind == kAfterInit ? k == 2 : kind == kAfterK2 ? k >= K1S : k < K1S) && live ? lds[k * 16 + w] : 0.0;
+    if (kind == kAfterK1) {
+        if (st.mode != M_CG)
+            return;
+        if (!REC)
+            st.pp = t[1];
+        const double pap = st.mass2 * st.pp + t[0];
+        a.st[cur][j].apap = t[0];
+        a.st[cur][j].pp = st.pp;
+        a.st[cur][j].alpha = finite_pos(pap) ? st.rr / pap : 0.0;
+    } else if (kind == kAfterK2) {
+        if (live) {
+            const double s[3] = {st.apap, REC ? t[1] : st.pp, t[2]};
+            advance<REC>(st, s);
+        }
+        a.st[ver][j] = st;
+    } else if (kind == kAfterInit) {
+        advance<REC>(st, t);
+        a.st[1][j] = st;
+    } else if (t[0] == -1.0) {  // never (a sum of squares): keeps the sums alive
+        a.st[cur][j].apap = t[0];
+    }
 }
+
 }  // namespace
 
-hipError_t Batch::launch_reduce(hipStream_t st, int buf, int slot0, int nslots, int nblk) const
+hipError_t Batch::launch_scalars(hipStream_t st, const CgArgs &a, int ver, int kind, int nblk) const
 {
-    hipLaunchKernelGGL(k_cg_reduce, dim3((unsigned)nsys(), (unsigned)nslots), dim3(256), 0, st, partials_, totals_,
-                       nsys(), pstride_, buf, slot0, nblk);
+    const dim3 grid((unsigned)nsys()), block(nblk > 1024 ? 1024 : 256);
+    if (prec_ == STAG_FP16_RU)
+        hipLaunchKernelGGL((k_cg_scalars<false>), grid, block, 0, st, a, ver, kind, nblk);
+    else
+        hipLaunchKernelGGL((k_cg_scalars<true>), grid, block, 0, st, a, ver, kind, nblk);
     return hipGetLastError();
 }
 
@@ -146,7 +215,7 @@ size_t Batch::host_bytes_for(int slots)
 // tiles: kTileGridCap; shared-link tiles: up to 4096 chunks of 64 sites).
 static int pstride_for(const Geom &g)
 {
-    const int p = std::min(4096, std::max(std::min(kTileGridCap, blocks_for(g.Vh, 8, 64)), (g.Vh + kChunk - 1) / kChunk));
+    const int p = std::min(kTileGridCap, std::max(std::min(kTileGridCap, blocks_for(g.Vh, 8, 64)), (g.Vh + kChunk - 1) / kChunk));
     return (p + 63) & ~63;
 }
 
@@ -163,7 +232,7 @@ void Batch::carve(void *base)
         return (void *)r;
     };
     p_[0] = take(nsys * Vh * spinor_bytes_of(prec_));
-    p_[1] = take(nsys * Vh * spinor_bytes_of(prec_));
+    p_[1] = prec_ == STAG_FP16_RU ? take(nsys * Vh * spinor_bytes_of(prec_)) : nullptr;
     ap_ = take(nsys * Vh * spinor_bytes_of(prec_));
     r_ = take(nsys * 3 * Vh * (prec_ == 0 ? 16 : 8));
     xlo_ = prec_ == 0 ? nullptr : (flt2 *)take(nsys * 3 * Vh * 8);
@@ -175,7 +244,6 @@ void Batch::carve(void *base)
     st_d_[1] = st_d_[0] + nsys;
     perm_d_ = (int *)take(nsys * sizeof(int));
     partials_ = (double *)take(2 * nsys * 3 * (size_t)pstride_ * sizeof(double));
-    totals_ = (double *)take(2 * nsys * 3 * sizeof(double));
 }
 
 int Batch::mark_stage()
@@ -197,12 +265,18 @@ void Batch::wait_stage()
     stage_busy_ = false;
 }
 
-int Batch::create()
+int Batch::create(bool own_work)
 {
     const Geom &g = f_->g;
     pstride_ = pstride_for(g);
     bytes_ = workspace_bytes(g, prec_, S_, pstride_);
-    mem_ = ctx_->arena.alloc(bytes_);
+    int idle = 0;
+    if (own_work && f_->work && bytes_ <= f_->work_bytes && f_->work_taken.compare_exchange_strong(idle, 1)) {
+        mem_ = f_->work;
+        field_mem_ = true;
+    } else {
+        mem_ = ctx_->arena.alloc(bytes_);
+    }
     if (!mem_)
         return set_error(STAG_ENOMEM, "arena exhausted: CG workspace needs %zu bytes (largest free block %zu)", bytes_,
                          ctx_->arena.largest_free());
@@ -332,23 +406,30 @@ double Batch::time_cg_config(const KernelCfg &c, int nblk, bool reduce)
     CgArgs a = args();
     for (int par = 0; par < 2; ++par)
         a.nbr[par] = c.tables ? f_->nbr_for(par) : nullptr;
-    a.remap = c.remap;
-    a.psum = reduce ? totals_ : partials_;
-    a.psum_stride = reduce ? 1 : pstride_;
-    a.nread = reduce ? 1 : nblk;
+    a.remap = remap_for(c, nblk);
+    a.nread = reduce ? 0 : nblk;
     if (c.shared && !t.shared1)
         return 1e30;
-    dim3 grid((unsigned)nblk, (unsigned)(nsys() / c.rtile)), blk(c.block);
+    a.npar = 2;
+    a.par0 = 0;
+    dim3 grid((unsigned)nblk * (unsigned)(nsys() / c.rtile)), blk(c.block);
+    // every shape starts from the same states, vectors and partials
+    const size_t ns = (size_t)nsys(), sb = ns * sizeof(SysState);
+    if (hipMemcpyAsync(st_d_[0], tune_st_.data(), sb, hipMemcpyHostToDevice, s_) != hipSuccess ||
+        hipMemcpyAsync(st_d_[1], tune_st_.data(), sb, hipMemcpyHostToDevice, s_) != hipSuccess ||
+        hipMemsetAsync(p_[0], 0x3f, (char *)tmp_ - (char *)p_[0] + ns * 3 * f_->g.Vh * 16, s_) != hipSuccess ||
+        hipMemsetAsync(partials_, 0x3f, 2 * ns * 3 * (size_t)pstride_ * sizeof(double), s_) != hipSuccess)
+        return 1e30;
     auto step = [&]() {
         hipError_t e = c.shared ? t.shared1(c.rtile, c.block / 64, grid, s_, a, 0)
                                  : t.step1(c.lps, c.rtile, grid, blk, s_, a, 0);
         if (e == hipSuccess && reduce)
-            e = launch_reduce(s_, 1, 0, 2, nblk);
+            e = launch_scalars(s_, a, 0, kSumOnly, nblk);
         if (e == hipSuccess)
             e = c.shared ? t.shared2(c.rtile, c.block / 64, grid, s_, a, 0)
                          : t.step2(c.lps, c.rtile, grid, blk, s_, a, 0);
         if (e == hipSuccess && reduce)
-            e = launch_reduce(s_, 1, 2, 1, nblk);
+            e = launch_scalars(s_, a, 0, kSumOnly, nblk);
         return e;
     };
     if (step() != hipSuccess)
@@ -396,7 +477,7 @@ static KernelCfg shared_shape(int code, int reduce)
     c.block = 64 * W;
     c.rtile = W * RR;
     c.tables = 0;
-    c.remap = 1;
+    c.remap = 2;
     c.reduce = reduce;
     c.shared = 1;
     return c;
@@ -431,16 +512,18 @@ KernelCfg Batch::tune_cg()
     if (tenv && tenv[0] == '0')
         return best;
     // Every system in a CG step; vectors and the partial sums the first
-    // prologue reads filled with a small positive pattern (bytes 0x3f), so the
-    // state stays in CG steps and every kernel does its full work.  x points at
+    // prologue reads filled with a small positive pattern (bytes 0x3f) before
+    // each shape's run, so the state stays in CG steps and every kernel does its
+    // full work.  x points at
     // the FP64 work vector.
     const size_t nsys = 2 * (size_t)S_, Vh = f_->g.Vh;
-    std::vector<SysState> st(nsys);
-    memset(st.data(), 0, nsys * sizeof(SysState));
-    for (auto &x : st) {
+    tune_st_.resize(nsys);
+    memset(tune_st_.data(), 0, nsys * sizeof(SysState));
+    for (auto &x : tune_st_) {
         x.mode = M_CG;
         x.mass2 = 1e-4;
         x.rr = 1.0;
+        x.alpha = 1e-30;
         x.maxiter = 1 << 30;
         x.mixed = prec_ != STAG_FP64;
     }
@@ -448,13 +531,8 @@ KernelCfg Batch::tune_cg()
     for (size_t j = 0; j < nsys; ++j)
         xs[j] = tmp_ + j * 3 * Vh;
     const bool verbose = getenv("STAG_TUNE_VERBOSE") != nullptr;
-    const size_t vec_bytes = (char *)tmp_ - (char *)p_[0] + nsys * 3 * Vh * 16;
-    if (hipMemcpyAsync(st_d_[0], st.data(), nsys * sizeof(SysState), hipMemcpyHostToDevice, s_) != hipSuccess ||
-        hipMemcpyAsync(xhi_d_, xs.data(), nsys * sizeof(void *), hipMemcpyHostToDevice, s_) != hipSuccess ||
+    if (hipMemcpyAsync(xhi_d_, xs.data(), nsys * sizeof(void *), hipMemcpyHostToDevice, s_) != hipSuccess ||
         hipMemcpyAsync(perm_d_, perm_h_, nsys * sizeof(int), hipMemcpyHostToDevice, s_) != hipSuccess ||
-        hipMemsetAsync(p_[0], 0x3f, vec_bytes, s_) != hipSuccess ||
-        hipMemsetAsync(partials_, 0x3f, 2 * nsys * 3 * (size_t)pstride_ * sizeof(double), s_) != hipSuccess ||
-        hipMemsetAsync(totals_, 0x3f, 2 * nsys * 3 * sizeof(double), s_) != hipSuccess ||
         hipEventCreate(&tune_ev_[0]) != hipSuccess || hipEventCreate(&tune_ev_[1]) != hipSuccess) {
         (void)hipStreamSynchronize(s_);
         return best;
@@ -507,10 +585,12 @@ KernelCfg Batch::tune_cg()
         }
     }
     for (int T = 0; T < 2; ++T)
-        for (int X = 0; X < 2; ++X) {
+        for (int X = 0; X < 4; ++X) {
             KernelCfg c = best;
             c.tables = T;
             c.remap = X;
+            if (remap_for(c, grid_x(c)) != X)
+                continue;
             const double ms = time_cg_config(c, grid_x(c), uses_reduction(c));
             if (verbose)
                 fprintf(stderr, "[stag tune cg] V=%d prec=%d slots=%d lps=%d block=%d rtile=%d tables=%d remap=%d: "
@@ -641,10 +721,18 @@ int Batch::upload_and_init(const std::vector<int> &systems)
     // one thread per site (the init kernel takes any block of up to 256 threads)
     hipError_t e = cfg_.shared ? t.init(grid, dim3(256), s_, a, 1) : t.init(grid, dim3(cfg_.block), s_, a, cfg_.lps);
     if (e == hipSuccess && reduce_)
-        e = launch_reduce(s_, 0, 2, 1, nblk_);
+        e = launch_scalars(s_, a, 0, kAfterInit, nblk_);
     if (e != hipSuccess)
         return set_error(STAG_EHIP, "init launch failed: %s", hipGetErrorString(e));
     return STAG_OK;
+}
+
+// The block order of shape c with nblk chunks: t-columns (remap 3) only where
+// each chunk is visited once and an eighth of a t-slice is whole chunks.
+int Batch::remap_for(const KernelCfg &c, int nblk) const
+{
+    const bool ok = c.shared ? slices_divide(f_->g, 1, kChunk, nblk) : slices_divide(f_->g, c.lps, c.block, nblk);
+    return c.remap == 3 && !ok ? 1 : c.remap;
 }
 
 CgArgs Batch::args() const
@@ -670,43 +758,45 @@ CgArgs Batch::args() const
     a.perm = perm_d_;
     a.partials = partials_;
     a.S = S_;
+    a.npar = parities_ == 3 ? 2 : 1;
+    a.par0 = parities_ == 2 ? 1 : 0;
     a.pstride = pstride_;
-    a.remap = cfg_.remap;
-    a.psum = reduce_ ? totals_ : partials_;
-    a.psum_stride = reduce_ ? 1 : pstride_;
-    a.nread = reduce_ ? 1 : nblk_;
+    a.remap = remap_for(cfg_, nblk_);
+    a.nread = reduce_ ? 0 : nblk_;
     return a;
 }
 
 int Batch::launch_step(int ver, hipStream_t st, const KernelCfg &c)
 {
     const CgLaunchTable &t = cg_table(prec_, f_->rows, f_->nt_links);
-    const CgArgs a = args();
+    CgArgs a = args();
+    a.remap = remap_for(c, nblk_);  // smaller tiles may have other shapes
     const int R = c.rtile;
-    dim3 grid((unsigned)nblk_, (unsigned)(nsys() / R)), blk(c.block);
+    dim3 grid((unsigned)nblk_ * (unsigned)(a.npar * S_ / R)), blk(c.block);
     if (c.shared && !t.shared1)
         return set_error(STAG_EINVAL, "no shared-link CG tiles for precision %d", prec_);
     hipError_t e = c.shared ? t.shared1(R, c.block / 64, grid, st, a, ver) : t.step1(c.lps, R, grid, blk, st, a, ver);
-    if (e == hipSuccess && reduce_)  // K1's partials: slots 0, 1 of buffer ver ^ 1
-        e = launch_reduce(st, ver ^ 1, 0, 2, nblk_);
+    if (e == hipSuccess && reduce_)
+        e = launch_scalars(st, a, ver, kAfterK1, nblk_);
     if (e == hipSuccess)
         e = c.shared ? t.shared2(R, c.block / 64, grid, st, a, ver) : t.step2(c.lps, R, grid, blk, st, a, ver);
-    if (e == hipSuccess && reduce_)  // K2's partials: slot 2 of buffer ver ^ 1
-        e = launch_reduce(st, ver ^ 1, 2, 1, nblk_);
+    if (e == hipSuccess && reduce_)
+        e = launch_scalars(st, a, ver, kAfterK2, nblk_);
     if (e != hipSuccess)
         return set_error(STAG_EHIP, "CG kernel launch failed: %s", hipGetErrorString(e));
     return STAG_OK;
 }
 
-// Key of the recorded epoch of `steps` steps with shape c (one shape per tile size).
-static int graph_key(const KernelCfg &c, int steps)
+// Key of the recorded epoch of `steps` steps with shape c (one shape per tile
+// size) over the given parities.
+static int graph_key(const KernelCfg &c, int steps, int parities)
 {
-    return ((c.shared ? c.block / 64 : 0) * 64 + c.rtile) * 1024 + steps;
+    return (((c.shared ? c.block / 64 : 0) * 64 + c.rtile) * 4 + parities) * 1024 + steps;
 }
 
 int Batch::record_epoch(int steps, const KernelCfg &c)
 {
-    const int key = graph_key(c, steps);
+    const int key = graph_key(c, steps, parities_);
     if (graphs_.count(key))
         return STAG_OK;
     hipGraph_t graph = nullptr;
@@ -757,7 +847,7 @@ int Batch::enqueue_epoch(int steps)
     int rc = record_epoch(steps, c);
     if (rc != STAG_OK)
         return rc;
-    auto it = graphs_.find(graph_key(c, steps));
+    auto it = graphs_.find(graph_key(c, steps, parities_));
     STAG_HIP_CHECK(hipGraphLaunch(it->second, s_));
     return STAG_OK;
 }
@@ -859,7 +949,7 @@ int acquire_batch(Ctx *ctx, const std::shared_ptr<GaugeField> &f, int prec, int 
     }
     for (int attempt = 0; attempt < 2; ++attempt) {
         auto b = std::make_shared<Batch>(ctx, f, prec, slots, s);
-        int rc = b->create();
+        int rc = b->create(slots == 1);
         if (rc == STAG_OK) {
             out = b;
             return STAG_OK;
@@ -976,6 +1066,11 @@ static int run_solve(Ctx *ctx, Batch &B, const std::shared_ptr<GaugeField> &f, i
         }
     }
     // a workspace taken from the cache keeps the tile order of its last solve
+    int parities = 0;
+    for (int par = 0; par < 2; ++par)
+        for (int i = 0; i < nrhs; ++i)
+            parities |= running[par * nrhs + i] ? 1 << par : 0;
+    B.set_parities(parities);
     if ((rc = B.upload_and_init(systems)) != STAG_OK || (rc = B.set_running(running)) != STAG_OK)
         return rc;
     int E = 8, Emax = kEpochMax;

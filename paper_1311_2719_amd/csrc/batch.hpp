@@ -20,9 +20,10 @@ public:
     Batch(const Batch &) = delete;
     Batch &operator=(const Batch &) = delete;
 
-    // Allocate workspace from the arena and pinned host mirrors.  ENOMEM if
-    // the arena cannot hold it.
-    int create();
+    // Allocate workspace from the arena (own_work: the field's own workspace if
+    // it is free and large enough) and pinned host mirrors.  ENOMEM if the
+    // arena cannot hold it.
+    int create(bool own_work = false);
     // Use caller-provided memory instead: `dev` (device, dev_bytes >=
     // workspace_bytes) and `host` (ordinary host memory, host_bytes >=
     // host_bytes_for(slots)).  Nothing is allocated: no arena, pinned memory,
@@ -68,6 +69,9 @@ public:
     // `running` first (per parity), the rest left out.  Stream-ordered: applies
     // to the kernels enqueued after this call.
     int set_running(const std::vector<char> &running);
+    // Parities the step kernels cover from now on (bit 0 even, bit 1 odd): a
+    // solve of one parity launches no blocks for the other.
+    void set_parities(int mask) { parities_ = mask; }
     // Tile shape of the next epoch: the tuned shape, or while fewer systems
     // run per parity than it takes, the smallest tuned tile that holds them.
     const KernelCfg &epoch_cfg() const;
@@ -79,8 +83,10 @@ private:
     int mark_stage();                 // the staged host data are being copied
     void wait_stage();                // ... and may be overwritten after this
     int grid_x(const KernelCfg &c) const;
+    int remap_for(const KernelCfg &c, int nblk) const;
+
     bool uses_reduction(const KernelCfg &c) const;
-    hipError_t launch_reduce(hipStream_t st, int buf, int slot0, int nslots, int nblk) const;
+    hipError_t launch_scalars(hipStream_t st, const CgArgs &a, int ver, int kind, int nblk) const;
     // Tune the tile shape on this workspace; also fills small_.
     KernelCfg tune_cg();
     KernelCfg default_cg_cfg() const;
@@ -101,6 +107,7 @@ private:
     // a reduction kernel sums each step kernel's partials before the next
     // kernel reads them (large grids); otherwise every prologue sums them
     bool reduce_ = false;
+    int parities_ = 3;  // parities the step kernels cover (set_parities)
     int live_ = 0;  // running systems per parity (the larger count), from set_running
     int pstride_ = 0;
     void *mem_ = nullptr;
@@ -114,7 +121,6 @@ private:
     SysState *st_d_[2] = {nullptr, nullptr};
     int *perm_d_ = nullptr;
     double *partials_ = nullptr;
-    double *totals_ = nullptr;  // [2][nsys][3] totals of the partials (reduction kernel)
     // pinned host memory
     SysState *stage_ = nullptr;   // [nsys] staged initial states
     SysState *snap_ = nullptr;    // [2][nsys] last snapshot of both state buffers
@@ -123,13 +129,15 @@ private:
     int *perm_h_ = nullptr;
     std::vector<int> perm_last_;
     hipEvent_t snap_ev_ = nullptr, stage_ev_ = nullptr;
+    std::vector<SysState> tune_st_;  // states a timed shape starts from
     hipEvent_t tune_ev_[2] = {nullptr, nullptr};
     bool stage_busy_ = false;
+    bool field_mem_ = false;  // mem_ is the field's own workspace (GaugeField::work)
     bool external_ = false;  // memory from create_external: nothing owned, no events
     // epochs recorded once as HIP graphs (kernel nodes only) and replayed
     bool use_graphs_ = true;
     hipStream_t cap_stream_ = nullptr;
-    std::map<int, hipGraphExec_t> graphs_;  // key: rtile * 1024 + steps
+    std::map<int, hipGraphExec_t> graphs_;  // key: graph_key
 };
 
 }  // namespace stag

@@ -159,13 +159,17 @@ int stag_set_gauge(stag_ctx *ctx, const int32_t dims[4], const double *links, in
         f->bytes += lb;
     }
     f->nbr = (int32_t *)c->arena.alloc(2 * 8 * Vh * sizeof(int32_t));
-    f->bytes += 2 * 8 * Vh * sizeof(int32_t);
+    // the workspace of one solve at a time on the field
+    f->work_bytes = f->bytes;
+    f->work = c->arena.alloc(f->work_bytes);
+    f->bytes += 2 * 8 * Vh * sizeof(int32_t) + f->work_bytes;
     auto release_all = [&]() {
         for (int p = 0; p < 3; ++p)
             c->arena.release(f->links[p]);
         c->arena.release(f->nbr);
+        c->arena.release(f->work);
     };
-    if (!f->links[0] || !f->links[1] || !f->links[2] || !f->nbr) {
+    if (!f->links[0] || !f->links[1] || !f->links[2] || !f->nbr || !f->work) {
         release_all();
         return set_error(STAG_ENOMEM, "stag_set_gauge: arena exhausted (%zu bytes needed)", f->bytes);
     }
@@ -209,6 +213,7 @@ int stag_free_gauge(stag_ctx *ctx, int32_t gauge_id)
     for (int p = 0; p < 3; ++p)
         c->arena.release(f->links[p]);
     c->arena.release(f->nbr);
+    c->arena.release(f->work);
     return STAG_OK;
     STAG_GUARD_END
 }

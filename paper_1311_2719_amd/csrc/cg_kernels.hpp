@@ -4,30 +4,38 @@
 // The iteration is the loop of the paper's Sec. 4 with the mass explicit,
 // arranged as two kernels per step so that every vector is streamed once and
 // every scalar stays on the device (large grids add a small reduction kernel
-// after each, see below):
-//   K1  prologue: reduce the previous step's partial sums and advance the
-//       system's scalar state (beta, the stopping test, reliable-update
-//       decisions); then, for a CG step, p' = r + beta p (formed on the fly at
-//       every gathered neighbour and stored once at the partner site),
-//       ap = D p' on the other parity, <ap,ap> and <p',p'>;
-//   K2  prologue: alpha = rr / (m^2 <p',p'> + <ap,ap>) from K1's partials;
-//       then Ap = m^2 p' - D ap; x += alpha p'; r -= alpha Ap; <r,r>
-//       (Ap is never stored).
+// after each, see below).  With u = D p (on the other parity):
+//   K1  u' = D r + beta u (= D p' for p' = r + beta p) and <u',u'>;
+//   K2  alpha = rr / (m^2 <p',p'> + <u',u'>); p' = r + beta p;
+//       Ap' = m^2 p' - D u'; x += alpha p'; r -= alpha Ap'; <r,r>, <r,p'>
+//       (Ap' is never stored).
+// K1's prologue reduces the previous step's partial sums and advances the
+// system's scalar state (beta, the stopping test, reliable-update decisions);
+// <p',p'> = <r,r> + 2 beta <r,p> + beta^2 <p,p> needs no sum of its own.
+// The recurrence of u carries the same relative rounding as that of p (each
+// adds one rounding per step and damps the earlier ones by the same beta).
+// It halves K1's gathers (r alone instead of r and p at eight neighbours).
+// Both kernels together, without prologues: FP64 32^4 271 -> 254 us, FP32 136 ->
+// 112, 16^4 FP64 14.8 -> 14.0.
+// FP16 vectors keep the direct form: p' = r + beta p is formed at every
+// gathered neighbour in K1 (and stored once), u' = D p', <p',p'> is summed in
+// K1.  A recurrence of u in 16 bits would drift from D p by 2^-11 per step.
 // A step of a system can instead be a residual recomputation in FP64
 // (reliable update in mixed precision, the final true-residual check in every
 // mode): K1 forms t = D (x_hi + x_lo) on the other parity, K2 forms
 // x_hi += x_lo, x_lo = 0, r = b - m^2 x_hi + D t and <r,r>.
 //
-// Every block of a kernel derives the same scalars from the same partials
-// (fixed summation order), so no block waits for another and no fence or
-// atomic is used; the state advanced by K1 is written by one block into the
+// Small grids: every block of a kernel derives the same scalars from the same
+// partials (fixed summation order), so no block waits for another and no fence
+// or atomic is used; the state advanced by K1 is written by one block into the
 // other of two state buffers, which the following kernels read.  Partial sums
 // alternate between two buffers the same way.  Each block of a prologue sums
 // all per-block partials of the kernel before it, which costs blocks x
-// partials reads; for large grids the host runs a small reduction kernel
-// between the step kernels instead, which writes each slot's total to a
-// separate array (CgArgs::psum, nread = 1), so that the step kernels can use
-// as many blocks as the lattice needs.
+// partials reads and, for each block, two to three microseconds before its
+// first load of a vector.  Large grids run a small kernel after each step
+// kernel instead (k_cg_scalars: one block per system) that sums the partials,
+// forms alpha or advances the state, and leaves both in the state, which the
+// step kernels then read as scalars (CgArgs::nread = 0).
 //
 // Systems: nsys = 2*S, system j has parity j / S (x, r, p on that parity; ap
 // and t on the other).  A tile is R systems of one parity processed together
@@ -50,13 +58,13 @@ struct SysState {
     double stop2;    // tol^2 <b,b>
     double bb;
     double rr;       // <r,r> of the current (iterated) residual
-    double pp;       // <p,p> of the last search direction
+    double pp;       // <p,p> of the search direction of the step (FP16: of the last one)
     double alpha;
     double beta;
     double maxr2;    // largest <r,r> since the last residual recomputation
     double delta2;   // reliable-update threshold squared (0: final check only)
     double true_rr;  // <r,r> of the last FP64 residual recomputation
-    double pad0;
+    double apap;     // <u',u'> of the step (k_cg_scalars)
     int32_t mode;        // Mode
     int32_t stopping;    // status to report if the next recomputation does not converge
     int32_t status;      // final status (mode == M_DONE)
@@ -66,18 +74,18 @@ struct SysState {
     int32_t restarts;
     int32_t max_restarts;
     int32_t mixed;
-    int32_t pcur;        // which of the two p buffers holds the current direction
+    int32_t pcur;        // FP16: which of the two p buffers holds the current direction
     int32_t step;        // steps taken (the newer of the two state buffers has the larger value)
     int32_t pad1;
 };
 
 struct CgArgs {
     Geom g;
-    const void *links[2];      // links of the working precision, per output parity
-    const dbl2 *links64[2];    // FP64 links, per output parity
+    const void *links[2];      // links of the working precision, per parity of their site
+    const dbl2 *links64[2];    // FP64 links, per parity of their site
     const int32_t *nbr[2];     // neighbour tables per output parity, or null
-    void *p[2];                // [nsys] stored search directions (working precision), two buffers
-    void *ap;                  // [nsys] stored spinors (working precision)
+    void *p[2];                // [nsys] search directions (working precision); FP16: two buffers
+    void *ap;                  // [nsys] D p (working precision)
     void *r;                   // [nsys][3][Vh] complex of the compute type
     flt2 *xlo;                 // [nsys][3][Vh] (mixed precision only)
     dbl2 *tmp;                 // [nsys][3][Vh] FP64 work vector (other parity)
@@ -87,13 +95,11 @@ struct CgArgs {
     const int *perm;           // [2][S] systems of each parity in tile order, -1 = none
     double *partials;          // [2 buffers][nsys][3 slots][pstride]
     int S;                     // systems per parity
+    int npar, par0;            // parities the grid covers: par0 .. par0 + npar - 1
     int pstride;
     int remap;
-    // what a prologue sums: nread entries per slot at psum (stride psum_stride
-    // between slots) -- the previous kernel's per-block partials (psum =
-    // partials), or the totals a reduction kernel formed from them (nread = 1)
-    const double *psum;
-    int psum_stride;
+    // per-block partials that a prologue sums per slot; 0: k_cg_scalars has
+    // summed them, st[ver ^ 1] holds the state of the step and alpha
     int nread;
 };
 
@@ -119,14 +125,12 @@ template <class P> __device__ __forceinline__ cplx<typename P::real> load_colour
     }
 }
 
-// Partial sums: slot 0 <ap,ap>, slot 1 <p',p'>, slot 2 <r,r> (CG, residual
-// recomputation or the source norm at initialisation).
-__device__ __forceinline__ const double *psum_slot(const CgArgs &a, int buf, int j, int slot)
-{
-    const size_t nsys = 2 * (size_t)a.S;
-    return a.psum + (((size_t)buf * nsys + j) * 3 + slot) * a.psum_stride;
-}
+// Whether precision P runs the recurrence form (see the top of the file).
+template <class P> constexpr bool kRecurrence = P::id != 2;
 
+// Partial sums: slot 0 <u',u'> (K1), slot 1 <r,p'> (K2; FP16: <p',p'>, K1), slot
+// 2 <r,r> (K2: CG, residual recomputation, or the source norm at
+// initialisation).
 __device__ __forceinline__ double *partial_slot(const CgArgs &a, int buf, int j, int slot)
 {
     const size_t nsys = 2 * (size_t)a.S;
@@ -190,7 +194,7 @@ __device__ __forceinline__ void load_prologue(const CgArgs &a, int pbuf, const S
     for (int r = 0; r < R; ++r)
 #pragma unroll
         for (int k = 0; k < NS; ++k)
-            base[r * NS + k] = psum_slot(a, pbuf, js[r], k);
+            base[r * NS + k] = partial_slot(a, pbuf, js[r], k);
 #pragma unroll
     for (int k = 0; k < NS * R; ++k)
         v[k] = 0.0;
@@ -254,8 +258,9 @@ __device__ __forceinline__ double wave_total(const double *lds, int k)
     return out;
 }
 
-// Advance a system's state over the step whose partial sums are `t`.
-__device__ __forceinline__ void advance(SysState &s, const double (&t)[3])
+// Advance a system's state over the step whose partial sums are `t`.  REC:
+// the recurrence form (t[1] = <r,p>), else t[1] = <p',p'>.
+template <bool REC> __device__ __forceinline__ void advance(SysState &s, const double (&t)[3])
 {
     s.step += 1;
     switch (s.mode) {
@@ -287,10 +292,11 @@ __device__ __forceinline__ void advance(SysState &s, const double (&t)[3])
         break;
     }
     case M_CG: {
-        s.pcur ^= 1;  // the previous K1 stored p' in the other buffer
-        const double apap = t[0], pp = t[1];
-        s.pp = pp;
-        const double pap = s.mass2 * pp + apap;
+        s.pcur ^= 1;  // FP16: the previous K1 stored p' in the other buffer
+        const double apap = t[0];
+        if (!REC)
+            s.pp = t[1];
+        const double pap = s.mass2 * s.pp + apap;
         if (!finite_pos(pap)) {  // K2 skipped this system's update
             s.stopping = STAG_EBREAKDOWN;
             s.mode = M_RU;
@@ -355,17 +361,30 @@ __device__ __forceinline__ void advance(SysState &s, const double (&t)[3])
     default:
         break;
     }
+    if (REC && s.mode == M_CG)  // <p',p'> of the direction this step takes
+        s.pp = s.beta != 0.0 ? s.rr + s.beta * (2.0 * t[1] + s.beta * s.pp) : s.rr;
 }
 
-// Directions per iteration of the rolled FP64 hop of a residual
-// recomputation: two keeps the register budget of the single-site CG kernels
-// while overlapping the loads of two directions.
-constexpr int kRecomputeUnroll = 2;
+// The tile of this block (pieces of `piece` threads of the sites'
+// threads_per_slice in a t-slice): output parity of the systems' own sites, first
+// place of the tile in `perm`, and the chunk of sites.  The grid is nchunks x
+// (npar S / R) blocks (block_tile); tiles of the two parities alternate.
+struct StepTile {
+    int par, k0, chunk, nchunks;
+};
+
+template <int R> __device__ __forceinline__ StepTile step_tile(const CgArgs &a, int threads_per_slice, int piece)
+{
+    const int tpp = a.S / R;
+    const BlockTile t = block_tile(a.npar * tpp, a.remap, threads_per_slice / piece);
+    const int par = a.par0 + (a.npar == 2 ? t.tile & 1 : 0), i = a.npar == 2 ? t.tile >> 1 : t.tile;
+    return {par, par * a.S + i * R, t.chunk, t.nchunks};
+}
 
 // First site index handled by this thread in grid-stride round `it`.
-__device__ __forceinline__ int64_t round_base(int it, int remap)
+__device__ __forceinline__ int64_t round_base(int it, int chunk, int nchunks)
 {
-    return ((int64_t)it * gridDim.x + logical_block(blockIdx.x, gridDim.x, remap)) * blockDim.x + threadIdx.x;
+    return ((int64_t)it * nchunks + chunk) * blockDim.x + threadIdx.x;
 }
 
 // ---- own-site values of a step ------------------------------------------------------
@@ -387,7 +406,24 @@ template <class P, int R, int LPS> struct OwnSite {
     cplx<real> ps_[G][3];
     xv_t xx_[G][3];
 
-    // K1: p (current buffer) and r of systems r0 .. r0 + G - 1 at the partner site
+    // K1, recurrence form: u at the output site (into pr_)
+    template <class Args>
+    __device__ __forceinline__ void load_u(const Args &a, const int *js, const bool *on, int s, int sub, int r0)
+    {
+        const int Vh = a.g.Vh;
+#pragma unroll
+        for (int q = 0; q < G; ++q) {
+            const int r = r0 + q;
+            if (r >= R || !on[r])
+                continue;
+            const v2 *uv = (const v2 *)spin_at<P>(a.ap, js[r], Vh);
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                if (owns_colour<LPS>(sub, c))
+                    pr_[q][c] = uv[(int64_t)c * Vh + s];
+        }
+    }
+    // K1, direct form: p (current buffer) and r of systems r0 .. r0 + G - 1 at the partner site
     template <class Args>
     __device__ __forceinline__ void load_k1(const Args &a, const int *js, const bool *cg, const int *pc, int s,
                                             int sub, int r0)
@@ -412,7 +448,7 @@ template <class P, int R, int LPS> struct OwnSite {
             }
         }
     }
-    // K2: p' (new buffer), x and r of systems r0 .. r0 + G - 1 at the own site.
+    // K2: p (recurrence form: the last direction; direct form: p'), x and r of systems r0 .. r0 + G - 1 at the own site.
     // x is read and written once per step, at its own site only: non-temporal
     // accesses keep it from evicting the gathered vectors (32^4 solves: FP16
     // +6%, FP32 +2%, FP64 unchanged; 16^4 within 1%).
@@ -451,7 +487,7 @@ template <class P, int R, int LPS> struct OwnSite {
 // ---- residual recomputation (FP64), one system at one site --------------------------
 // The reliable update of mixed precision and the final true-residual check.
 // K1 side: t = D (x_hi + x_lo) on the other parity.
-template <int LPS, int ROWS, int UNROLL = kRecomputeUnroll>
+template <int LPS, int ROWS>
 __device__ __forceinline__ void recompute_k1(const CgArgs &a, int j, int pout, int s, int sub)
 {
     const int Vh = a.g.Vh;
@@ -470,8 +506,8 @@ __device__ __forceinline__ void recompute_k1(const CgArgs &a, int j, int pout, i
             chi[c] = {v.x, v.y};
         }
     };
-    hop_accumulate<PrecF64, LPS, 1, decltype(load), true, ROWS, UNROLL>(a.g, a.links64[pout], a.nbr[pout],
-                                                                                  pout, s, sub, acc, load);
+    hop_accumulate<PrecF64, LPS, 1, decltype(load), true, ROWS>(a.g, a.links64[pout], a.links64[1 - pout],
+                                                                a.nbr[pout], pout, s, sub, acc, load);
     dbl2 *t = a.tmp + (size_t)j * 3 * Vh;
 #pragma unroll
     for (int c = 0; c < 3; ++c)
@@ -480,9 +516,11 @@ __device__ __forceinline__ void recompute_k1(const CgArgs &a, int j, int pout, i
 }
 
 // K2 side: x_hi += x_lo, x_lo = 0, r = b - m^2 x_hi + D t; this lane's
-// terms of <r,r> are added to nrm.
-template <class P, int LPS, int ROWS, int UNROLL = kRecomputeUnroll>
-__device__ __forceinline__ void recompute_k2(const CgArgs &a, int j, int par, int s, int sub, double m2d, double &nrm)
+// terms of <r,r> are added to nrm and, in the recurrence form with a reliable
+// update (which keeps p), those of <r,p> to nrp.
+template <class P, int LPS, int ROWS>
+__device__ __forceinline__ void recompute_k2(const CgArgs &a, int j, int par, int s, int sub, double m2d, double &nrm,
+                                             double &nrp)
 {
     using real = typename P::real;
     using v2 = typename vec2_of<real>::type;
@@ -490,8 +528,8 @@ __device__ __forceinline__ void recompute_k2(const CgArgs &a, int j, int par, in
     const dbl2 *t = a.tmp + (size_t)j * 3 * Vh;
     cplx<double> acc[1][3] = {{czero<double>(), czero<double>(), czero<double>()}};
     auto load = [&](int, int n, cplx<double> *chi) { PrecF64::load_spinor(t, Vh, n, chi); };
-    hop_accumulate<PrecF64, LPS, 1, decltype(load), true, ROWS, UNROLL>(a.g, a.links64[par], a.nbr[par], par,
-                                                                                  s, sub, acc, load);
+    hop_accumulate<PrecF64, LPS, 1, decltype(load), true, ROWS>(a.g, a.links64[par], a.links64[1 - par], a.nbr[par],
+                                                                par, s, sub, acc, load);
     dbl2 *x = a.xhi[j];
     const dbl2 *b = a.b[j];
     v2 *rv = (v2 *)a.r + (size_t)j * 3 * Vh;
@@ -513,60 +551,204 @@ __device__ __forceinline__ void recompute_k2(const CgArgs &a, int j, int par, in
         const double rim = bv.y - m2d * xv.y + acc[0][c].im;
         rv[o] = v2{(real)rre, (real)rim};
         nrm += rre * rre + rim * rim;
+        if constexpr (P::id != 0 && kRecurrence<P>) {
+            const v2 pv = ((const v2 *)spin_at<P>(a.p[0], j, Vh))[o];
+            nrp += rre * pv.x + rim * pv.y;
+        }
     }
+}
+
+// K1's prologue in small grids: the previous step's totals and states; thread
+// r (< R) advances system r.  Leaves the states in `sst`, mode M_IDLE for
+// systems that do not run.
+template <bool REC, int R>
+__device__ __forceinline__ void k1_prologue(const CgArgs &a, int ver, const StepTile &tl, const int *js,
+                                            const bool *valid, double *lds, SysState *sst)
+{
+    double v[3 * R];
+    load_prologue<R, 3>(a, ver, a.st[ver], a.perm + tl.k0, js, valid, a.nread, sst, v);
+    wave_sums_to_lds<3 * R>(v, lds);
+    const int r = threadIdx.x;
+    if (r < R) {
+        const int j = a.perm[tl.k0 + r];
+        SysState st = sst[r];
+        const bool live = j >= 0 && st.mode != M_IDLE && st.mode != M_DONE;
+        if (live) {
+            const double tot[3] = {wave_total(lds, 3 * r), wave_total(lds, 3 * r + 1), wave_total(lds, 3 * r + 2)};
+            advance<REC>(st, tot);
+        }
+        // the state K2 of this step reads: advanced, or the same idle/done
+        // state (never the stale one of two kernels ago)
+        if (j >= 0 && tl.chunk == 0)
+            a.st[ver ^ 1][j] = st;
+        if (!live)
+            st.mode = M_IDLE;  // not running: nothing to do in this step
+        sst[r] = st;
+    }
+    __syncthreads();
 }
 
 // ---- K1 -----------------------------------------------------------------------------
 
+// Recurrence form: u' = D r + beta u, <u',u'>.
 template <class P, int LPS, int R, int ROWS>
-__global__ void __launch_bounds__(256) k_cg_step1(CgArgs a, int ver)
+__device__ __forceinline__ void step1_recurrence(const CgArgs &a, int ver)
 {
     using real = typename P::real;
     using v2 = typename vec2_of<real>::type;
+    using Own = OwnSite<P, R, LPS>;
     __shared__ double lds[3 * R * 4];
-    const int tpp = a.S / R;
-    const int par = blockIdx.y / tpp, k0 = par * a.S + (blockIdx.y % tpp) * R, pout = 1 - par;
+    __shared__ __align__(16) SysState sst[R];
+    const StepTile tl = step_tile<R>(a, a.g.st * LPS, blockDim.x);
+    const int par = tl.par, k0 = tl.k0, pout = 1 - par;
     const int Vh = a.g.Vh;
     int js[R];
     bool valid[R];
     if (!tile_systems<R>(a.perm + k0, js, valid))
         return;
-    // the previous step's totals and states; thread r (< R) advances system r
-    __shared__ SysState sst[R];
-    {
-        double v[3 * R];
-        load_prologue<R, 3>(a, ver, a.st[ver], a.perm + k0, js, valid, a.nread, sst, v);
-        wave_sums_to_lds<3 * R>(v, lds);
-        const int r = threadIdx.x;
-        if (r < R) {
-            const int j = a.perm[k0 + r];
-            SysState st = sst[r];
-            const bool live = j >= 0 && st.mode != M_IDLE && st.mode != M_DONE;
-            if (live) {
-                const double tot[3] = {wave_total(lds, 3 * r), wave_total(lds, 3 * r + 1), wave_total(lds, 3 * r + 2)};
-                advance(st, tot);
-            }
-            // the state K2 of this step reads: advanced, or the same idle/done
-            // state (never the stale one of two kernels ago)
-            if (j >= 0 && blockIdx.x == 0)
-                a.st[ver ^ 1][j] = st;
-            if (!live)
-                st.mode = M_IDLE;  // not running: nothing to do in this step
-            sst[r] = st;
+    bool cg[R], ru[R], anycg = false, anyru = false;
+    real beta[R];
+    if (a.nread == 0) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const SysState &st = a.st[ver ^ 1][js[r]];
+            const int mode = st.mode;
+            cg[r] = valid[r] && mode == M_CG;
+            ru[r] = valid[r] && mode == M_RU;
+            beta[r] = (real)st.beta;
         }
-        __syncthreads();
+    } else {
+        k1_prologue<true, R>(a, ver, tl, js, valid, lds, sst);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int mode = valid[r] ? uniform(sst[r].mode) : (int)M_IDLE;
+            cg[r] = mode == M_CG;
+            ru[r] = mode == M_RU;
+            beta[r] = (real)uniform(sst[r].beta);
+        }
     }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        anycg |= cg[r];
+        anyru |= ru[r];
+    }
+    if (!anycg && !anyru)
+        return;
+    double nrm[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        nrm[r] = 0.0;
+    const int64_t nthreads = (int64_t)Vh * LPS;
+    if (anycg) {
+        for (int it = 0;; ++it) {
+            const int64_t gt = round_base(it, tl.chunk, tl.nchunks);
+            if (gt - threadIdx.x >= nthreads)
+                break;
+            int s, sub;
+            site_of_thread<LPS>((int)gt, s, sub);
+            if (s >= Vh)
+                continue;
+            cplx<real> acc[R][3];
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    acc[r][c] = czero<real>();
+            auto load = [&](int r, int n, cplx<real> *chi) {
+                const v2 *rv = (const v2 *)a.r + (size_t)js[r] * 3 * Vh;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const v2 t = rv[(int64_t)c * Vh + n];
+                    chi[c] = {t.x, t.y};
+                }
+            };
+            Own own;
+            if constexpr (Own::kBeforeHop)
+                own.load_u(a, js, cg, s, sub, 0);
+            hop_accumulate<P, LPS, R, decltype(load), false, ROWS>(
+                a.g, (const typename P::link_t *)a.links[pout], (const typename P::link_t *)a.links[1 - pout],
+                a.nbr[pout], pout, s, sub, acc, load);
+#pragma unroll
+            for (int g = 0; g < R; g += Own::G) {
+                if constexpr (!Own::kBeforeHop)
+                    own.load_u(a, js, cg, s, sub, g);
+#pragma unroll
+                for (int q = 0; q < Own::G; ++q) {
+                    const int r = g + q;
+                    if (r >= R || !cg[r])
+                        continue;
+                    v2 *uv = (v2 *)spin_at<P>(a.ap, js[r], Vh);
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        if (!owns_colour<LPS>(sub, c))
+                            continue;
+                        // beta = 0 starts from u = 0, whatever the buffer holds
+                        const v2 uo = own.pr_[q][c];
+                        const v2 un = beta[r] != real(0) ? v2{fma(beta[r], uo.x, acc[r][c].re), fma(beta[r], uo.y, acc[r][c].im)}
+                                                         : v2{acc[r][c].re, acc[r][c].im};
+                        uv[(int64_t)c * Vh + s] = un;
+                        nrm[r] += (double)un.x * un.x + (double)un.y * un.y;
+                    }
+                }
+            }
+        }
+    }
+    if (anyru) {
+        for (int it = 0;; ++it) {
+            const int64_t gt = round_base(it, tl.chunk, tl.nchunks);
+            if (gt - threadIdx.x >= nthreads)
+                break;
+            int s, sub;
+            site_of_thread<LPS>((int)gt, s, sub);
+            if (s >= Vh)
+                continue;
+            // residual recomputation in FP64, one system at a time
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (ru[r])
+                    recompute_k1<LPS, ROWS>(a, js[r], pout, s, sub);
+        }
+    }
+    if (!anycg)
+        return;
+    double tot;
+    block_sum_multi<R>(nrm, lds, tot);
+    if (threadIdx.x < R) {
+        const int j = a.perm[k0 + (int)threadIdx.x];
+        if (j >= 0)
+            partial_slot(a, ver ^ 1, j, 0)[tl.chunk] = tot;
+    }
+}
+
+// Direct form (FP16): p' = r + beta p at every gathered neighbour, stored once; u' = D p'.
+template <class P, int LPS, int R, int ROWS>
+__device__ __forceinline__ void step1_direct(const CgArgs &a, int ver)
+{
+    using real = typename P::real;
+    using v2 = typename vec2_of<real>::type;
+    __shared__ double lds[3 * R * 4];
+    const StepTile tl = step_tile<R>(a, a.g.st * LPS, blockDim.x);
+    const int par = tl.par, k0 = tl.k0, pout = 1 - par;
+    const int Vh = a.g.Vh;
+    int js[R];
+    bool valid[R];
+    if (!tile_systems<R>(a.perm + k0, js, valid))
+        return;
+    __shared__ __align__(16) SysState sst[R];
     bool cg[R], ru[R];
     real beta[R];
     int pc[R];
     bool anycg = false, anyru = false;
+    if (a.nread != 0)
+        k1_prologue<false, R>(a, ver, tl, js, valid, lds, sst);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int mode = valid[r] ? uniform(sst[r].mode) : (int)M_IDLE;
+        const SysState &st = a.st[ver ^ 1][js[r]];  // k_cg_scalars has advanced it
+        const int mode = !valid[r] ? (int)M_IDLE : a.nread == 0 ? st.mode : uniform(sst[r].mode);
         cg[r] = mode == M_CG;
         ru[r] = mode == M_RU;
-        beta[r] = (real)uniform(sst[r].beta);
-        pc[r] = uniform(sst[r].pcur);
+        beta[r] = (real)(a.nread == 0 ? st.beta : uniform(sst[r].beta));
+        pc[r] = a.nread == 0 ? st.pcur : uniform(sst[r].pcur);
         anycg |= cg[r];
         anyru |= ru[r];
     }
@@ -579,7 +761,7 @@ __global__ void __launch_bounds__(256) k_cg_step1(CgArgs a, int ver)
     const int64_t nthreads = (int64_t)Vh * LPS;
     if (anycg) {
         for (int it = 0;; ++it) {
-            const int64_t gt = round_base(it, a.remap);
+            const int64_t gt = round_base(it, tl.chunk, tl.nchunks);
             if (gt - threadIdx.x >= nthreads)
                 break;
             int s, sub;
@@ -610,6 +792,7 @@ __global__ void __launch_bounds__(256) k_cg_step1(CgArgs a, int ver)
             if constexpr (Own::kBeforeHop)
                 own.load_k1(a, js, cg, pc, s, sub, 0);
             hop_accumulate<P, LPS, R, decltype(load), false, ROWS>(a.g, (const typename P::link_t *)a.links[pout],
+                                                                   (const typename P::link_t *)a.links[1 - pout],
                                                                    a.nbr[pout], pout, s, sub, acc, load);
 #pragma unroll
             for (int g = 0; g < R; g += Own::G) {
@@ -623,39 +806,22 @@ __global__ void __launch_bounds__(256) k_cg_step1(CgArgs a, int ver)
                     const int j = js[r];
                     void *out = spin_at<P>(a.ap, j, Vh);
                     void *pnew = spin_at<P>(a.p[pc[r] ^ 1], j, Vh);
-                    if constexpr (P::id == 2) {
-                        if (sub == 0) {
-                            P::store_spinor(out, Vh, s, acc[r]);
-                            // the new direction at the partner site (same index, parity par)
-                            cplx<real> pv[3];
-#pragma unroll
-                            for (int c = 0; c < 3; ++c) {
-                                const v2 t = own.rr_[q][c];
-                                pv[c].re = fma(beta[r], own.ps_[q][c].re, t.x);
-                                pv[c].im = fma(beta[r], own.ps_[q][c].im, t.y);
-                            }
-                            P::store_spinor_read_back(pnew, Vh, s, pv);  // pv: the value D will read
-#pragma unroll
-                            for (int c = 0; c < 3; ++c)
-                                nrm[R + r] += (double)pv[c].re * pv[c].re + (double)pv[c].im * pv[c].im;
-                        }
-                    } else {
+                    if (sub == 0) {
+                        P::store_spinor(out, Vh, s, acc[r]);
+                        // the new direction at the partner site (same index, parity par)
+                        cplx<real> pv[3];
 #pragma unroll
                         for (int c = 0; c < 3; ++c) {
-                            if (!owns_colour<LPS>(sub, c))
-                                continue;
-                            const int64_t o = (int64_t)c * Vh + s;
-                            ((v2 *)out)[o] = v2{acc[r][c].re, acc[r][c].im};
-                            const v2 po = own.pr_[q][c], t = own.rr_[q][c];
-                            const v2 pn = v2{fma(beta[r], po.x, t.x), fma(beta[r], po.y, t.y)};
-                            ((v2 *)pnew)[o] = pn;
-                            nrm[R + r] += (double)pn.x * pn.x + (double)pn.y * pn.y;
+                            const v2 t = own.rr_[q][c];
+                            pv[c].re = fma(beta[r], own.ps_[q][c].re, t.x);
+                            pv[c].im = fma(beta[r], own.ps_[q][c].im, t.y);
                         }
-                    }
-                    if (sub == 0) {
+                        P::store_spinor_read_back(pnew, Vh, s, pv);  // pv: the value D will read
 #pragma unroll
-                        for (int c = 0; c < 3; ++c)
+                        for (int c = 0; c < 3; ++c) {
+                            nrm[R + r] += (double)pv[c].re * pv[c].re + (double)pv[c].im * pv[c].im;
                             nrm[r] += (double)acc[r][c].re * acc[r][c].re + (double)acc[r][c].im * acc[r][c].im;
+                        }
                     }
                 }
             }
@@ -663,7 +829,7 @@ __global__ void __launch_bounds__(256) k_cg_step1(CgArgs a, int ver)
     }
     if (anyru) {
         for (int it = 0;; ++it) {
-            const int64_t gt = round_base(it, a.remap);
+            const int64_t gt = round_base(it, tl.chunk, tl.nchunks);
             if (gt - threadIdx.x >= nthreads)
                 break;
             int s, sub;
@@ -685,20 +851,193 @@ __global__ void __launch_bounds__(256) k_cg_step1(CgArgs a, int ver)
         const int r = (int)threadIdx.x % R;
         const int j = a.perm[k0 + r];
         if (j >= 0)
-            partial_slot(a, ver ^ 1, j, (int)threadIdx.x / R)[blockIdx.x] = tot2;
+            partial_slot(a, ver ^ 1, j, (int)threadIdx.x / R)[tl.chunk] = tot2;
     }
+}
+
+template <class P, int LPS, int R, int ROWS>
+__global__ void __launch_bounds__(256) k_cg_step1(CgArgs a, int ver)
+{
+    if constexpr (kRecurrence<P>)
+        step1_recurrence<P, LPS, R, ROWS>(a, ver);
+    else
+        step1_direct<P, LPS, R, ROWS>(a, ver);
 }
 
 // ---- K2 -----------------------------------------------------------------------------
 
+// Recurrence form: p' = r + beta p, x += alpha p', r -= alpha (m^2 p' - D u'),
+// <r,r> and <r,p'>.
 template <class P, int LPS, int R, int ROWS>
-__global__ void __launch_bounds__(256) k_cg_step2(CgArgs a, int ver)
+__device__ __forceinline__ void step2_recurrence(const CgArgs &a, int ver)
+{
+    using real = typename P::real;
+    using v2 = typename vec2_of<real>::type;
+    using Own = OwnSite<P, R, LPS>;
+    __shared__ double lds[2 * R * 4];
+    __shared__ __align__(16) SysState sst[R];
+    const StepTile tl = step_tile<R>(a, a.g.st * LPS, blockDim.x);
+    const int par = tl.par, k0 = tl.k0;
+    const int Vh = a.g.Vh;
+    const int cur = ver ^ 1;  // the state K1 of this step wrote
+    int js[R];
+    bool valid[R];
+    if (!tile_systems<R>(a.perm + k0, js, valid))
+        return;
+    bool cg[R], ru[R], anycg = false, anyru = false;
+    real alpha[R], beta[R], m2[R];
+    int p0[R];
+    if (a.nread == 0) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const SysState &st = a.st[cur][js[r]];
+            const int mode = st.mode;
+            const double al = st.alpha;  // 0: <p',Ap'> was not a positive number
+            cg[r] = valid[r] && mode == M_CG && al != 0.0;
+            ru[r] = valid[r] && mode == M_RU;
+            alpha[r] = (real)al;
+            beta[r] = (real)st.beta;
+            m2[r] = (real)st.mass2;
+        }
+    } else {
+        // alpha from K1's partial sums (slot 0); thread r (< R) decides for system r
+        double v[R];
+        load_prologue<R, 1>(a, cur, a.st[cur], a.perm + k0, js, valid, a.nread, sst, v);
+        wave_sums_to_lds<R>(v, lds);
+        const int t = threadIdx.x;
+        if (t < R) {
+            const double pap = sst[t].mass2 * sst[t].pp + wave_total(lds, t);
+            int mode = a.perm[k0 + t] >= 0 ? sst[t].mode : (int)M_IDLE;
+            if (mode == M_CG) {
+                if (finite_pos(pap))
+                    sst[t].alpha = sst[t].rr / pap;
+                else
+                    mode = M_IDLE;  // K1 of the next step reports the breakdown
+            }
+            sst[t].mode = mode;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int mode = valid[r] ? uniform(sst[r].mode) : (int)M_IDLE;
+            cg[r] = mode == M_CG;
+            ru[r] = mode == M_RU;
+            alpha[r] = (real)uniform(sst[r].alpha);
+            beta[r] = (real)uniform(sst[r].beta);
+            m2[r] = (real)uniform(sst[r].mass2);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        p0[r] = 0;  // p is updated in place
+        anycg |= cg[r];
+        anyru |= ru[r];
+    }
+    if (!anycg && !anyru)
+        return;
+    double nrm[2 * R];  // <r,r>, then <r,p'>
+#pragma unroll
+    for (int r = 0; r < 2 * R; ++r)
+        nrm[r] = 0.0;
+    const int64_t nthreads = (int64_t)Vh * LPS;
+    for (int it = 0; anycg; ++it) {
+        const int64_t gt = round_base(it, tl.chunk, tl.nchunks);
+        if (gt - threadIdx.x >= nthreads)
+            break;
+        int s, sub;
+        site_of_thread<LPS>((int)gt, s, sub);
+        if (s >= Vh)
+            continue;
+        cplx<real> acc[R][3];
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                acc[r][c] = czero<real>();
+        auto load = [&](int r, int n, cplx<real> *chi) {
+            P::load_spinor(spin_at<P>(a.ap, js[r], Vh), Vh, n, chi);
+        };
+        // this site's p, x and r
+        Own own;
+        if constexpr (Own::kBeforeHop)
+            own.load_k2(a, js, cg, p0, s, sub, 0);
+        hop_accumulate<P, LPS, R, decltype(load), false, ROWS>(
+            a.g, (const typename P::link_t *)a.links[par], (const typename P::link_t *)a.links[1 - par], a.nbr[par],
+            par, s, sub, acc, load);
+#pragma unroll
+        for (int g = 0; g < R; g += Own::G) {
+            if constexpr (!Own::kBeforeHop)
+                own.load_k2(a, js, cg, p0, s, sub, g);
+#pragma unroll
+            for (int q = 0; q < Own::G; ++q) {
+                const int r = g + q;
+                if (r >= R || !cg[r])
+                    continue;
+                const int j = js[r];
+                v2 *rv = (v2 *)a.r + (size_t)j * 3 * Vh;
+                v2 *pv = (v2 *)spin_at<P>(a.p[0], j, Vh);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    if (!owns_colour<LPS>(sub, c))
+                        continue;
+                    const int64_t o = (int64_t)c * Vh + s;
+                    v2 rr = own.rr_[q][c];
+                    // beta = 0 starts from p = 0, whatever the buffer holds
+                    const v2 po = v2{own.ps_[q][c].re, own.ps_[q][c].im};
+                    const v2 pn = beta[r] != real(0) ? v2{fma(beta[r], po.x, rr.x), fma(beta[r], po.y, rr.y)} : rr;
+                    pv[o] = pn;
+                    const auto xv = own.xx_[q][c];
+                    if constexpr (P::id == 0)
+                        __builtin_nontemporal_store(dbl2{fma(alpha[r], pn.x, xv.x), fma(alpha[r], pn.y, xv.y)},
+                                                    &a.xhi[j][o]);
+                    else
+                        __builtin_nontemporal_store(flt2{fmaf(alpha[r], pn.x, xv.x), fmaf(alpha[r], pn.y, xv.y)},
+                                                    &a.xlo[(size_t)j * 3 * Vh + o]);
+                    const real apr = m2[r] * pn.x - acc[r][c].re;
+                    const real api = m2[r] * pn.y - acc[r][c].im;
+                    rr.x = fma(-alpha[r], apr, rr.x);
+                    rr.y = fma(-alpha[r], api, rr.y);
+                    rv[o] = rr;
+                    nrm[r] += (double)rr.x * rr.x + (double)rr.y * rr.y;
+                    nrm[R + r] += (double)rr.x * pn.x + (double)rr.y * pn.y;
+                }
+            }
+        }
+    }
+    if (anyru) {
+        for (int it = 0;; ++it) {
+            const int64_t gt = round_base(it, tl.chunk, tl.nchunks);
+            if (gt - threadIdx.x >= nthreads)
+                break;
+            int s, sub;
+            site_of_thread<LPS>((int)gt, s, sub);
+            if (s >= Vh)
+                continue;
+            // residual recomputation in FP64, one system at a time
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (ru[r])
+                    recompute_k2<P, LPS, ROWS>(a, js[r], par, s, sub, a.st[cur][js[r]].mass2, nrm[r], nrm[R + r]);
+        }
+    }
+    double tot;
+    block_sum_multi<2 * R>(nrm, lds, tot);
+    if (threadIdx.x < 2 * R) {
+        const int j = a.perm[k0 + (int)threadIdx.x % R];
+        if (j >= 0)
+            partial_slot(a, cur, j, threadIdx.x < R ? 2 : 1)[tl.chunk] = tot;
+    }
+}
+
+// Direct form (FP16).
+template <class P, int LPS, int R, int ROWS>
+__device__ __forceinline__ void step2_direct(const CgArgs &a, int ver)
 {
     using real = typename P::real;
     using v2 = typename vec2_of<real>::type;
     __shared__ double lds[3 * R * 4];
-    const int tpp = a.S / R;
-    const int par = blockIdx.y / tpp, k0 = par * a.S + (blockIdx.y % tpp) * R;
+    const StepTile tl = step_tile<R>(a, a.g.st * LPS, blockDim.x);
+    const int par = tl.par, k0 = tl.k0;
     const int Vh = a.g.Vh;
     const int cur = ver ^ 1;  // the state K1 of this step wrote
     int js[R];
@@ -706,28 +1045,22 @@ __global__ void __launch_bounds__(256) k_cg_step2(CgArgs a, int ver)
     if (!tile_systems<R>(a.perm + k0, js, valid))
         return;
     // alpha from K1's partial sums (slots 0 and 1); thread r (< R) decides for system r
-    __shared__ SysState sst[R];
-    {
+    __shared__ __align__(16) SysState sst[R];
+    if (a.nread != 0) {
         double v[2 * R];
         load_prologue<R, 2>(a, cur, a.st[cur], a.perm + k0, js, valid, a.nread, sst, v);
         wave_sums_to_lds<2 * R>(v, lds);
         const int r = threadIdx.x;
         if (r < R) {
-            const int j = a.perm[k0 + r];
-            SysState st = sst[r];
-            int mode = M_IDLE;
-            double alpha = 0.0;
-            if (j >= 0 && st.mode == M_CG) {
-                const double pap = st.mass2 * wave_total(lds, 2 * r + 1) + wave_total(lds, 2 * r);
-                if (finite_pos(pap)) {  // otherwise K1 of the next step reports the breakdown
-                    mode = M_CG;
-                    alpha = st.rr / pap;
-                }
-            } else if (j >= 0 && st.mode == M_RU) {
-                mode = M_RU;
+            int mode = a.perm[k0 + r] >= 0 ? sst[r].mode : (int)M_IDLE;
+            if (mode == M_CG) {
+                const double pap = sst[r].mass2 * wave_total(lds, 2 * r + 1) + wave_total(lds, 2 * r);
+                if (finite_pos(pap))
+                    sst[r].alpha = sst[r].rr / pap;
+                else
+                    mode = M_IDLE;  // K1 of the next step reports the breakdown
             }
             sst[r].mode = mode;
-            sst[r].alpha = alpha;
         }
         __syncthreads();
     }
@@ -737,17 +1070,21 @@ __global__ void __launch_bounds__(256) k_cg_step2(CgArgs a, int ver)
     bool anycg = false, anyru = false;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int mode = valid[r] ? uniform(sst[r].mode) : (int)M_IDLE;
-        cg[r] = mode == M_CG;
+        const SysState &st = a.st[cur][js[r]];
+        const bool glob = a.nread == 0;
+        const int mode = !valid[r] ? (int)M_IDLE : glob ? st.mode : uniform(sst[r].mode);
+        const double al = glob ? st.alpha : uniform(sst[r].alpha);
+        cg[r] = mode == M_CG && al != 0.0;  // 0: <p',Ap'> was not a positive number
         ru[r] = mode == M_RU;
-        alpha[r] = (real)uniform(sst[r].alpha);
-        m2[r] = (real)uniform(sst[r].mass2);
-        pnew[r] = uniform(sst[r].pcur) ^ 1;  // p' written by K1 of this step
+        alpha[r] = (real)al;
+        m2[r] = (real)(glob ? st.mass2 : uniform(sst[r].mass2));
+        pnew[r] = (glob ? st.pcur : uniform(sst[r].pcur)) ^ 1;  // p' written by K1 of this step
         anycg |= cg[r];
         anyru |= ru[r];
     }
     if (!anycg && !anyru)
         return;
+    double nrp = 0.0;  // not summed in this form
     double nrm[R];
 #pragma unroll
     for (int r = 0; r < R; ++r)
@@ -755,7 +1092,7 @@ __global__ void __launch_bounds__(256) k_cg_step2(CgArgs a, int ver)
     const int64_t nthreads = (int64_t)Vh * LPS;
     if (anycg) {
         for (int it = 0;; ++it) {
-            const int64_t gt = round_base(it, a.remap);
+            const int64_t gt = round_base(it, tl.chunk, tl.nchunks);
             if (gt - threadIdx.x >= nthreads)
                 break;
             int s, sub;
@@ -777,6 +1114,7 @@ __global__ void __launch_bounds__(256) k_cg_step2(CgArgs a, int ver)
             if constexpr (Own::kBeforeHop)
                 own.load_k2(a, js, cg, pnew, s, sub, 0);
             hop_accumulate<P, LPS, R, decltype(load), false, ROWS>(a.g, (const typename P::link_t *)a.links[par],
+                                                                   (const typename P::link_t *)a.links[1 - par],
                                                                    a.nbr[par], par, s, sub, acc, load);
 #pragma unroll
             for (int g = 0; g < R; g += Own::G) {
@@ -795,15 +1133,9 @@ __global__ void __launch_bounds__(256) k_cg_step2(CgArgs a, int ver)
                             continue;
                         const cplx<real> pv = own.ps_[q][c];
                         const int64_t o = (int64_t)c * Vh + s;
-                        if constexpr (P::id == 0) {
-                            const dbl2 xv = own.xx_[q][c];
-                            __builtin_nontemporal_store(dbl2{fma(alpha[r], pv.re, xv.x), fma(alpha[r], pv.im, xv.y)},
-                                                        &a.xhi[j][o]);
-                        } else {
-                            const flt2 xv = own.xx_[q][c];
-                            __builtin_nontemporal_store(flt2{fmaf(alpha[r], pv.re, xv.x), fmaf(alpha[r], pv.im, xv.y)},
-                                                        &a.xlo[(size_t)j * 3 * Vh + o]);
-                        }
+                        const flt2 xv = own.xx_[q][c];
+                        __builtin_nontemporal_store(flt2{fmaf(alpha[r], pv.re, xv.x), fmaf(alpha[r], pv.im, xv.y)},
+                                                    &a.xlo[(size_t)j * 3 * Vh + o]);
                         const real apr = m2[r] * pv.re - acc[r][c].re;
                         const real api = m2[r] * pv.im - acc[r][c].im;
                         v2 rr = own.rr_[q][c];
@@ -818,7 +1150,7 @@ __global__ void __launch_bounds__(256) k_cg_step2(CgArgs a, int ver)
     }
     if (anyru) {
         for (int it = 0;; ++it) {
-            const int64_t gt = round_base(it, a.remap);
+            const int64_t gt = round_base(it, tl.chunk, tl.nchunks);
             if (gt - threadIdx.x >= nthreads)
                 break;
             int s, sub;
@@ -829,7 +1161,7 @@ __global__ void __launch_bounds__(256) k_cg_step2(CgArgs a, int ver)
 #pragma unroll
             for (int r = 0; r < R; ++r)
                 if (ru[r])
-                    recompute_k2<P, LPS, ROWS>(a, js[r], par, s, sub, uniform(sst[r].mass2), nrm[r]);
+                    recompute_k2<P, LPS, ROWS>(a, js[r], par, s, sub, a.st[cur][js[r]].mass2, nrm[r], nrp);
         }
     }
     double tot2;
@@ -837,8 +1169,17 @@ __global__ void __launch_bounds__(256) k_cg_step2(CgArgs a, int ver)
     if (threadIdx.x < R) {
         const int j = a.perm[k0 + (int)threadIdx.x];
         if (j >= 0)
-            partial_slot(a, cur, j, 2)[blockIdx.x] = tot2;
+            partial_slot(a, cur, j, 2)[tl.chunk] = tot2;
     }
+}
+
+template <class P, int LPS, int R, int ROWS>
+__global__ void __launch_bounds__(256) k_cg_step2(CgArgs a, int ver)
+{
+    if constexpr (kRecurrence<P>)
+        step2_recurrence<P, LPS, R, ROWS>(a, ver);
+    else
+        step2_direct<P, LPS, R, ROWS>(a, ver);
 }
 
 // ---- initialisation: x = 0, r = b, p = r; <b,b> into slot 2 of buffer 0 -------------
@@ -859,7 +1200,7 @@ __global__ void __launch_bounds__(256) k_cg_init(CgArgs a, int lps)
     // one thread per site; the grid covers Vh * lps threads per round like the step kernels
     const int64_t nthreads = (int64_t)Vh * lps;
     for (int it = 0;; ++it) {
-        const int64_t gt = round_base(it, a.remap);
+        const int64_t gt = round_base(it, blockIdx.x, gridDim.x);
         if (gt - threadIdx.x >= nthreads)
             break;
         if (gt % lps)
@@ -891,22 +1232,23 @@ __global__ void __launch_bounds__(256) k_cg_init(CgArgs a, int lps)
 }
 
 // ---- tuning probe: out_r = D in_r for R systems, no reductions -------------------
-// blockIdx.y = tile; tiles alternate output parity like the CG kernels' tiles.
+// Tiles alternate output parity like the CG kernels' tiles (block_tile).
 
 template <class P, int LPS, int R, int ROWS>
 __global__ void __launch_bounds__(256) k_hop_probe(Geom g, const void *links, const int32_t *nbr, const void *in,
-                                                    void *out, int remap)
+                                                    void *out, int ntiles, int remap)
 {
     using real = typename P::real;
     const int Vh = g.Vh;
-    const int pout = blockIdx.y & 1;
+    const BlockTile tl = block_tile(ntiles, remap, g.st * LPS / (int)blockDim.x);
+    const int pout = tl.tile & 1;
     int s, sub;
-    site_of_thread<LPS>(logical_block(blockIdx.x, gridDim.x, remap) * blockDim.x + threadIdx.x, s, sub);
+    site_of_thread<LPS>(tl.chunk * blockDim.x + threadIdx.x, s, sub);
     if (s >= Vh)
         return;
     const size_t vb = (size_t)Vh * P::spinor_bytes;
-    const char *inb = (const char *)in + (size_t)blockIdx.y * R * vb;
-    char *outb = (char *)out + (size_t)blockIdx.y * R * vb;
+    const char *inb = (const char *)in + (size_t)tl.tile * R * vb;
+    char *outb = (char *)out + (size_t)tl.tile * R * vb;
     cplx<real> acc[R][3];
 #pragma unroll
     for (int r = 0; r < R; ++r)
@@ -914,9 +1256,11 @@ __global__ void __launch_bounds__(256) k_hop_probe(Geom g, const void *links, co
         for (int c = 0; c < 3; ++c)
             acc[r][c] = czero<real>();
     auto load = [&](int r, int n, cplx<real> *chi) { P::load_spinor(inb + r * vb, Vh, n, chi); };
-    const typename P::link_t *lk = (const typename P::link_t *)links + link_parity_entries(ROWS, Vh) * pout;
-    hop_accumulate<P, LPS, R, decltype(load), false, ROWS>(g, lk, nbr ? nbr + (size_t)pout * 8 * Vh : nullptr, pout, s,
-                                                           sub, acc, load);
+    const typename P::link_t *lk = (const typename P::link_t *)links;
+    const int64_t lp = link_parity_entries(ROWS, Vh);
+    hop_accumulate<P, LPS, R, decltype(load), false, ROWS>(g, lk + lp * pout, lk + lp * (1 - pout),
+                                                           nbr ? nbr + (size_t)pout * 8 * Vh : nullptr, pout, s, sub,
+                                                           acc, load);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         void *o = outb + r * vb;

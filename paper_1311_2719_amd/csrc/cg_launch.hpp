@@ -14,9 +14,9 @@ struct CgLaunchTable {
     hipError_t (*step1)(int lps, int R, dim3 grid, dim3 block, hipStream_t s, const CgArgs &a, int ver);
     hipError_t (*step2)(int lps, int R, dim3 grid, dim3 block, hipStream_t s, const CgArgs &a, int ver);
     hipError_t (*init)(dim3 grid, dim3 block, hipStream_t s, const CgArgs &a, int lps);
-    // out_r = D in_r over grid.y tiles of R right-hand sides (tiles alternate parity)
+    // out_r = D in_r over ntiles tiles of R right-hand sides (tiles alternate parity); grid.x = chunks x ntiles
     hipError_t (*probe)(int lps, int R, dim3 grid, dim3 block, hipStream_t s, const Geom &g, const void *links,
-                        const int32_t *nbr, const void *in, void *out, int remap);
+                        const int32_t *nbr, const void *in, void *out, int ntiles, int remap);
     const int *rtiles;  // right-hand-side tile sizes compiled for this precision
     int n_rtiles;
     // shared-link tiles (FP32 / FP16 working precision; null otherwise): W
@@ -52,9 +52,9 @@ template <class P, int R, int ROWS> struct RLaunch {
         return hipGetLastError();
     }
     static hipError_t probe(int lps, dim3 grid, dim3 block, hipStream_t s, const Geom &g, const void *links,
-                            const int32_t *nbr, const void *in, void *out, int remap)
+                            const int32_t *nbr, const void *in, void *out, int ntiles, int remap)
     {
-        STAG_LPS_SWITCH(k_hop_probe, P, R, ROWS, g, links, nbr, in, out, remap);
+        STAG_LPS_SWITCH(k_hop_probe, P, R, ROWS, g, links, nbr, in, out, ntiles, remap);
         return hipGetLastError();
     }
 };
@@ -85,10 +85,11 @@ template <class P, int ROWS, int... Rs> struct TileTable {
         return e;
     }
     static hipError_t probe(int lps, int R, dim3 grid, dim3 block, hipStream_t s, const Geom &g, const void *links,
-                            const int32_t *nbr, const void *in, void *out, int remap)
+                            const int32_t *nbr, const void *in, void *out, int ntiles, int remap)
     {
         hipError_t e = hipErrorInvalidValue;
-        (void)((R == Rs && ((e = RLaunch<P, Rs, ROWS>::probe(lps, grid, block, s, g, links, nbr, in, out, remap)),
+        (void)((R == Rs && ((e = RLaunch<P, Rs, ROWS>::probe(lps, grid, block, s, g, links, nbr, in, out, ntiles,
+                                                               remap)),
                             true)) ||
                ...);
         return e;

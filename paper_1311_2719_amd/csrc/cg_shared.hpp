@@ -16,7 +16,8 @@
 // registers of RR systems only.
 //
 // The step arithmetic is that of k_cg_step1 / k_cg_step2 (the loop of the
-// paper's Sec. 4 with the mass explicit): same products, same storage
+// paper's Sec. 4 with the mass explicit; FP32 the recurrence of u = D p, FP16
+// the direct form): same products, same storage
 // formats, same state machine (advance()); only the summation order of the
 // partial sums differs (each system's sums stay in one wavefront: lane sums
 // over the chunks a block visits, then the wavefront sum).
@@ -45,36 +46,67 @@ constexpr int kSharedMinWaves = 1;
 
 __device__ __forceinline__ int chunk_link_index(int k, int d, int i) { return (k * 8 + d) * kLdsRow + i; }
 
-// Stage the links of output sites [s0, s0 + 64) (parity p_out) into lk.
-// Consecutive threads take consecutive stored entries (site tile, direction,
-// site), so every global load of a wavefront reads 512 contiguous bytes.  A
-// block reads its links once: non-temporal loads leave the L2 to the
-// gathered vectors (24^4, 12 systems per parity: 2% per step).
-template <class P, int ROWS>
-__device__ __forceinline__ void stage_chunk_links(const Geom &g, const typename P::link_t *__restrict__ links,
-                                                  int p_out, int s0, flt2 *lk)
-{
-    const int Vh = g.Vh;
-    const int n = (Vh - s0 >= kChunk ? kChunk : Vh - s0) * 8;  // Vh - s0 is a multiple of 8
-    const typename P::link_t *base = links + (int64_t)(s0 >> 3) * 64;
-    for (int it = threadIdx.x; it < n; it += blockDim.x) {
-        const int d = (it >> 3) & 7;
-        const int i = (it >> 6) * 8 + (it & 7);
-        cplx<float> U[9];
-#pragma unroll
-        for (int k = 0; k < 3 * ROWS; ++k) {
-            const auto v = __builtin_nontemporal_load(base + (int64_t)k * 8 * Vh + it);
-            U[k] = {(float)v.x, (float)v.y};
-        }
-        if constexpr (ROWS == 2) {
-            const SiteCoord c = decode_site(g, p_out, s0 + i);
-            third_row(U, folded_negative(g, c, d) ? -2.f : 2.f);
-        }
-#pragma unroll
-        for (int k = 0; k < 9; ++k)
-            lk[chunk_link_index(k, d, i)] = flt2{U[k].re, U[k].im};
+// Staging of the matrices of the 8 hops of output sites [s0, s0 + 64) (parity
+// p_out) into lk: W_mu(s) for the forward hops, -W_mu(s - mu)^dagger for the
+// backward ones.  A wavefront takes one hop of the 64 sites, so its loads and
+// its LDS stores are contiguous (the backward neighbours of 64 consecutive
+// sites are consecutive but for the x direction's and the boundaries' steps).
+// Two parts, so that the step's prologue runs while the first loads are in
+// flight: load() starts the loads of a wavefront's first kPre hops, store()
+// writes them to LDS and does the rest.
+template <class P, int ROWS, int W> struct ChunkLinks {
+    static constexpr int kPre = (8 + W - 1) / W <= 2 ? (8 + W - 1) / W : 1;
+    SiteCoord c;
+    int s;
+    cplx<float> U[kPre][9];
+
+    static __device__ __forceinline__ int wave() { return uniform((int)(threadIdx.x >> 6)); }
+
+    __device__ __forceinline__ void load_hop(const Geom &g, const typename P::link_t *lout,
+                                             const typename P::link_t *lin, int d, cplx<float> (&u)[9])
+    {
+        const bool back = d >= 4;
+        load_link_rows<P, ROWS, false>(
+            (back ? lin : lout) + link_offset(ROWS, d & 3, back ? neighbour(g, c, s, d) : s), u);
     }
-}
+    __device__ __forceinline__ void load(const Geom &g, const typename P::link_t *lout, const typename P::link_t *lin,
+                                         int p_out, int s0)
+    {
+        s = s0 + (threadIdx.x & 63);
+        s = s < g.Vh ? s : g.Vh - 1;  // past the end: staged, never used
+        c = decode_site(g, p_out, s);
+#pragma unroll
+        for (int k = 0; k < kPre; ++k)
+            if (wave() + k * W < 8)
+                load_hop(g, lout, lin, wave() + k * W, U[k]);
+    }
+    __device__ __forceinline__ void store_hop(const Geom &g, int d, cplx<float> (&u)[9], flt2 *lk)
+    {
+        const bool back = d >= 4;
+        if constexpr (ROWS == 2)
+            third_row(u, folded_negative(g, c, d) != back ? -2.f : 2.f);
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                const cplx<float> f = u[a * 3 + b], t = u[b * 3 + a];
+                lk[chunk_link_index(a * 3 + b, d, threadIdx.x & 63)] = back ? flt2{-t.re, t.im} : flt2{f.re, f.im};
+            }
+    }
+    __device__ __forceinline__ void store(const Geom &g, const typename P::link_t *lout, const typename P::link_t *lin,
+                                          flt2 *lk)
+    {
+#pragma unroll
+        for (int k = 0; k < kPre; ++k)
+            if (wave() + k * W < 8)
+                store_hop(g, wave() + k * W, U[k], lk);
+        for (int d = wave() + kPre * W; d < 8; d += W) {
+            cplx<float> u[9];
+            load_hop(g, lout, lin, d, u);
+            store_hop(g, d, u, lk);
+        }
+    }
+};
 
 // acc[q][a] += sum_d L_d(s)[a][b] chi_qd[b] for the RR systems of a
 // wavefront, the links from the staged chunk (lane i = site s0 + i),
@@ -124,7 +156,7 @@ __device__ __forceinline__ void hop_shared(const Geom &g, const int32_t *nbr, in
 }
 
 // Totals of slots [0, NS) of system j's partial sums (the previous kernel's
-// per-block sums, or the reduction kernel's totals), formed by one wavefront:
+// per-block sums), formed by one wavefront:
 // lane l adds entries l, l + 64, ... in order, then the wavefront sum.
 template <int NS> __device__ __forceinline__ void wave_prologue_sums(const CgArgs &a, int buf, int j, double (&t)[NS])
 {
@@ -136,17 +168,16 @@ template <int NS> __device__ __forceinline__ void wave_prologue_sums(const CgArg
     for (int i = lane; i < a.nread; i += 64)
 #pragma unroll
         for (int k = 0; k < NS; ++k)
-            v[k] += psum_slot(a, buf, j, k)[i];
+            v[k] += partial_slot(a, buf, j, k)[i];
 #pragma unroll
     for (int k = 0; k < NS; ++k)
         t[k] = wave_sum(v[k]);
 }
 
 // First site of the chunk a block takes in round `it`, or -1 past the end.
-__device__ __forceinline__ int chunk_start(int it, int Vh, int remap)
+__device__ __forceinline__ int chunk_start(int it, int Vh, const StepTile &tl)
 {
-    const int64_t ch = (int64_t)it * gridDim.x + logical_block(blockIdx.x, gridDim.x, remap);
-    const int64_t s0 = ch * kChunk;
+    const int64_t s0 = ((int64_t)it * tl.nchunks + tl.chunk) * kChunk;
     return s0 < Vh ? (int)s0 : -1;
 }
 
@@ -165,12 +196,21 @@ __global__ void __launch_bounds__(64 * W, kSharedMinWaves) k_cg_shared1(CgArgs a
     using v2 = typename vec2_of<real>::type;
     __shared__ flt2 lk[9 * 8 * kLdsRow];
     __shared__ int modes[R];
-    const int tpp = a.S / R;
-    const int par = blockIdx.y / tpp, k0 = par * a.S + (blockIdx.y % tpp) * R, pout = 1 - par;
+    const StepTile tl = step_tile<R>(a, a.g.st, kChunk);
+    const int par = tl.par, k0 = tl.k0, pout = 1 - par;
     const int Vh = a.g.Vh;
     // the wavefront index is the same in every lane: kept in a scalar register,
     // so that its systems, their states and pointers stay scalar too
     const int w = uniform((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    bool anyplace = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        anyplace |= a.perm[k0 + r] >= 0;
+    if (!anyplace)
+        return;
+    const auto *lout = (const typename P::link_t *)a.links[pout], *lin = (const typename P::link_t *)a.links[1 - pout];
+    ChunkLinks<P, ROWS, W> cl;
+    cl.load(a.g, lout, lin, pout, chunk_start(0, Vh, tl));  // every block has a first chunk
     // prologue: this wavefront advances its own systems over the previous step
     int js[RR];
     bool cg[RR], ru[RR];
@@ -181,15 +221,20 @@ __global__ void __launch_bounds__(64 * W, kSharedMinWaves) k_cg_shared1(CgArgs a
         const int j = a.perm[k0 + w * RR + q];
         int mode = M_IDLE, p = 0;
         double b = 0.0;
-        if (j >= 0) {
+        if (j >= 0 && a.nread == 0) {  // k_cg_scalars has advanced the state
+            const SysState &st = a.st[ver ^ 1][j];
+            mode = st.mode;
+            b = st.beta;
+            p = st.pcur;
+        } else if (j >= 0) {
             double t[3];
             wave_prologue_sums<3>(a, ver, j, t);
             SysState st = a.st[ver][j];
             const bool live = st.mode != M_IDLE && st.mode != M_DONE;
             if (live)
-                advance(st, t);
+                advance<kRecurrence<P>>(st, t);
             // the state K2 of this step reads: advanced, or the same idle/done state
-            if (blockIdx.x == 0 && lane == 0)
+            if (tl.chunk == 0 && lane == 0)
                 a.st[ver ^ 1][j] = st;
             mode = live ? uniform(st.mode) : (int)M_IDLE;
             b = uniform(st.beta);
@@ -219,24 +264,28 @@ __global__ void __launch_bounds__(64 * W, kSharedMinWaves) k_cg_shared1(CgArgs a
     // every place gathers in bounds: an empty place reads system 0's vectors
     const v2 *rv[RR];
     const void *pold[RR];
+    void *uv[RR];
 #pragma unroll
     for (int q = 0; q < RR; ++q) {
         const int jj = js[q] >= 0 ? js[q] : 0;
         rv[q] = (const v2 *)a.r + (size_t)jj * 3 * Vh;
-        pold[q] = spin_at<P>(a.p[pc[q]], jj, Vh);
+        pold[q] = spin_at<P>(a.p[kRecurrence<P> ? 0 : pc[q]], jj, Vh);
+        uv[q] = spin_at<P>(a.ap, jj, Vh);
     }
     double nrm_ap[RR], nrm_p[RR];
 #pragma unroll
     for (int q = 0; q < RR; ++q)
         nrm_ap[q] = nrm_p[q] = 0.0;
     for (int it = 0;; ++it) {
-        const int s0 = chunk_start(it, Vh, a.remap);
+        const int s0 = chunk_start(it, Vh, tl);
         if (s0 < 0)
             break;
         if (anycg) {
-            if (it > 0)
+            if (it > 0) {
                 __syncthreads();  // every wavefront is done with the previous chunk's links
-            stage_chunk_links<P, ROWS>(a.g, (const typename P::link_t *)a.links[pout], pout, s0, lk);
+                cl.load(a.g, lout, lin, pout, s0);
+            }
+            cl.store(a.g, lout, lin, lk);
             __syncthreads();
         }
         const int s = s0 + lane;
@@ -249,55 +298,88 @@ __global__ void __launch_bounds__(64 * W, kSharedMinWaves) k_cg_shared1(CgArgs a
 #pragma unroll
                 for (int c = 0; c < 3; ++c)
                     acc[q][c] = czero<float>();
-            // the partner site's p and r (same index, parity par): before the
-            // gathers for a single system, after them for several
-            cplx<real> po[RR][3];
-            v2 ro[RR][3];
-            auto own = [&]() {
+            if constexpr (kRecurrence<P>) {
+                // u at this site: before the gathers for a single system, after them for several
+                cplx<real> uo[RR][3];
+                auto own = [&]() {
+#pragma unroll
+                    for (int q = 0; q < RR; ++q)
+                        P::load_spinor(uv[q], Vh, s, uo[q]);
+                };
+                if constexpr (RR == 1)
+                    own();
+                auto load = [&](int q, int n, cplx<float> *chi) {
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        const v2 t = rv[q][(int64_t)c * Vh + n];
+                        chi[c] = {t.x, t.y};
+                    }
+                };
+                hop_shared<RR>(a.g, a.nbr[pout], pout, s, lane, lk, acc, load);
+                if constexpr (RR > 1)
+                    own();
 #pragma unroll
                 for (int q = 0; q < RR; ++q) {
-                    P::load_spinor(pold[q], Vh, s, po[q]);
+                    if (!cg[q])
+                        continue;
+                    cplx<real> un[3];
 #pragma unroll
-                    for (int c = 0; c < 3; ++c)
-                        ro[q][c] = rv[q][(int64_t)c * Vh + s];
+                    for (int c = 0; c < 3; ++c) {
+                        // beta = 0 starts from u = 0, whatever the buffer holds
+                        un[c].re = beta[q] != 0.f ? fmaf(beta[q], uo[q][c].re, acc[q][c].re) : acc[q][c].re;
+                        un[c].im = beta[q] != 0.f ? fmaf(beta[q], uo[q][c].im, acc[q][c].im) : acc[q][c].im;
+                        nrm_ap[q] += (double)un[c].re * un[c].re + (double)un[c].im * un[c].im;
+                    }
+                    P::store_spinor(uv[q], Vh, s, un);
                 }
-            };
-            if constexpr (RR == 1)
-                own();
-            auto load = [&](int q, int n, cplx<float> *chi) {
-                cplx<real> pv[3];
-                P::load_spinor(pold[q], Vh, n, pv);
+            } else {
+                // the partner site's p and r (same index, parity par): before the
+                // gathers for a single system, after them for several
+                cplx<real> po[RR][3];
+                v2 ro[RR][3];
+                auto own = [&]() {
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    const v2 t = rv[q][(int64_t)c * Vh + n];
-                    chi[c].re = fma(beta[q], pv[c].re, t.x);
-                    chi[c].im = fma(beta[q], pv[c].im, t.y);
-                }
-            };
-            hop_shared<RR>(a.g, a.nbr[pout], pout, s, lane, lk, acc, load);
-            if constexpr (RR > 1)
-                own();
+                    for (int q = 0; q < RR; ++q) {
+                        P::load_spinor(pold[q], Vh, s, po[q]);
 #pragma unroll
-            for (int q = 0; q < RR; ++q) {
-                if (!cg[q])
-                    continue;
-                const int j = js[q];
-                cplx<real> pn[3];
+                        for (int c = 0; c < 3; ++c)
+                            ro[q][c] = rv[q][(int64_t)c * Vh + s];
+                    }
+                };
+                if constexpr (RR == 1)
+                    own();
+                auto load = [&](int q, int n, cplx<float> *chi) {
+                    cplx<real> pv[3];
+                    P::load_spinor(pold[q], Vh, n, pv);
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    pn[c].re = fma(beta[q], po[q][c].re, ro[q][c].x);
-                    pn[c].im = fma(beta[q], po[q][c].im, ro[q][c].y);
-                }
-                P::store_spinor(spin_at<P>(a.ap, j, Vh), Vh, s, acc[q]);
-                void *pnew = spin_at<P>(a.p[pc[q] ^ 1], j, Vh);
-                if constexpr (P::id == 2)
+                    for (int c = 0; c < 3; ++c) {
+                        const v2 t = rv[q][(int64_t)c * Vh + n];
+                        chi[c].re = fma(beta[q], pv[c].re, t.x);
+                        chi[c].im = fma(beta[q], pv[c].im, t.y);
+                    }
+                };
+                hop_shared<RR>(a.g, a.nbr[pout], pout, s, lane, lk, acc, load);
+                if constexpr (RR > 1)
+                    own();
+#pragma unroll
+                for (int q = 0; q < RR; ++q) {
+                    if (!cg[q])
+                        continue;
+                    const int j = js[q];
+                    cplx<real> pn[3];
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        pn[c].re = fma(beta[q], po[q][c].re, ro[q][c].x);
+                        pn[c].im = fma(beta[q], po[q][c].im, ro[q][c].y);
+                    }
+                    P::store_spinor(spin_at<P>(a.ap, j, Vh), Vh, s, acc[q]);
+                    void *pnew = spin_at<P>(a.p[pc[q] ^ 1], j, Vh);
                     P::store_spinor_read_back(pnew, Vh, s, pn);  // pn: the value D will read
-                else
-                    P::store_spinor(pnew, Vh, s, pn);
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    nrm_p[q] += (double)pn[c].re * pn[c].re + (double)pn[c].im * pn[c].im;
-                    nrm_ap[q] += (double)acc[q][c].re * acc[q][c].re + (double)acc[q][c].im * acc[q][c].im;
+                    for (int c = 0; c < 3; ++c) {
+                        nrm_p[q] += (double)pn[c].re * pn[c].re + (double)pn[c].im * pn[c].im;
+                        nrm_ap[q] += (double)acc[q][c].re * acc[q][c].re + (double)acc[q][c].im * acc[q][c].im;
+                    }
                 }
             }
         }
@@ -309,14 +391,14 @@ __global__ void __launch_bounds__(64 * W, kSharedMinWaves) k_cg_shared1(CgArgs a
             continue;
         const int j = a.perm[k0 + r];
         for (int it = 0;; ++it) {
-            const int s0 = chunk_start(it, Vh, a.remap);
+            const int s0 = chunk_start(it, Vh, tl);
             if (s0 < 0)
                 break;
             for (int t = threadIdx.x; t < kChunk * 8; t += blockDim.x) {  // whole wavefronts
                 int sl, sub;
                 site_of_thread<8>(t, sl, sub);
                 if (s0 + sl < Vh)
-                    recompute_k1<8, ROWS, 1>(a, j, pout, s0 + sl, sub);
+                    recompute_k1<8, ROWS>(a, j, pout, s0 + sl, sub);
             }
         }
     }
@@ -326,10 +408,13 @@ __global__ void __launch_bounds__(64 * W, kSharedMinWaves) k_cg_shared1(CgArgs a
     for (int q = 0; q < RR; ++q) {
         if (js[q] < 0)
             continue;
-        const double tap = wave_sum(nrm_ap[q]), tpp2 = wave_sum(nrm_p[q]);
-        if (lane == 0) {
-            partial_slot(a, ver ^ 1, js[q], 0)[blockIdx.x] = tap;
-            partial_slot(a, ver ^ 1, js[q], 1)[blockIdx.x] = tpp2;
+        const double tap = wave_sum(nrm_ap[q]);
+        if (lane == 0)
+            partial_slot(a, ver ^ 1, js[q], 0)[tl.chunk] = tap;
+        if constexpr (!kRecurrence<P>) {
+            const double tpp2 = wave_sum(nrm_p[q]);
+            if (lane == 0)
+                partial_slot(a, ver ^ 1, js[q], 1)[tl.chunk] = tpp2;
         }
     }
 }
@@ -345,34 +430,50 @@ __global__ void __launch_bounds__(64 * W, kSharedMinWaves) k_cg_shared2(CgArgs a
     using v2 = typename vec2_of<real>::type;
     __shared__ flt2 lk[9 * 8 * kLdsRow];
     __shared__ int modes[R];
-    __shared__ double red[W];
-    const int tpp = a.S / R;
-    const int par = blockIdx.y / tpp, k0 = par * a.S + (blockIdx.y % tpp) * R;
+    __shared__ double red[2 * W];
+    const StepTile tl = step_tile<R>(a, a.g.st, kChunk);
+    const int par = tl.par, k0 = tl.k0;
     const int Vh = a.g.Vh;
     const int cur = ver ^ 1;  // the state K1 of this step wrote
     // the wavefront index is the same in every lane: kept in a scalar register,
     // so that its systems, their states and pointers stay scalar too
     const int w = uniform((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-    // alpha from K1's partial sums (slots 0 and 1)
+    bool anyplace = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        anyplace |= a.perm[k0 + r] >= 0;
+    if (!anyplace)
+        return;
+    const auto *lout = (const typename P::link_t *)a.links[par], *lin = (const typename P::link_t *)a.links[1 - par];
+    ChunkLinks<P, ROWS, W> cl;
+    cl.load(a.g, lout, lin, par, chunk_start(0, Vh, tl));  // every block has a first chunk
+    // alpha from K1's partial sums (slot 0; FP16: slots 0 and 1)
+    constexpr int NS = kRecurrence<P> ? 1 : 2;
     int js[RR], pn_buf[RR];
     bool cg[RR], ru[RR];
-    real al[RR], m2r[RR];
+    real al[RR], be[RR], m2r[RR];
     double m2[RR];
 #pragma unroll
     for (int q = 0; q < RR; ++q) {
         const int j = a.perm[k0 + w * RR + q];
         int mode = M_IDLE, pb = 0;
-        double alpha = 0.0, mass2 = 0.0;
+        double alpha = 0.0, beta = 0.0, mass2 = 0.0;
         if (j >= 0) {
             const SysState &st = a.st[cur][j];
             const int smode = st.mode;
             const double rr = st.rr;
             const int pcur = st.pcur;
             mass2 = st.mass2;
-            double t[2];
-            wave_prologue_sums<2>(a, cur, j, t);
-            if (smode == M_CG) {
-                const double pap = mass2 * t[1] + t[0];
+            beta = uniform(st.beta);
+            const double pp = st.pp;
+            double t[NS];
+            if (a.nread != 0)
+                wave_prologue_sums<NS>(a, cur, j, t);
+            if (smode == M_CG && a.nread == 0) {
+                alpha = st.alpha;  // 0: <p',Ap'> was not a positive number
+                mode = alpha != 0.0 ? (int)M_CG : (int)M_IDLE;
+            } else if (smode == M_CG) {
+                const double pap = mass2 * (kRecurrence<P> ? pp : t[NS - 1]) + t[0];
                 if (finite_pos(pap)) {  // otherwise K1 of the next step reports the breakdown
                     mode = M_CG;
                     alpha = rr / pap;
@@ -383,12 +484,13 @@ __global__ void __launch_bounds__(64 * W, kSharedMinWaves) k_cg_shared2(CgArgs a
             mode = uniform(mode);
             alpha = uniform(alpha);
             mass2 = uniform(mass2);
-            pb = uniform(pcur) ^ 1;  // p' written by K1 of this step
+            pb = kRecurrence<P> ? 0 : uniform(pcur) ^ 1;  // FP16: p' written by K1 of this step
         }
         js[q] = j;
         cg[q] = mode == M_CG;
         ru[q] = mode == M_RU;
         al[q] = (real)alpha;
+        be[q] = (real)beta;
         m2[q] = mass2;
         m2r[q] = (real)mass2;
         pn_buf[q] = pb;
@@ -412,25 +514,27 @@ __global__ void __launch_bounds__(64 * W, kSharedMinWaves) k_cg_shared2(CgArgs a
 #pragma unroll
     for (int q = 0; q < RR; ++q)
         apv[q] = spin_at<P>(a.ap, js[q] >= 0 ? js[q] : 0, Vh);
-    double nrm[RR];
+    double nrm[RR], nrp[RR];  // <r,r>; <r,p'> (recurrence form)
 #pragma unroll
     for (int q = 0; q < RR; ++q)
-        nrm[q] = 0.0;
+        nrm[q] = nrp[q] = 0.0;
     for (int it = 0;; ++it) {
-        const int s0 = chunk_start(it, Vh, a.remap);
+        const int s0 = chunk_start(it, Vh, tl);
         if (s0 < 0)
             break;
         if (anycg) {
-            if (it > 0)
+            if (it > 0) {
                 __syncthreads();
-            stage_chunk_links<P, ROWS>(a.g, (const typename P::link_t *)a.links[par], par, s0, lk);
+                cl.load(a.g, lout, lin, par, s0);
+            }
+            cl.store(a.g, lout, lin, lk);
             __syncthreads();
         }
         const int s = s0 + lane;
         if (s >= Vh)
             continue;
         if (wcg) {
-            // this site's p', x and r: before the gathers for a single system,
+            // this site's p (FP16: p'), x and r: before the gathers for a single system,
             // after them for several
             cplx<real> pv[RR][3];
             flt2 xv[RR][3];
@@ -471,6 +575,11 @@ __global__ void __launch_bounds__(64 * W, kSharedMinWaves) k_cg_shared2(CgArgs a
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     const int64_t o = (int64_t)c * Vh + s;
+                    if constexpr (kRecurrence<P>) {
+                        // p' = r + beta p; beta = 0 starts from p = 0, whatever the buffer holds
+                        pv[q][c].re = be[q] != 0.f ? fmaf(be[q], pv[q][c].re, ro[q][c].x) : ro[q][c].x;
+                        pv[q][c].im = be[q] != 0.f ? fmaf(be[q], pv[q][c].im, ro[q][c].y) : ro[q][c].y;
+                    }
                     xl[o] = flt2{fmaf(al[q], pv[q][c].re, xv[q][c].x), fmaf(al[q], pv[q][c].im, xv[q][c].y)};
                     const real apr = m2r[q] * pv[q][c].re - acc[q][c].re;
                     const real api = m2r[q] * pv[q][c].im - acc[q][c].im;
@@ -479,7 +588,11 @@ __global__ void __launch_bounds__(64 * W, kSharedMinWaves) k_cg_shared2(CgArgs a
                     rn.y = fma(-al[q], api, rn.y);
                     rv[o] = rn;
                     nrm[q] += (double)rn.x * rn.x + (double)rn.y * rn.y;
+                    if constexpr (kRecurrence<P>)
+                        nrp[q] += (double)rn.x * pv[q][c].re + (double)rn.y * pv[q][c].im;
                 }
+                if constexpr (kRecurrence<P>)
+                    P::store_spinor(spin_at<P>(a.p[0], j, Vh), Vh, s, pv[q]);
             }
         }
     }
@@ -490,22 +603,24 @@ __global__ void __launch_bounds__(64 * W, kSharedMinWaves) k_cg_shared2(CgArgs a
             continue;
         const int j = a.perm[k0 + r];
         const double m2d = a.st[cur][j].mass2;
-        double nr[1] = {0.0};
+        double nr[2] = {0.0, 0.0};
         for (int it = 0;; ++it) {
-            const int s0 = chunk_start(it, Vh, a.remap);
+            const int s0 = chunk_start(it, Vh, tl);
             if (s0 < 0)
                 break;
             for (int t = threadIdx.x; t < kChunk * 8; t += blockDim.x) {  // whole wavefronts
                 int sl, sub;
                 site_of_thread<8>(t, sl, sub);
                 if (s0 + sl < Vh)
-                    recompute_k2<P, 8, ROWS, 1>(a, j, par, s0 + sl, sub, m2d, nr[0]);
+                    recompute_k2<P, 8, ROWS>(a, j, par, s0 + sl, sub, m2d, nr[0], nr[1]);
             }
         }
         double tot;
-        block_sum_multi<1>(nr, red, tot);
+        block_sum_multi<2>(nr, red, tot);
         if (threadIdx.x == 0)
-            partial_slot(a, cur, j, 2)[blockIdx.x] = tot;
+            partial_slot(a, cur, j, 2)[tl.chunk] = tot;
+        if (kRecurrence<P> && threadIdx.x == 1)
+            partial_slot(a, cur, j, 1)[tl.chunk] = tot;
     }
 #pragma unroll
     for (int q = 0; q < RR; ++q) {
@@ -513,7 +628,12 @@ __global__ void __launch_bounds__(64 * W, kSharedMinWaves) k_cg_shared2(CgArgs a
             continue;
         const double tot = wave_sum(nrm[q]);
         if (lane == 0)
-            partial_slot(a, cur, js[q], 2)[blockIdx.x] = tot;
+            partial_slot(a, cur, js[q], 2)[tl.chunk] = tot;
+        if constexpr (kRecurrence<P>) {
+            const double trp = wave_sum(nrp[q]);
+            if (lane == 0)
+                partial_slot(a, cur, js[q], 1)[tl.chunk] = trp;
+        }
     }
 }
 

@@ -34,7 +34,7 @@ const CgLaunchTable &cg_table(int prec, int rows, int nt_links)
 namespace {
 
 // out(x) (+)= (D in)(x) for checkerboard sites [offset, offset + count) of the
-// output parity (blockIdx.y selects the parity when par_fixed < 0), with
+// output parity (both parities, their blocks alternating, when par_fixed < 0), with
 // links, vectors and arithmetic of precision P: FP64 / FP32 vectors are
 // [parity][colour][Vh] complex, FP16 vectors [parity][Vh] records of three
 // scaled half2 colours and their FP32 scale.
@@ -45,10 +45,11 @@ k_dslash(Geom g, const typename P::link_t *__restrict__ links, const int32_t *__
          int remap)
 {
     using real = typename P::real;
-    const int p = par_fixed >= 0 ? par_fixed : (int)blockIdx.y;
+    const BlockTile tl = block_tile(par_fixed >= 0 ? 1 : 2, remap, g.st * LPS / (int)blockDim.x);
+    const int p = par_fixed >= 0 ? par_fixed : tl.tile;
     const int Vh = g.Vh;
     int site, sub;
-    site_of_thread<LPS>(logical_block(blockIdx.x, gridDim.x, remap) * blockDim.x + threadIdx.x, site, sub);
+    site_of_thread<LPS>(tl.chunk * blockDim.x + threadIdx.x, site, sub);
     if (site >= count)
         return;
     const int s = offset + site;
@@ -56,7 +57,8 @@ k_dslash(Geom g, const typename P::link_t *__restrict__ links, const int32_t *__
     const char *src = (const char *)in + (size_t)(1 - p) * half;
     cplx<real> acc[1][3] = {{czero<real>(), czero<real>(), czero<real>()}};
     auto load = [&](int, int n, cplx<real> *chi) { P::load_spinor(src, Vh, n, chi); };
-    hop_accumulate<P, LPS, 1, decltype(load), false, ROWS>(g, links + link_parity_entries(ROWS, Vh) * p,
+    const int64_t lp = link_parity_entries(ROWS, Vh);
+    hop_accumulate<P, LPS, 1, decltype(load), false, ROWS>(g, links + lp * p, links + lp * (1 - p),
                                                            nbr ? nbr + (size_t)p * 8 * Vh : nullptr, p, s, sub, acc,
                                                            load);
     char *o = (char *)out + (size_t)p * half;
@@ -115,13 +117,15 @@ hipError_t launch_dslash_p(const KernelCfg &cfg, const GaugeField *f, int par_fi
                            int count, const void *in, void *out, int accumulate, hipStream_t s)
 {
     const int64_t threads = (int64_t)count * cfg.lps;  // site = wave * (64/lps) + lane % (64/lps)
-    dim3 grid((unsigned)((threads + cfg.block - 1) / cfg.block), (unsigned)nparity);
+    dim3 grid((unsigned)((threads + cfg.block - 1) / cfg.block) * (unsigned)nparity);
     dim3 block(cfg.block);
+    // t-columns need the whole parity; other site ranges take the XCD order
+    const int remap = cfg.remap == 3 && !slices_divide(f->g, cfg.lps, cfg.block, grid.x / nparity) ? 1 : cfg.remap;
     const auto *lk = (const typename P::link_t *)f->links[P::id];
     const int32_t *nb = cfg.tables ? f->nbr : nullptr;
 #define STAG_DSLASH_CASE(L, ROWS)                                                                                    \
     hipLaunchKernelGGL((k_dslash<P, L, ROWS>), grid, block, 0, s, f->g, lk, nb, in, out, par_fixed, offset, count,  \
-                       accumulate, cfg.remap)
+                       accumulate, remap)
     const int key = cfg.lps * 4 + f->rows;
     switch (key) {
     case 1 * 4 + 3: STAG_DSLASH_CASE(1, 3); break;
@@ -228,10 +232,19 @@ static int default_rtile(const CgLaunchTable &t, int nrhs)
     return best;
 }
 
+// Lanes per site of the D_slash by lattice size: more lanes where the sites
+// alone leave the chip idle.  Fixed rather than timed, so that the order of a
+// site's sum, and with it the last bits of D, never depends on a timing.
+// Best of 24 shapes with 1 / 2 / 4 / 8 lanes, us: FP64 8^4 4.3 / 3.8 / 3.6 / 3.6, 12^3 16
+// 4.6 / 4.4 / 4.5 / 5.1, 16^4 7.2 / 6.4 / 6.4 / 7.7, 32^4 106 / 102 / 110 / 109; FP32 8^4
+// 4.1 / 3.7 / 3.5 / 3.6, 20^4 9.9 / 9.4 / 9.5 / 11.3, 32^4 42.5 / 41.9 / 47.5 / -; FP16
+// 20^4 8.2 / 7.4 / 8.5 / 11.6, 32^4 27.5 / 28.0 / 35.5 / -.
+static int dslash_lps(const GaugeField *f) { return 2 * (int64_t)f->g.Vh <= 20736 ? 4 : 2; }
+
 static KernelCfg default_config(const GaugeField *f, int prec, int nrhs)
 {
     KernelCfg best;
-    best.lps = prec == 0 ? 2 : 1;
+    best.lps = dslash_lps(f);
     best.block = 256;
     best.rtile = default_rtile(cg_table(prec, f->rows, f->nt_links), nrhs);
     best.tables = 0;
@@ -280,50 +293,66 @@ KernelCfg tune_config(Ctx *ctx, GaugeField *f, int prec, int nrhs, hipStream_t s
         bool ok = in && out && hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess &&
                   hipMemsetAsync(in, 0, vbytes, s) == hipSuccess;
         double best_t = 1e30;
-        const int lps_c[4] = {1, 2, 4, 8}, blk_c[3] = {64, 128, 256};
-        for (int R : tiles) {
-            for (int L : lps_c) {
-                for (int B : blk_c) {
-                    for (int T = 0; T < 2 && ok; ++T) {
-                        for (int X = 0; X < 2 && ok; ++X) {
-                            const int64_t threads = (int64_t)f->g.Vh * L;
-                            dim3 grid((unsigned)((threads + B - 1) / B), (unsigned)(2 * nrhs / R)), block(B);
-                            const void *links = f->links_for(prec, 0);
-                            const int32_t *nb = T ? f->nbr_for(0) : nullptr;
-                            auto run = [&]() { return tab.probe(L, R, grid, block, s, f->g, links, nb, in, out, X); };
-                            if (run() != hipSuccess) {
-                                ok = false;
-                                break;
-                            }
-                            const int reps = 4;
-                            (void)hipEventRecord(e0, s);
-                            for (int i = 0; i < reps; ++i)
-                                (void)run();
-                            (void)hipEventRecord(e1, s);
-                            if (hipEventSynchronize(e1) != hipSuccess) {
-                                ok = false;
-                                break;
-                            }
-                            float ms = 0.f;
-                            (void)hipEventElapsedTime(&ms, e0, e1);
-                            const double per_rhs = ms / reps / nrhs;
-                            if (verbose)
-                                fprintf(stderr, "[stag tune] V=%d prec=%d nrhs=%d lps=%d block=%d rtile=%d tables=%d "
-                                                "remap=%d: %.2f us per rhs\n",
-                                        2 * f->g.Vh, prec, nrhs, L, B, R, T, X, per_rhs * 1e3);
-                            if (per_rhs < best_t * 0.995) {
-                                best_t = per_rhs;
-                                best.lps = L;
-                                best.block = B;
-                                best.rtile = R;
-                                best.tables = T;
-                                best.remap = X;
-                            }
-                        }
-                    }
-                }
+        // the faster of two runs of one shape, us per right-hand side (1e30: failed)
+        auto timed = [&](const KernelCfg &c) {
+            const int64_t threads = (int64_t)f->g.Vh * c.lps;
+            const int ntiles = 2 * nrhs / c.rtile;
+            dim3 grid((unsigned)((threads + c.block - 1) / c.block) * (unsigned)ntiles), block(c.block);
+            const void *links = f->links_for(prec, 0);
+            const int32_t *nb = c.tables ? f->nbr_for(0) : nullptr;
+            auto run = [&]() {
+                return tab.probe(c.lps, c.rtile, grid, block, s, f->g, links, nb, in, out, ntiles, c.remap);
+            };
+            if (!ok || run() != hipSuccess) {
+                ok = false;
+                return 1e30;
             }
+            const int reps = 4;
+            double t = 1e30;
+            for (int k = 0; k < 2 && ok; ++k) {
+                (void)hipEventRecord(e0, s);
+                for (int i = 0; i < reps; ++i)
+                    (void)run();
+                (void)hipEventRecord(e1, s);
+                ok = hipEventSynchronize(e1) == hipSuccess;
+                float ms = 0.f;
+                (void)hipEventElapsedTime(&ms, e0, e1);
+                t = std::min(t, (double)ms * 1e3 / reps / nrhs);
+            }
+            if (verbose)
+                fprintf(stderr, "[stag tune] V=%d prec=%d nrhs=%d lps=%d block=%d rtile=%d tables=%d remap=%d: %.2f us "
+                                "per rhs\n", 2 * f->g.Vh, prec, nrhs, c.lps, c.block, c.rtile, c.tables, c.remap, t);
+            return ok ? t : 1e30;
+        };
+        // the block size and tile, then the block order, then the tables, each
+        // kept where it gains
+        auto keep = [&](KernelCfg c) {
+            const double t = timed(c);
+            if (t < best_t * 0.99) {
+                best_t = t;
+                best = c;
+            }
+        };
+        const int blk_c[3] = {64, 128, 256};
+        const int lps = best.lps;
+        for (int R : tiles)
+            for (int B : blk_c) {
+                KernelCfg c;
+                c.lps = lps;
+                c.block = B;
+                c.rtile = R;
+                keep(c);
+            }
+        for (int X : {0, 2, 3}) {
+            KernelCfg c = best;
+            c.remap = X;
+            const int64_t threads = (int64_t)f->g.Vh * c.lps;
+            if (X != 3 || slices_divide(f->g, c.lps, c.block, (threads + c.block - 1) / c.block))
+                keep(c);
         }
+        KernelCfg c = best;
+        c.tables = 1;
+        keep(c);
         if (e0)
             (void)hipEventDestroy(e0);
         if (e1)

@@ -23,6 +23,7 @@
 // Bytes per site: 4 forward links (FP64, stored rows), the site's and its
 // four forward neighbours' W (48 B each, the neighbours' amortised to one),
 // 4 x 144 B written (plus 4 x 144 B read when accumulating).
+#include "hop.hpp"
 #include "runtime.hpp"
 
 namespace stag {
@@ -31,7 +32,7 @@ namespace {
 
 constexpr int kForceSites = 64;  // lexicographic sites per block
 
-template <class P64, int ROWS>
+template <int ROWS>
 __global__ void __launch_bounds__(256)
 k_fermion_force(Geom g, const dbl2 *__restrict__ links, const dbl2 *__restrict__ w, dbl2 *__restrict__ force,
                 double coeff, int accumulate)
@@ -58,11 +59,8 @@ k_fermion_force(Geom g, const dbl2 *__restrict__ links, const dbl2 *__restrict__
         PrecF64::load_spinor(w + (size_t)p * 3 * Vh, Vh, s, wz);
         cplx<double> wf[3];
         PrecF64::load_spinor(w + (size_t)(1 - p) * 3 * Vh, Vh, neighbour(g, c, s, mu), wf);
-        const dbl2 *lk = links + link_parity_entries(ROWS, Vh) * p;
         cplx<double> L[9];
-#pragma unroll
-        for (int k = 0; k < 3 * ROWS; ++k)
-            L[k] = P64::load_link(lk + link_offset(Vh, mu, k, s));
+        load_link_rows<PrecF64, ROWS, false>(links + link_parity_entries(ROWS, Vh) * p + link_offset(ROWS, mu, s), L);
         if constexpr (ROWS == 2)
             third_row(L, folded_negative(g, c, mu) ? -2.0 : 2.0);
         // B = L (W(z+mu) W(z)^dagger): B_ab = (L wf)_a conj(wz_b)
@@ -115,20 +113,13 @@ int fermion_force(GaugeField *f, const double *w, double *force, double coeff, i
     const int64_t V = (int64_t)2 * g.Vh;
     const dim3 grid((unsigned)((V + kForceSites - 1) / kForceSites));
     const dim3 block(kForceSites * 4);
-#define STAG_FORCE_CASE(P64, ROWS)                                                                                   \
-    hipLaunchKernelGGL((k_fermion_force<P64, ROWS>), grid, block, 0, s, g, (const dbl2 *)f->links[0],              \
-                       (const dbl2 *)w, (dbl2 *)force, coeff, accumulate)
-    if (f->nt_links) {
-        if (f->rows == 2)
-            STAG_FORCE_CASE(PrecF64NT, 2);
-        else
-            STAG_FORCE_CASE(PrecF64NT, 3);
-    } else {
-        if (f->rows == 2)
-            STAG_FORCE_CASE(PrecF64, 2);
-        else
-            STAG_FORCE_CASE(PrecF64, 3);
-    }
+#define STAG_FORCE_CASE(ROWS)                                                                                        \
+    hipLaunchKernelGGL((k_fermion_force<ROWS>), grid, block, 0, s, g, (const dbl2 *)f->links[0], (const dbl2 *)w,    \
+                       (dbl2 *)force, coeff, accumulate)
+    if (f->rows == 2)
+        STAG_FORCE_CASE(2);
+    else
+        STAG_FORCE_CASE(3);
 #undef STAG_FORCE_CASE
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess)

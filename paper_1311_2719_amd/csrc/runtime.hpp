@@ -78,17 +78,24 @@ struct GaugeField {
     int32_t tap = 1;
     Geom g{};
     int32_t rows = 3;                                // link rows stored (2: third row rebuilt)
-    int32_t nt_links = 0;                            // 1: FP64 kernels read links non-temporally
-    void *links[3] = {nullptr, nullptr, nullptr};  // per precision id: [2 parities][3 * rows][Vh / 8][8][8]
+    int32_t nt_links = 0;                            // 1: FP64 kernels read the backward neighbours' links non-temporally
+    void *links[3] = {nullptr, nullptr, nullptr};  // per precision id, layout in stag_types.hpp
     int32_t *nbr = nullptr;                          // [2][8][Vh]
+    // Kept with the field for the workspace of stag_cg_solve (as many bytes as
+    // the links; an FP64 solve takes 240 per site and 0.2 MB): taken by the
+    // first single-source batch, given back when that batch goes.  Batches of
+    // more sources, the server's, and those that find it taken use the arena.
+    void *work = nullptr;
+    size_t work_bytes = 0;
+    std::atomic<int> work_taken{0};
     std::atomic<int> users{0};                       // serving requests queued / running
     std::map<uint64_t, KernelCfg> tuned;             // key: (prec, nrhs)
     size_t bytes = 0;
 
-    const void *links_for(int prec, int out_parity) const
+    const void *links_for(int prec, int parity) const
     {
         const size_t per_parity = (size_t)link_parity_entries(rows, g.Vh) * link_entry_bytes_of(prec);
-        return (const char *)links[prec] + (size_t)out_parity * per_parity;
+        return (const char *)links[prec] + (size_t)parity * per_parity;
     }
     const int32_t *nbr_for(int out_parity) const { return nbr + (size_t)out_parity * 8 * g.Vh; }
 };
@@ -143,14 +150,14 @@ constexpr double kTwoRowTolerance = 1e-14;
 // Check the lexicographic links on the device: ENONFINITE for NaN/Inf;
 // two_rows = whether every folded link admits the two-row form.
 int gauge_check(Ctx *ctx, const Geom &g, const double *links_dev, hipStream_t s, bool &two_rows);
-// Whether the FP64 kernels of field f read its links non-temporally: when its
-// FP64 links do not fit the Infinity Cache (STAG_NT_LINKS=0/1 forces it).
+// Whether the FP64 kernels of field f read links of backward neighbours
+// non-temporally: when its FP64 links do not fit the Infinity Cache (STAG_NT_LINKS=0/1 forces it).
 int nt_links_for(const GaugeField &f);
 // Fill f->links (f->rows rows, every precision) and f->nbr from the links.
 int gauge_prepare(GaugeField *f, const double *links_dev, hipStream_t s);
 
 // Wilson fermions: check the links, choose the stored rows, allocate and fill
-// f->links[0] (FP64; t-boundary sign folded, backward links daggered).
+// f->links[0] (FP64; t-boundary sign folded).
 int wilson_prepare(Ctx *ctx, GaugeField *f, const double *links_dev, hipStream_t s);
 // lexicographic [V][4][3] <-> even-odd [2][12][Vh] complex128
 int launch_pack_spinor(const Geom &g, const double *lex, double *eo, int to_eo, hipStream_t s);

@@ -2,17 +2,23 @@
 //
 // Storage formats (structure-of-arrays over the checkerboard index of one
 // parity, so lanes that take consecutive sites touch consecutive addresses):
-//   links   per parity [entry 9][site tile Vh/8][dir 8][site 8] of a complex
-//           type: each (entry, tile) is a contiguous 8 x 8 block, so a
-//           wavefront reading one entry for 64 consecutive sites and one
-//           direction, or for 8 sites and all 8 directions, touches whole
-//           cache lines either way.  Dir 0..3 are the forward links
-//           W_mu(x) = 1/2 eta_mu(x) s_fwd(x) U_mu(x), dir 4..7 the backward
-//           links B_mu(x) = -1/2 eta_mu(x) s_bwd(x) U_mu(x-mu)^dagger, both stored
-//           at the site x that uses them; s_fwd / s_bwd are the t-boundary
-//           signs.  With these, (D chi)(x) = sum_d L_d(x) chi(n_d(x)),
-//           n_d = x+mu (d < 4) or x-mu (d >= 4).  Vh is a multiple of 8
-//           because every extent is even.
+//   links   per parity of the site x they start from, the four forward links
+//           W_mu(x) = 1/2 eta_mu(x) s(x) U_mu(x) (s: the t-boundary sign of the
+//           hop from x to x + mu), in tiles of 64 sites: [tile][mu 4][entry 9]
+//           [site 64] of a complex type, the last tile padded.  Since eta_mu
+//           does not depend on x_mu, the backward hop uses the same matrix:
+//             (D chi)(x) = sum_mu [W_mu(x) chi(x+mu) - W_mu(x-mu)^dagger chi(x-mu)],
+//           so a hop at x takes the forward links of x and, daggered in
+//           registers, those of its backward neighbours (the other parity's
+//           array, gathered like the vectors).  A daggered copy stored at x
+//           would double the link bytes: where both parities are applied in
+//           one launch every link is needed twice, by its two ends, and the
+//           second read is then served by a cache.  FP64 D_slash, both
+//           parities, two stored copies -> one: 32^4 152 -> 103 us, 24^4
+//           44.9 -> 32.1, 16^4 9.7 -> 5.7; FP32 32^4 91.9 -> 47.5, FP16 36.6 ->
+//           27.8.  A tile is one wavefront of one-lane-per-site kernels, whose
+//           loads are whole lines; 8-site tiles measured 118, 58 and 43 us
+//           at 32^4 in the three precisions, whole planes 110, 49 and 28.
 //           Two-row form (fields whose links are special unitary): only
 //           entries 0..5 (rows 0 and 1) are stored.  Every stored matrix is
 //           c V with V in SU(3) and c = +-1/2, so row 2 = conj(row0 x row1) / c,
@@ -64,16 +70,20 @@ inline Geom make_geom(const int32_t d[4])
     return g;
 }
 
-// Link entries per output parity: 8 directions x (3 x rows) complex per site.
+constexpr int kLinkTile = 64;  // sites per tile of the link arrays
+
+// Link entries of one parity: 4 directions x (3 x rows) complex per site, whole tiles.
 __host__ __device__ __forceinline__ int64_t link_parity_entries(int rows, int Vh)
 {
-    return (int64_t)24 * rows * Vh;
+    return (int64_t)12 * rows * ((Vh + kLinkTile - 1) / kLinkTile * kLinkTile);
 }
 
-// Offset of link entry k of direction d at checkerboard site s, within one parity.
-__host__ __device__ __forceinline__ int64_t link_offset(int Vh, int d, int k, int s)
+// Offset of entry 0 of the forward link mu of checkerboard site s, within one
+// parity; entry k is kLinkTile * k further on.
+__host__ __device__ __forceinline__ int64_t link_offset(int rows, int mu, int s)
 {
-    return (int64_t)k * 8 * Vh + (int64_t)(s >> 3) * 64 + d * 8 + (s & 7);
+    const uint32_t u = (uint32_t)s;
+    return (int64_t)(u / kLinkTile) * (12 * rows * kLinkTile) + mu * 3 * rows * kLinkTile + (int)(u % kLinkTile);
 }
 
 struct SiteCoord {
@@ -96,10 +106,11 @@ __device__ __forceinline__ SiteCoord decode_site(const Geom &g, int p, int s)
     return c;
 }
 
-// True when the real factor folded into link d of the site with coordinates
-// c is negative: eta_mu(x), the minus of a backward link and the sign of a hop
+// True when the real factor of hop d of the site with coordinates c is
+// negative: eta_mu(x), the minus of a backward hop and the sign of a hop
 // across the t boundary of an antiperiodic field (the rule the gauge
-// preparation applies).
+// preparation applies).  The factor of the stored link that a backward hop
+// daggers is the opposite one.
 __device__ __forceinline__ bool folded_negative(const Geom &g, const SiteCoord &c, int d)
 {
     // every field is read before any choice is made, so the choices below
@@ -150,6 +161,16 @@ __device__ __forceinline__ void cmac(cplx<T> &acc, const cplx<T> &a, const cplx<
     acc.im = fma(a.im, b.re, acc.im);
 }
 
+// acc -= conj(a) * b
+template <typename T>
+__device__ __forceinline__ void cmsub_conj(cplx<T> &acc, const cplx<T> &a, const cplx<T> &b)
+{
+    acc.re = fma(-a.re, b.re, acc.re);
+    acc.re = fma(-a.im, b.im, acc.re);
+    acc.im = fma(-a.re, b.im, acc.im);
+    acc.im = fma(a.im, b.re, acc.im);
+}
+
 // Row 2 of W = c V (V special unitary, c real) from rows 0 and 1 (entries
 // U[0..5], row-major): W_2 = conj(W_0 x W_1) / c; inv_c = 1 / c.
 template <typename T> __device__ __forceinline__ void third_row(cplx<T> (&U)[9], T inv_c)
@@ -183,6 +204,7 @@ struct PrecF64 {
         const dbl2 v = *p;
         return {v.x, v.y};
     }
+    static __device__ __forceinline__ cplx<real> load_back_link(const link_t *p) { return load_link(p); }
     static __device__ __forceinline__ void load_spinor(const void *base, int Vh, int s, cplx<real> out[3])
     {
         const dbl2 *b = (const dbl2 *)base;
@@ -203,16 +225,16 @@ struct PrecF64 {
     static constexpr size_t link_bytes = 16;     // per complex entry
 };
 
-// FP64 with non-temporal link loads, for fields whose FP64 links do not fit
-// the 256 MB Infinity Cache.  A kernel reads each link once and never again
-// while it runs; non-temporal loads keep the links from evicting the
-// gathered vectors, which every site reads eight times (32^4 D_slash:
-// 170 -> 152 us, FP64 CG 4.14 -> 4.80 solves/s).  Where the links do fit,
-// the cache serves them across the CG's kernels and plain loads are faster
-// (16^4 CG: 238 against 213 solves/s; 24^4: 22.6 against 21.6).  The FP32
-// and FP16 tiles measured slower with them at every size.
+// FP64 with non-temporal loads of the backward neighbours' links, for fields
+// whose FP64 links do not fit the 256 MB Infinity Cache.  In the order the
+// sites are visited the backward use of a link is its last one (its forward
+// use came up to a t-slice earlier), so the line need not be kept; where a
+// launch applies one parity only, each link is read once.  32^4 (402 MB): one
+// parity 85 -> 70 us, both 103 -> 104; smaller fields lose 2 to 5%, and so
+// do FP32 and FP16 (32^4: 49 -> 55 us, 27.8 -> 29.1).  Non-temporal loads of the
+// forward links cost 30% at 32^4: they drop lines the backward use finds.
 struct PrecF64NT : PrecF64 {
-    static __device__ __forceinline__ cplx<real> load_link(const link_t *p)
+    static __device__ __forceinline__ cplx<real> load_back_link(const link_t *p)
     {
         const dbl2 v = __builtin_nontemporal_load(p);
         return {v.x, v.y};
@@ -228,6 +250,7 @@ struct PrecF32 {
         flt2 v = *p;
         return {v.x, v.y};
     }
+    static __device__ __forceinline__ cplx<real> load_back_link(const link_t *p) { return load_link(p); }
     static __device__ __forceinline__ void load_spinor(const void *base, int Vh, int s, cplx<real> out[3])
     {
         const flt2 *b = (const flt2 *)base;
@@ -257,6 +280,7 @@ struct PrecF16 {
         hlf2 v = *p;
         return {(float)v.x, (float)v.y};
     }
+    static __device__ __forceinline__ cplx<real> load_back_link(const link_t *p) { return load_link(p); }
     static __device__ __forceinline__ void decode(const HalfSpinor &h, cplx<real> out[3])
     {
 #pragma unroll

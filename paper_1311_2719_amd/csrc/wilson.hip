@@ -16,31 +16,22 @@ namespace stag {
 
 namespace {
 
-// The link of direction d at checkerboard site s of output parity p for the
-// Wilson operator: W_mu(x) = s_fwd U_mu(x) (d < 4), B_mu(x) = s_bwd
-// U_mu(x - mu)^dagger (d >= 4), s_* the t-boundary signs.  False if an entry is
+// The forward link mu of checkerboard site s of parity p for the Wilson
+// operator: W_mu(x) = s U_mu(x), s the t-boundary sign.  False if an entry is
 // not finite.
-__device__ bool wilson_link(const Geom &g, const double *__restrict__ U, int p, int d, int s, dbl2 (&w)[9])
+__device__ bool wilson_link(const Geom &g, const double *__restrict__ U, int p, int mu, int s, dbl2 (&w)[9])
 {
     const SiteCoord c = decode_site(g, p, s);
-    const int mu = d & 3;
-    int src[4] = {c.x, c.y, c.z, c.t};
-    const bool back = d >= 4;
-    double fac = wil::wilson_link_negative(g, c, d) ? -1.0 : 1.0;
-    if (back)
-        src[mu] = src[mu] == 0 ? g.L[mu] - 1 : src[mu] - 1;
-    const int64_t lex = src[0] + (int64_t)g.L[0] * (src[1] + (int64_t)g.L[1] * (src[2] + (int64_t)g.L[2] * src[3]));
+    const double fac = wil::wilson_link_negative(g, c, mu) ? -1.0 : 1.0;
+    const int64_t lex = c.x + (int64_t)g.L[0] * (c.y + (int64_t)g.L[1] * (c.z + (int64_t)g.L[2] * c.t));
     const double *u = U + (lex * 4 + mu) * 18;
     bool finite = true;
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            const int k = back ? (b * 3 + a) : (a * 3 + b);
-            const double re = u[2 * k], im = back ? -u[2 * k + 1] : u[2 * k + 1];
-            w[a * 3 + b] = dbl2{re * fac, im * fac};
-            finite = finite && isfinite(re) && isfinite(im);
-        }
+    for (int k = 0; k < 9; ++k) {
+        const double re = u[2 * k], im = u[2 * k + 1];
+        w[k] = dbl2{re * fac, im * fac};
+        finite = finite && isfinite(re) && isfinite(im);
+    }
     return finite;
 }
 
@@ -49,19 +40,19 @@ __device__ bool wilson_link(const Geom &g, const double *__restrict__ U, int p, 
 __global__ void __launch_bounds__(256) k_wcheck_links(Geom g, const double *__restrict__ U, double tol, int *flags)
 {
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= (int64_t)2 * 8 * g.Vh)
+    if (gid >= (int64_t)2 * 4 * g.Vh)
         return;
-    const int s = (int)(gid % g.Vh), d = (int)((gid / g.Vh) % 8), p = (int)(gid / ((int64_t)8 * g.Vh));
+    const int s = (int)(gid % g.Vh), mu = (int)((gid / g.Vh) % 4), p = (int)(gid / ((int64_t)4 * g.Vh));
     dbl2 w[9];
     int f = 0;
-    if (!wilson_link(g, U, p, d, s, w)) {
+    if (!wilson_link(g, U, p, mu, s, w)) {
         f = 1;
     } else {
         cplx<double> W[9];
         for (int k = 0; k < 9; ++k)
             W[k] = {w[k].x, w[k].y};
         const cplx<double> given[3] = {W[6], W[7], W[8]};
-        third_row(W, wil::wilson_link_negative(g, decode_site(g, p, s), d) ? -1.0 : 1.0);
+        third_row(W, wil::wilson_link_negative(g, decode_site(g, p, s), mu) ? -1.0 : 1.0);
         double dev = 0.0;
         for (int k = 0; k < 3; ++k)
             dev = fmax(dev, fmax(fabs(W[6 + k].re - given[k].re), fabs(W[6 + k].im - given[k].im)));
@@ -76,15 +67,15 @@ template <int ROWS>
 __global__ void __launch_bounds__(256) k_wprepare_links(Geom g, const double *__restrict__ U, dbl2 *__restrict__ l64)
 {
     const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gid >= (int64_t)2 * 8 * g.Vh)
+    if (gid >= (int64_t)2 * 4 * g.Vh)
         return;
-    const int s = (int)(gid % g.Vh), d = (int)((gid / g.Vh) % 8), p = (int)(gid / ((int64_t)8 * g.Vh));
+    const int s = (int)(gid % g.Vh), mu = (int)((gid / g.Vh) % 4), p = (int)(gid / ((int64_t)4 * g.Vh));
     dbl2 w[9];
-    (void)wilson_link(g, U, p, d, s, w);
-    const int64_t base = link_parity_entries(ROWS, g.Vh) * p;
+    (void)wilson_link(g, U, p, mu, s, w);
+    const int64_t base = link_parity_entries(ROWS, g.Vh) * p + link_offset(ROWS, mu, s);
 #pragma unroll
     for (int k = 0; k < 3 * ROWS; ++k)
-        l64[base + link_offset(g.Vh, d, k, s)] = w[k];
+        l64[base + k * kLinkTile] = w[k];
 }
 
 // lexicographic [V][4][3] <-> even-odd [2][12][Vh]
@@ -129,7 +120,7 @@ constexpr int kWBlock = 128;
 int wilson_prepare(Ctx *ctx, GaugeField *f, const double *links_dev, hipStream_t s)
 {
     const Geom &g = f->g;
-    const int64_t n = (int64_t)2 * 8 * g.Vh;
+    const int64_t n = (int64_t)2 * 4 * g.Vh;
     const dim3 grid((unsigned)((n + 255) / 256)), block(256);
     int *flags = (int *)ctx->arena.alloc(256);
     if (!flags)
@@ -186,7 +177,10 @@ namespace {
 // The launches of the hop and of one solve, for one link format and one
 // number of lanes per site.
 template <int ROWS, int LPS, class LP> struct WLaunch {
-    static dim3 grid(int Vh, int ny = 1) { return dim3((unsigned)(((int64_t)Vh * LPS + kWBlock - 1) / kWBlock), ny); }
+    static dim3 grid(int Vh, int tiles = 1)
+    {
+        return dim3((unsigned)(((int64_t)Vh * LPS + kWBlock - 1) / kWBlock) * (unsigned)tiles);
+    }
     static void hop(const GaugeField *f, int pf, const double *in, double *out, int remap, hipStream_t s)
     {
         hipLaunchKernelGGL((wil::k_wilson_dslash<ROWS, LPS, LP>), grid(f->g.Vh, pf < 0 ? 2 : 1), dim3(kWBlock), 0, s, f->g,

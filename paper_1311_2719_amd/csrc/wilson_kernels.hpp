@@ -3,8 +3,8 @@
 //
 // The paper's second workload is an N_f = 2 Wilson-fermion program (Sec. 2, Sec. 6);
 // it does not write the operator out, so the textbook form is used:
-//   (H psi)(x) = sum_mu [(1 - gamma_mu) W_mu(x) psi(x + mu) + (1 + gamma_mu) B_mu(x) psi(x - mu)],
-//   W_mu(x) = s U_mu(x), B_mu(x) = s U_mu(x - mu)^dagger (s: the t-boundary sign),
+//   (H psi)(x) = sum_mu [(1 - gamma_mu) W_mu(x) psi(x + mu) + (1 + gamma_mu) W_mu(x - mu)^dagger psi(x - mu)],
+//   W_mu(x) = s U_mu(x) (s: the t-boundary sign of the hop from x to x + mu),
 // gamma matrices of a chiral basis with gamma_5 = diag(1, 1, -1, -1).
 //
 // Spin projection: 1 -+ gamma_mu has rank 2 in this basis, so each hop
@@ -12,13 +12,16 @@
 // the 3x3 link to those only, and rebuilds spins 2 and 3 as multiples of
 // them (half the colour arithmetic of the full product).
 //
-// Layout: links as for the staggered operator ([entry][tile][dir][site], FP64,
-// two or three stored rows); spinors of one parity as 12 planes of Vh complex
+// Layout: links as for the staggered operator (the forward links of a site in
+// tiles of 64 sites, FP64, two or three stored rows; the backward hop daggers
+// the neighbour's); spinors of one parity as 12 planes of Vh complex
 // (plane = 3 * spin + colour), a full field as [parity][12][Vh].  The template
 // parameter LP reads the links: PrecF64 with plain loads, PrecF64NT with
-// non-temporal ones (fields whose links do not fit the Infinity Cache, where
-// each link, read once per launch, would otherwise evict gathered spinors).
+// non-temporal ones for the backward neighbours' (fields whose links do not
+// fit the Infinity Cache).
 #pragma once
+
+#include <type_traits>
 
 #include "hop.hpp"
 
@@ -81,13 +84,11 @@ __device__ __forceinline__ Proj unpack_proj(uint32_t w)
             (int)(w >> 16 & 15), (int)(w >> 20 & 15), (int)(w >> 24 & 15), (int)(w >> 28)};
 }
 
-// Projector of direction j * LPS + sub.  The table is never read from memory:
-// with j known at compile time (unrolled loop) the word is chosen among the
-// LPS candidates of the lanes; with a runtime j (rolled loop, LPS = 1, the
-// same in every lane) among all eight.
-template <int LPS> __device__ __forceinline__ Proj proj_of(int j, int sub)
+// Projector of direction d.  The table is never read from memory: with d
+// known at compile time (unrolled loop, one lane per site) the word is a
+// constant, else it is chosen by selects among the candidates.
+__device__ __forceinline__ Proj proj_of(int d)
 {
-    const int d = j * LPS + sub;
     uint32_t w = pack_proj(kProj[0]);
 #pragma unroll
     for (int t = 1; t < 8; ++t)
@@ -95,8 +96,8 @@ template <int LPS> __device__ __forceinline__ Proj proj_of(int j, int sub)
     return unpack_proj(w);
 }
 
-// True when the t-boundary sign folded into Wilson link d of the site with
-// coordinates c is negative.
+// True when the t-boundary sign of Wilson hop d of the site with coordinates c
+// is negative (the sign of the stored link it uses, forward or daggered).
 __device__ __forceinline__ bool wilson_link_negative(const Geom &g, const SiteCoord &c, int d)
 {
     const int ct = c.t, Lt = g.L[3], tap = g.tap;  // values first: the choice below is a select
@@ -104,13 +105,15 @@ __device__ __forceinline__ bool wilson_link_negative(const Geom &g, const SiteCo
 }
 
 // acc[spin][colour] = (H psi)(s) for output site s of parity p_out, computed
-// by LPS lanes (sub = 0 .. LPS-1; lane sub takes directions sub, sub + LPS,
-// ...) and summed over them, so every lane of the site ends with the total.
-// load(n, sp, col) returns component (sp, col) of the input at site n of the
-// other parity (with gamma_5 or any fused combination applied by the caller).
+// by LPS lanes (sub = 0 .. LPS-1; lane sub takes mu = sub, sub + LPS, ...,
+// forward and backward; with LPS = 8 one hop each) and summed over them, so
+// every lane of the site ends with the total.  lout / lin: the links of the
+// output parity and of the other one.  load(n, sp, col) returns component
+// (sp, col) of the input at site n of the other parity (with gamma_5 or any
+// fused combination applied by the caller).
 template <int ROWS, int LPS, class LP, class Load>
-__device__ __forceinline__ void wilson_hop(const Geom &g, const dbl2 *__restrict__ links, int p_out, int s, int sub,
-                                           cplx<double> (&acc)[4][3], Load load)
+__device__ __forceinline__ void wilson_hop(const Geom &g, const dbl2 *__restrict__ lout, const dbl2 *__restrict__ lin,
+                                           int p_out, int s, int sub, cplx<double> (&acc)[4][3], Load load)
 {
 #pragma unroll
     for (int sp = 0; sp < 4; ++sp)
@@ -118,17 +121,29 @@ __device__ __forceinline__ void wilson_hop(const Geom &g, const dbl2 *__restrict
         for (int a = 0; a < 3; ++a)
             acc[sp][a] = czero<double>();
     const SiteCoord c = decode_site(g, p_out, s);
-    auto one_direction = [&](int j) {
-        const int d = sub + j * LPS;
-        const Proj q = proj_of<LPS>(j, sub);
+    // one hop; kind 0: forward, 1: backward, 2: backward if d >= 4, by lane
+    // (the matrix is then formed by selects, so lanes do not diverge)
+    auto one_hop = [&](auto kind, int d) {
+        constexpr int K = decltype(kind)::value;
+        const bool back = K == 2 ? d >= 4 : K == 1;
+        const int mu = d & 3;
+        const Proj q = proj_of(d);
         const int n = neighbour(g, c, s, d);
         cplx<double> U[9];
-        const dbl2 *lp = links + link_offset(g.Vh, d, 0, s);
-#pragma unroll
-        for (int k = 0; k < 3 * ROWS; ++k)
-            U[k] = LP::load_link(lp + (int64_t)k * 8 * g.Vh);
+        if constexpr (K == 1)
+            load_link_rows<LP, ROWS, true>(lin + link_offset(ROWS, mu, n), U);
+        else
+            load_link_rows<LP, ROWS, false>((back ? lin : lout) + link_offset(ROWS, mu, back ? n : s), U);
         if constexpr (ROWS == 2)
             third_row(U, wilson_link_negative(g, c, d) ? -1.0 : 1.0);
+        cplx<double> M[9];
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+#pragma unroll
+            for (int b = 0; b < 3; ++b) {
+                const cplx<double> u = U[a * 3 + b], v = U[b * 3 + a];
+                M[a * 3 + b] = {back ? v.re : u.re, back ? -v.im : u.im};
+            }
         cplx<double> h[2][3];
 #pragma unroll
         for (int col = 0; col < 3; ++col) {
@@ -146,7 +161,7 @@ __device__ __forceinline__ void wilson_hop(const Geom &g, const dbl2 *__restrict
                 u[k][a] = czero<double>();
 #pragma unroll
                 for (int b = 0; b < 3; ++b)
-                    cmac(u[k][a], U[a * 3 + b], h[k][b]);
+                    cmac(u[k][a], M[a * 3 + b], h[k][b]);
             }
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
@@ -162,15 +177,26 @@ __device__ __forceinline__ void wilson_hop(const Geom &g, const dbl2 *__restrict
             acc[3][a].im += r3.im;
         }
     };
+    using fwd_t = std::integral_constant<int, 0>;
+    using back_t = std::integral_constant<int, 1>;
+    using lane_t = std::integral_constant<int, 2>;
     if constexpr (LPS == 1) {
         // two directions per iteration: enough loads in flight without spilling
-#pragma unroll 2
-        for (int j = 0; j < 8; ++j)
-            one_direction(j);
+#pragma unroll 1
+        for (int mu = 0; mu < 4; ++mu) {
+            one_hop(fwd_t{}, mu);
+            one_hop(back_t{}, 4 + mu);
+        }
     } else {
+        if constexpr (LPS == 8) {
+            one_hop(lane_t{}, sub);
+        } else {
 #pragma unroll
-        for (int j = 0; j < 8 / LPS; ++j)
-            one_direction(j);
+            for (int j = 0; j < 4 / LPS; ++j) {
+                one_hop(fwd_t{}, sub + j * LPS);
+                one_hop(back_t{}, 4 + sub + j * LPS);
+            }
+        }
 #pragma unroll
         for (int sp = 0; sp < 4; ++sp)
 #pragma unroll
@@ -208,21 +234,25 @@ template <int LPS> __device__ __forceinline__ bool wsite(int Vh, int remap, int 
     return s < Vh;
 }
 
-// ---- the standalone hop: out_p = H_p in (one parity, or both with blockIdx.y) -------
+// ---- the standalone hop: out_p = H_p in (one parity, or both, their blocks
+// alternating so that the two uses of a link meet in one XCD's L2) ---------------------
 
 template <int ROWS, int LPS, class LP>
 __global__ void __launch_bounds__(128)
 k_wilson_dslash(Geom g, const dbl2 *__restrict__ links, const dbl2 *__restrict__ in, dbl2 *__restrict__ out,
                 int par_fixed, int remap)
 {
-    const int p = par_fixed >= 0 ? par_fixed : (int)blockIdx.y;
+    const BlockTile tl = block_tile(par_fixed >= 0 ? 1 : 2, remap, g.st * LPS / (int)blockDim.x);
+    const int p = par_fixed >= 0 ? par_fixed : tl.tile;
     const int Vh = g.Vh;
     int s, sub;
-    if (!wsite<LPS>(Vh, remap, s, sub))
+    site_of_thread<LPS>(tl.chunk * blockDim.x + threadIdx.x, s, sub);
+    if (s >= Vh)
         return;
     const dbl2 *src = in + (size_t)(1 - p) * 12 * Vh;
     cplx<double> acc[4][3];
-    wilson_hop<ROWS, LPS, LP>(g, links + link_parity_entries(ROWS, Vh) * p, p, s, sub, acc,
+    const int64_t lp = link_parity_entries(ROWS, Vh);
+    wilson_hop<ROWS, LPS, LP>(g, links + lp * p, links + lp * (1 - p), p, s, sub, acc,
                           [&](int n, int sp, int col) { return comp(src, Vh, n, sp, col); });
     dbl2 *o = out + (size_t)p * 12 * Vh;
 #pragma unroll
@@ -256,7 +286,7 @@ static_assert(sizeof(WState) == 96, "state layout");
 
 struct WArgs {
     Geom g;
-    const dbl2 *links[2];  // per output parity
+    const dbl2 *links[2];  // per parity of their site
     double kappa;
     const dbl2 *b;         // caller's source [2][12][Vh]
     dbl2 *x;               // caller's solution [2][12][Vh]; even half iterated, odd half at the end
@@ -351,7 +381,7 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
         return;
     const dbl2 *bo = a.b + (size_t)12 * Vh;
     cplx<double> acc[4][3];
-    wilson_hop<ROWS, LPS, LP>(a.g, a.links[0], 0, s, sub, acc,
+    wilson_hop<ROWS, LPS, LP>(a.g, a.links[0], a.links[1], 0, s, sub, acc,
                           [&](int n, int sp, int col) { return comp(bo, Vh, n, sp, col); });
 #pragma unroll
     for (int sp = 0; sp < 4; ++sp)
@@ -375,7 +405,7 @@ __global__ void __launch_bounds__(128) k_wil_odd_g5(WArgs a, const dbl2 *__restr
     if (!wsite<LPS>(Vh, a.remap, s, sub))
         return;
     cplx<double> acc[4][3];
-    wilson_hop<ROWS, LPS, LP>(a.g, a.links[1], 1, s, sub, acc, [&](int n, int sp, int col) {
+    wilson_hop<ROWS, LPS, LP>(a.g, a.links[1], a.links[0], 1, s, sub, acc, [&](int n, int sp, int col) {
         const cplx<double> z = comp(src, Vh, n, sp, col);
         return sp < 2 ? z : cplx<double>{-z.re, -z.im};
     });
@@ -397,7 +427,7 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
     double nrm = 0.0;
     if (wsite<LPS>(Vh, a.remap, s, sub)) {
         cplx<double> acc[4][3];
-        wilson_hop<ROWS, LPS, LP>(a.g, a.links[0], 0, s, sub, acc,
+        wilson_hop<ROWS, LPS, LP>(a.g, a.links[0], a.links[1], 0, s, sub, acc,
                               [&](int n, int sp, int col) { return comp(a.t, Vh, n, sp, col); });
         const double k2 = a.kappa * a.kappa;
 #pragma unroll
@@ -491,7 +521,7 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
     if (!wsite<LPS>(Vh, a.remap, s, sub))
         return;
     cplx<double> acc[4][3];
-    wilson_hop<ROWS, LPS, LP>(a.g, a.links[1], 1, s, sub, acc, [&](int n, int sp, int col) {
+    wilson_hop<ROWS, LPS, LP>(a.g, a.links[1], a.links[0], 1, s, sub, acc, [&](int n, int sp, int col) {
         const cplx<double> r = comp(a.r, Vh, n, sp, col), p = comp(pold, Vh, n, sp, col);
         return cplx<double>{fma(beta, p.re, r.re), fma(beta, p.im, r.im)};
     });
@@ -521,7 +551,7 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
     double nrm = 0.0;
     if (wsite<LPS>(Vh, a.remap, s, sub)) {
         cplx<double> acc[4][3];
-        wilson_hop<ROWS, LPS, LP>(a.g, a.links[0], 0, s, sub, acc,
+        wilson_hop<ROWS, LPS, LP>(a.g, a.links[0], a.links[1], 0, s, sub, acc,
                               [&](int n, int sp, int col) { return comp(a.t, Vh, n, sp, col); });
         const double k2 = a.kappa * a.kappa;
 #pragma unroll
@@ -559,7 +589,7 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
     double nrm = 0.0;
     if (wsite<LPS>(Vh, a.remap, s, sub)) {
         cplx<double> acc[4][3];
-        wilson_hop<ROWS, LPS, LP>(a.g, a.links[0], 0, s, sub, acc,
+        wilson_hop<ROWS, LPS, LP>(a.g, a.links[0], a.links[1], 0, s, sub, acc,
                               [&](int n, int sp, int col) { return comp(a.t, Vh, n, sp, col); });
         const double k2 = a.kappa * a.kappa;
 #pragma unroll
@@ -591,7 +621,7 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
     if (!wsite<LPS>(Vh, a.remap, s, sub))
         return;
     cplx<double> acc[4][3];
-    wilson_hop<ROWS, LPS, LP>(a.g, a.links[1], 1, s, sub, acc,
+    wilson_hop<ROWS, LPS, LP>(a.g, a.links[1], a.links[0], 1, s, sub, acc,
                           [&](int n, int sp, int col) { return comp(a.x, Vh, n, sp, col); });
     const dbl2 *bo = a.b + (size_t)12 * Vh;
     dbl2 *xo = a.x + (size_t)12 * Vh;
@@ -616,7 +646,7 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
     if (wsite<LPS>(Vh, a.remap, s, sub)) {
         const dbl2 *xin = a.x + (size_t)(1 - par) * 12 * Vh;
         cplx<double> acc[4][3];
-        wilson_hop<ROWS, LPS, LP>(a.g, a.links[par], par, s, sub, acc,
+        wilson_hop<ROWS, LPS, LP>(a.g, a.links[par], a.links[1 - par], par, s, sub, acc,
                               [&](int n, int sp, int col) { return comp(xin, Vh, n, sp, col); });
         const dbl2 *bp = a.b + (size_t)par * 12 * Vh;
         const dbl2 *xp = a.x + (size_t)par * 12 * Vh;
