@@ -342,7 +342,7 @@ int wilson_cg_solve(Ctx *ctx, GaugeField *f, double kappa, double tol, int maxit
     const int nblk_max = (int)(((int64_t)Vh * 8 + kWBlock - 1) / kWBlock);
     const int pstride = (nblk_max + 63) & ~63;
     const size_t vec = (size_t)12 * Vh * sizeof(dbl2);
-    const size_t bytes = 6 * vec + 256 + (size_t)4 * pstride * sizeof(double);
+    const size_t bytes = 5 * vec + 256 + (size_t)4 * pstride * sizeof(double);
     char *mem = (char *)ctx->arena.alloc(bytes);
     if (!mem)
         return set_error(STAG_ENOMEM, "arena exhausted: Wilson CG workspace needs %zu bytes", bytes);
@@ -366,13 +366,12 @@ int wilson_cg_solve(Ctx *ctx, GaugeField *f, double kappa, double tol, int maxit
     a.x = (dbl2 *)x;
     a.bh = (dbl2 *)mem;
     a.r = (dbl2 *)(mem + vec);
-    a.p[0] = (dbl2 *)(mem + 2 * vec);
-    a.p[1] = (dbl2 *)(mem + 3 * vec);
-    a.ap = (dbl2 *)(mem + 4 * vec);
-    a.t = (dbl2 *)(mem + 5 * vec);
-    a.st[0] = (wil::WState *)(mem + 6 * vec);
+    a.p = (dbl2 *)(mem + 2 * vec);
+    a.ap = (dbl2 *)(mem + 3 * vec);
+    a.t = (dbl2 *)(mem + 4 * vec);
+    a.st[0] = (wil::WState *)(mem + 5 * vec);
     a.st[1] = a.st[0] + 1;
-    a.partials = (double *)(mem + 6 * vec + 256);
+    a.partials = (double *)(mem + 5 * vec + 256);
     a.pstride = pstride;
 
     wil::WState *host = nullptr;
@@ -397,9 +396,9 @@ int wilson_cg_solve(Ctx *ctx, GaugeField *f, double kappa, double tol, int maxit
     host[1] = host[0];
     STAG_HIP_CHECK(hipMemcpyAsync(a.st[0], host, 2 * sizeof(wil::WState), hipMemcpyHostToDevice, s));
 
-    // lanes per site: tuned on this workspace (bh|r and p[0]|p[1] are two
-    // adjacent full-field vectors) before the solve uses it
-    const KernelCfg cfg = wilson_cfg(ctx, f, (const double *)a.bh, (double *)a.p[0], s);
+    // lanes per site: tuned on this workspace (bh|r and p|ap are two full-field
+    // vectors) before the solve uses it
+    const KernelCfg cfg = wilson_cfg(ctx, f, (const double *)a.bh, (double *)a.p, s);
     const int lps = cfg.lps;
     a.remap = cfg.remap;
     const WTable &tab = wilson_table(f, lps);

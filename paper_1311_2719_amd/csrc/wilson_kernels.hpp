@@ -278,9 +278,8 @@ struct WState {
     int32_t status;
     int32_t iters;
     int32_t maxiter;
-    int32_t pcur;  // buffer holding the current direction
     int32_t step;
-    int32_t pad1[2];
+    int32_t pad1[3];
 };
 static_assert(sizeof(WState) == 96, "state layout");
 
@@ -292,8 +291,8 @@ struct WArgs {
     dbl2 *x;               // caller's solution [2][12][Vh]; even half iterated, odd half at the end
     dbl2 *bh;              // even: b_e + kappa D_eo b_o
     dbl2 *r;               // even
-    dbl2 *p[2];            // even, two buffers
-    dbl2 *ap;              // even: Mhat p'
+    dbl2 *p;               // even
+    dbl2 *ap;              // even: Mhat p
     dbl2 *t;               // odd work vector
     WState *st[2];
     double *partials;      // [2 buffers][2 slots: 0 <ap,ap>, 1 <r,r>][pstride]
@@ -418,7 +417,7 @@ __global__ void __launch_bounds__(128) k_wil_odd_g5(WArgs a, const dbl2 *__restr
 }
 
 // init 3 (even outputs): r = bh - kappa^2 gamma_5 (H t)_e = Mhat^dagger bh;
-// p[0] = r; x_e = 0; <r,r> into slot 1 of buffer 0
+// x_e = 0; <r,r> into slot 1 of buffer 0
 template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_wil_init(WArgs a)
 {
     __shared__ double lds[4];
@@ -440,7 +439,6 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
                 const cplx<double> bh = comp(a.bh, Vh, s, sp, c);
                 const cplx<double> r = {bh.re - g5 * acc[sp][c].re, bh.im - g5 * acc[sp][c].im};
                 put(a.r, Vh, s, sp, c, r);
-                put(a.p[0], Vh, s, sp, c, r);
                 put(a.x, Vh, s, sp, c, czero<double>());
                 nrm += r.re * r.re + r.im * r.im;
             }
@@ -448,14 +446,50 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
     wpartial(a, 0, 1, nrm, lds);
 }
 
-// K1 (odd outputs): advance the state over the previous step, then
-// t = H_oe p' with p' = r + beta p formed at every gathered neighbour; p' is
-// also stored at the partner site (same index, even parity).
+// A step, with ap = Mhat p carried by a recurrence (ap' = Mhat r + beta ap for
+// p' = r + beta p; its relative rounding is that of the recurrence of p):
+//   K1  t = H_oe r, no scalar needed;
+//   K2  beta, then ap' = r - kappa^2 H_eo t + beta ap and <ap',ap'>;
+//   K3  t = H_oe gamma_5 ap';
+//   K4  alpha, then p' = r + beta p, x += alpha p', r -= alpha Mhat^dagger ap'
+//       (= ap' - kappa^2 gamma_5 H_eo t) and <r,r>.
+// The direct form gathered r and p at every neighbour in K1 (3 KB a site
+// instead of 1.5), and its prologue ran before K1's hop.
+
+// K1 (odd outputs): t = H_oe r while the system iterates (or has not begun)
 template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_wil_step1(WArgs a, int ver)
+{
+    const int mode = a.st[ver]->mode;
+    if (mode != W_CG && mode != W_INIT)
+        return;
+    const int Vh = a.g.Vh;
+    int s, sub;
+    if (!wsite<LPS>(Vh, a.remap, s, sub))
+        return;
+    cplx<double> acc[4][3];
+    wilson_hop<ROWS, LPS, LP>(a.g, a.links[1], a.links[0], 1, s, sub, acc,
+                              [&](int n, int sp, int col) { return comp(a.r, Vh, n, sp, col); });
+#pragma unroll
+    for (int sp = 0; sp < 4; ++sp)
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            if (owns_component<LPS>(sub, sp, c))
+                put(a.t, Vh, s, sp, c, acc[sp][c]);
+}
+
+// K2 (even outputs): advance the state over the previous step, then
+// ap' = r - kappa^2 (H t)_e + beta ap; <ap',ap'> into slot 0 of buffer ver^1
+template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_wil_step2(WArgs a, int ver)
 {
     __shared__ double lds[8];
     __shared__ __align__(16) WState sst;
     const int Vh = a.g.Vh, nblk = gridDim.x;
+    const int mode0 = a.st[ver]->mode;
+    if (mode0 != W_CG && mode0 != W_INIT) {
+        if (blockIdx.x == 0 && threadIdx.x == 0)
+            *a.st[ver ^ 1] = *a.st[ver];  // pass the final state on
+        return;
+    }
     if (threadIdx.x < sizeof(WState) / 16)
         ((uint4 *)&sst)[threadIdx.x] = ((const uint4 *)a.st[ver])[threadIdx.x];
     double tot[2];
@@ -463,7 +497,6 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
     if (threadIdx.x == 0) {
         WState st = sst;
         st.step += 1;
-        bool run = false;
         if (st.mode == W_INIT) {
             const double bb = tot[1];
             st.bb = bb;
@@ -482,9 +515,8 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
                 st.status = STAG_ENOCONV;
             } else {
                 st.mode = W_CG;
-                run = true;
             }
-        } else if (st.mode == W_CG) {
+        } else {
             const double pap = tot[0], rn = tot[1];
             st.iters += 1;
             if (!wfinite_pos(pap) || !(rn < INFINITY)) {
@@ -501,11 +533,8 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
             } else {
                 st.beta = rn / st.rr;
                 st.rr = rn;
-                run = true;
             }
         }
-        if (run)
-            st.pcur ^= 1;  // p' goes to the other buffer
         if (blockIdx.x == 0)
             *a.st[ver ^ 1] = st;
         sst = st;
@@ -514,45 +543,12 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
     if (wuniform(sst.mode) != W_CG)
         return;
     const double beta = wuniform(sst.beta);
-    const int pn = wuniform(sst.pcur);
-    const dbl2 *pold = a.p[pn ^ 1];
-    dbl2 *pnew = a.p[pn];
-    int s, sub;
-    if (!wsite<LPS>(Vh, a.remap, s, sub))
-        return;
-    cplx<double> acc[4][3];
-    wilson_hop<ROWS, LPS, LP>(a.g, a.links[1], a.links[0], 1, s, sub, acc, [&](int n, int sp, int col) {
-        const cplx<double> r = comp(a.r, Vh, n, sp, col), p = comp(pold, Vh, n, sp, col);
-        return cplx<double>{fma(beta, p.re, r.re), fma(beta, p.im, r.im)};
-    });
-#pragma unroll
-    for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            if (!owns_component<LPS>(sub, sp, c))
-                continue;
-            put(a.t, Vh, s, sp, c, acc[sp][c]);
-            const cplx<double> r = comp(a.r, Vh, s, sp, c), p = comp(pold, Vh, s, sp, c);
-            put(pnew, Vh, s, sp, c, {fma(beta, p.re, r.re), fma(beta, p.im, r.im)});
-        }
-}
-
-// K2 (even outputs): ap = p' - kappa^2 (H t)_e = Mhat p'; <ap,ap> into slot 0
-// of buffer ver^1
-template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_wil_step2(WArgs a, int ver)
-{
-    __shared__ double lds[4];
-    const WState *st = a.st[ver ^ 1];
-    if (st->mode != W_CG)
-        return;
-    const dbl2 *pn = a.p[wuniform(st->pcur)];
-    const int Vh = a.g.Vh;
     int s, sub;
     double nrm = 0.0;
     if (wsite<LPS>(Vh, a.remap, s, sub)) {
         cplx<double> acc[4][3];
         wilson_hop<ROWS, LPS, LP>(a.g, a.links[0], a.links[1], 0, s, sub, acc,
-                              [&](int n, int sp, int col) { return comp(a.t, Vh, n, sp, col); });
+                                  [&](int n, int sp, int col) { return comp(a.t, Vh, n, sp, col); });
         const double k2 = a.kappa * a.kappa;
 #pragma unroll
         for (int sp = 0; sp < 4; ++sp)
@@ -560,8 +556,12 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
             for (int c = 0; c < 3; ++c) {
                 if (!owns_component<LPS>(sub, sp, c))
                     continue;
-                const cplx<double> p = comp(pn, Vh, s, sp, c);
-                const cplx<double> v = {p.re - k2 * acc[sp][c].re, p.im - k2 * acc[sp][c].im};
+                const cplx<double> r = comp(a.r, Vh, s, sp, c);
+                cplx<double> v = {r.re - k2 * acc[sp][c].re, r.im - k2 * acc[sp][c].im};
+                if (beta != 0.0) {  // beta = 0 starts from ap = 0, whatever the buffer holds
+                    const cplx<double> o = comp(a.ap, Vh, s, sp, c);
+                    v = {fma(beta, o.re, v.re), fma(beta, o.im, v.im)};
+                }
                 put(a.ap, Vh, s, sp, c, v);
                 nrm += v.re * v.re + v.im * v.im;
             }
@@ -569,9 +569,9 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
     wpartial(a, ver ^ 1, 0, nrm, lds);
 }
 
-// K4 (even outputs): alpha = rr / <ap,ap>; atap = ap - kappa^2 gamma_5 (H t)_e
-// (= Mhat^dagger Mhat p'); x += alpha p'; r -= alpha atap; <r,r> into slot 1 of
-// buffer ver^1
+// K4 (even outputs): alpha = rr / <ap',ap'>; p' = r + beta p; atap = ap' -
+// kappa^2 gamma_5 (H t)_e (= Mhat^dagger Mhat p'); x += alpha p'; r -= alpha
+// atap; <r,r> into slot 1 of buffer ver^1
 template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_wil_step4(WArgs a, int ver)
 {
     __shared__ double lds[8];
@@ -579,8 +579,7 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
     if (st->mode != W_CG)
         return;
     const int cur = ver ^ 1;
-    const double rr = wuniform(st->rr);
-    const dbl2 *pn = a.p[wuniform(st->pcur)];
+    const double rr = wuniform(st->rr), beta = wuniform(st->beta);
     double tot[1];
     wtotals<1>(a, cur, gridDim.x, lds, tot);
     const double alpha = wfinite_pos(tot[0]) ? rr / tot[0] : 0.0;
@@ -601,10 +600,15 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
                 const double g5 = sp < 2 ? k2 : -k2;
                 const cplx<double> ap = comp(a.ap, Vh, s, sp, c);
                 const cplx<double> atap = {ap.re - g5 * acc[sp][c].re, ap.im - g5 * acc[sp][c].im};
-                const cplx<double> p = comp(pn, Vh, s, sp, c);
+                cplx<double> r = comp(a.r, Vh, s, sp, c);
+                cplx<double> p = r;
+                if (beta != 0.0) {
+                    const cplx<double> o = comp(a.p, Vh, s, sp, c);
+                    p = {fma(beta, o.re, r.re), fma(beta, o.im, r.im)};
+                }
+                put(a.p, Vh, s, sp, c, p);
                 const cplx<double> x = comp(a.x, Vh, s, sp, c);
                 put(a.x, Vh, s, sp, c, {fma(alpha, p.re, x.re), fma(alpha, p.im, x.im)});
-                cplx<double> r = comp(a.r, Vh, s, sp, c);
                 r = {fma(-alpha, atap.re, r.re), fma(-alpha, atap.im, r.im)};
                 put(a.r, Vh, s, sp, c, r);
                 nrm += r.re * r.re + r.im * r.im;
