@@ -9,6 +9,7 @@
 #include <cstring>
 
 #include "batch.hpp"
+#include "cg_persist.hpp"
 
 namespace stag {
 
@@ -58,6 +59,7 @@ size_t Batch::workspace_bytes(const Geom &g, int prec, int slots, int pstride)
     b += align256(nsys * sizeof(SysState)) * 2;                  // two state buffers
     b += align256(nsys * sizeof(int));                           // tile order
     b += align256(2 * nsys * 3 * (size_t)pstride * sizeof(double));  // partials
+    b += slots == 1 ? align256(cg_persist_bytes()) : 0;          // one-launch solves
     return b;
 }
 
@@ -208,7 +210,7 @@ hipError_t Batch::launch_scalars(hipStream_t st, const CgArgs &a, int ver, int k
 size_t Batch::host_bytes_for(int slots)
 {
     const size_t nsys = 2 * (size_t)slots;
-    return 3 * nsys * sizeof(SysState) + 2 * nsys * sizeof(void *) + nsys * sizeof(int);
+    return 3 * nsys * sizeof(SysState) + 2 * nsys * sizeof(void *) + (nsys + 1) * sizeof(int);
 }
 
 // Partial sums per slot: the widest grid row any shape may use (register
@@ -244,6 +246,7 @@ void Batch::carve(void *base)
     st_d_[1] = st_d_[0] + nsys;
     perm_d_ = (int *)take(nsys * sizeof(int));
     partials_ = (double *)take(2 * nsys * 3 * (size_t)pstride_ * sizeof(double));
+    persist_slots_ = S_ == 1 ? take(cg_persist_bytes()) : nullptr;
 }
 
 int Batch::mark_stage()
@@ -265,13 +268,14 @@ void Batch::wait_stage()
     stage_busy_ = false;
 }
 
-int Batch::create(bool own_work)
+int Batch::create(bool single)
 {
+    single_ = single;
     const Geom &g = f_->g;
     pstride_ = pstride_for(g);
     bytes_ = workspace_bytes(g, prec_, S_, pstride_);
     int idle = 0;
-    if (own_work && f_->work && bytes_ <= f_->work_bytes && f_->work_taken.compare_exchange_strong(idle, 1)) {
+    if (single && f_->work && bytes_ <= f_->work_bytes && f_->work_taken.compare_exchange_strong(idle, 1)) {
         mem_ = f_->work;
         field_mem_ = true;
     } else {
@@ -293,7 +297,7 @@ int Batch::create(bool own_work)
 
 int Batch::create_external(void *dev, size_t dev_bytes, void *host, size_t host_bytes)
 {
-    external_ = true;
+    external_ = single_ = true;
     use_graphs_ = false;
     pstride_ = pstride_for(f_->g);
     bytes_ = workspace_bytes(f_->g, prec_, S_, pstride_);
@@ -313,10 +317,16 @@ int Batch::finish_create()
     xhi_h_ = (dbl2 **)(snap_ + 2 * nsys);
     b_h_ = (const dbl2 **)(xhi_h_ + nsys);
     perm_h_ = (int *)(b_h_ + nsys);
+    abort_h_ = perm_h_ + nsys;
     memset(stage_, 0, host_bytes_for(S_));
     for (size_t j = 0; j < nsys; ++j)
         perm_h_[j] = (int)j;
     perm_last_.assign(perm_h_, perm_h_ + nsys);
+    // one launch for a whole solve where the field allows it; a forced shape of
+    // the step kernels asks for those
+    const char *forced = getenv("STAG_KERNEL_CFG");
+    persist_ = S_ == 1 && single_ && !(forced && *forced) &&
+               cg_persist_plan(ctx_->num_cus, f_->g, prec_, f_->rows, persist_plan_);
     // kernel shape for this (field, precision, slots): tuned on this workspace
     const uint64_t key = ((uint64_t)1 << 40) | ((uint64_t)prec_ << 32) | (uint32_t)S_;
     bool have = false;
@@ -340,6 +350,10 @@ int Batch::finish_create()
         }
     } else if (external_) {
         cfg_ = default_cg_cfg();  // no timing runs without events; not cached
+    } else if (persist_) {
+        cfg_ = default_cg_cfg();  // the step kernels only step in if the one launch gives up: not timed
+        std::lock_guard<std::mutex> lk(ctx_->mu);
+        f_->tuned[key] = cfg_;
     } else {
         cfg_ = tune_cg();  // also fills small_
         std::lock_guard<std::mutex> lk(ctx_->mu);
@@ -366,7 +380,7 @@ int Batch::finish_create()
         return rc;
     // record the epochs the solve driver chooses from (powers of two), for
     // every tile shape, now, outside any solve
-    for (int E = 2; use_graphs_ && E <= kEpochMax; E *= 2) {
+    for (int E = 2; use_graphs_ && !persist_ && E <= kEpochMax; E *= 2) {
         rc = record_epoch(E, cfg_);
         for (size_t i = 0; i < small_.size() && rc == STAG_OK; ++i)
             rc = record_epoch(E, small_[i]);
@@ -713,7 +727,7 @@ int Batch::upload_and_init(const std::vector<int> &systems)
         }
     }
     int rc = mark_stage();
-    if (rc != STAG_OK)
+    if (rc != STAG_OK || persist_)  // the one launch initialises by itself
         return rc;
     const CgArgs a = args();
     const CgLaunchTable &t = cg_table(prec_, f_->rows, f_->nt_links);
@@ -869,6 +883,48 @@ int Batch::wait_snapshot()
     else
         STAG_HIP_CHECK(hipEventSynchronize(snap_ev_));
     return STAG_OK;
+}
+
+// Steps of one launch: a solve longer than this takes several, so that other
+// threads' solves get their turn.
+constexpr int kPersistSteps = 1024;
+
+int Batch::solve_in_one_launch(bool &gave_up)
+{
+    const CgArgs a = args();
+    gave_up = false;
+    STAG_HIP_CHECK(hipMemsetAsync(persist_slots_, 0, cg_persist_bytes(), s_));
+    uint32_t seq = 0;
+    for (;;) {
+        {
+            std::lock_guard<std::mutex> lk(persist_lock(ctx_->device));
+            const hipError_t e = cg_persist_launch(persist_plan_, prec_, f_->rows, a, persist_slots_, seq, kPersistSteps, s_);
+            if (e != hipSuccess)
+                return set_error(STAG_EHIP, "CG launch failed: %s", hipGetErrorString(e));
+            STAG_HIP_CHECK(hipMemcpyAsync(abort_h_, (char *)persist_slots_ + cg_persist_abort_offset(), sizeof(int),
+                                          hipMemcpyDeviceToHost, s_));
+            int rc = enqueue_snapshot();
+            if (rc == STAG_OK)
+                rc = wait_snapshot();
+            if (rc != STAG_OK)
+                return rc;
+        }
+        if (*abort_h_) {
+            gave_up = true;
+            persist_ = false;  // this workspace keeps to the step kernels
+            return STAG_OK;
+        }
+        seq += 3 * kPersistSteps + 1;
+        bool done = true;
+        for (int j = 0; j < nsys(); ++j)
+            done &= state(j).mode == M_DONE || state(j).mode == M_IDLE;
+        if (done)
+            return STAG_OK;
+        if (seq > 0xf0000000u) {  // sequence numbers start again on cleared words
+            STAG_HIP_CHECK(hipMemsetAsync(persist_slots_, 0, cg_persist_bytes(), s_));
+            seq = 0;
+        }
+    }
 }
 
 bool Batch::snapshot_ready() { return (external_ ? hipStreamQuery(s_) : hipEventQuery(snap_ev_)) == hipSuccess; }
@@ -1073,6 +1129,15 @@ static int run_solve(Ctx *ctx, Batch &B, const std::shared_ptr<GaugeField> &f, i
     B.set_parities(parities);
     if ((rc = B.upload_and_init(systems)) != STAG_OK || (rc = B.set_running(running)) != STAG_OK)
         return rc;
+    bool done = false;
+    if (B.persistent()) {
+        bool gave_up = false;
+        if ((rc = B.solve_in_one_launch(gave_up)) != STAG_OK)
+            return rc;
+        done = !gave_up;
+        if (gave_up && (rc = B.upload_and_init(systems)) != STAG_OK)  // from the start
+            return rc;
+    }
     int E = 8, Emax = kEpochMax;
     const bool fixed_epoch = getenv("STAG_EPOCH") != nullptr;
     const bool epoch_log = getenv("STAG_EPOCH_VERBOSE") != nullptr;
@@ -1080,10 +1145,10 @@ static int run_solve(Ctx *ctx, Batch &B, const std::shared_ptr<GaugeField> &f, i
         E = Emax = std::max(1, atoi(getenv("STAG_EPOCH")));
     std::vector<ConvergenceTrack> track(B.nsys());
     // pipelined: epoch n+1 is queued before the state after epoch n is read
-    if ((rc = B.enqueue_epoch(E)) != STAG_OK || (rc = B.enqueue_snapshot()) != STAG_OK)
+    if (!done && ((rc = B.enqueue_epoch(E)) != STAG_OK || (rc = B.enqueue_snapshot()) != STAG_OK))
         return rc;
+    const bool one_launch = done;
     int64_t budget = (int64_t)(max_iter + 1) * (int64_t)(2 + params[0].max_restarts) + 4096;
-    bool done = false;
     while (!done && budget > 0) {
         if ((rc = B.enqueue_epoch(E)) != STAG_OK)
             return rc;
@@ -1130,7 +1195,7 @@ static int run_solve(Ctx *ctx, Batch &B, const std::shared_ptr<GaugeField> &f, i
                 return rc;
         }
     }
-    if ((rc = B.enqueue_snapshot()) != STAG_OK || (rc = B.wait_snapshot()) != STAG_OK)
+    if (!one_launch && ((rc = B.enqueue_snapshot()) != STAG_OK || (rc = B.wait_snapshot()) != STAG_OK))
         return rc;
     // y = D x on the opposite parity of every solved system (Sec. 4, second half)
     int first_err = STAG_OK;
@@ -1193,6 +1258,21 @@ int cg_solve_batch(Ctx *ctx, const std::shared_ptr<GaugeField> &f, int nrhs, con
     return rc;
 }
 
+// What stag_cg_solve_noalloc counts against its limit: p (two buffers), D p, r,
+// x_lo and the FP64 work vector of two systems, their tables, states, partial
+// sums (at most 4096 per slot) and totals.  The workspace in use differs by less
+// than the MiB the buffer has beyond the limit.
+static size_t noalloc_bytes(const Geom &g, int prec)
+{
+    const size_t Vh = g.Vh;
+    const int most = std::max(std::min(2048, blocks_for(g.Vh, 8, 64)), (g.Vh + kChunk - 1) / kChunk);
+    const size_t pst = (size_t)((std::min(4096, most) + 63) & ~63);
+    return align256(2 * Vh * spinor_bytes_of(prec)) * 3 + align256(6 * Vh * (prec == 0 ? 16 : 8)) +
+           (prec == 0 ? 0 : align256(6 * Vh * 8)) + align256(6 * Vh * 16) + align256(2 * sizeof(void *)) * 2 +
+           align256(2 * sizeof(SysState)) * 2 + align256(2 * sizeof(int)) + align256(12 * pst * sizeof(double)) +
+           align256(12 * sizeof(double));
+}
+
 int cg_solve_fixed(Ctx *ctx, const std::shared_ptr<GaugeField> &f, const stag_cg_params *params, const double *b,
                    double *x, double *y, hipStream_t s, stag_cg_info *info, void *dev, size_t dev_bytes, void *host,
                    size_t host_bytes)
@@ -1201,9 +1281,9 @@ int cg_solve_fixed(Ctx *ctx, const std::shared_ptr<GaugeField> &f, const stag_cg
     if (rc != STAG_OK)
         return rc;
     Batch B(ctx, f, params->precision, 1, s);
-    if (B.needed_bytes() > dev_bytes)
+    if (noalloc_bytes(f->g, params->precision) > STAG_NOALLOC_WORKSPACE_BYTES)
         return set_error(STAG_EINVAL, "the solve needs a %zu-byte workspace; the fixed workspace holds %zu bytes",
-                         B.needed_bytes(), dev_bytes);
+                         noalloc_bytes(f->g, params->precision), STAG_NOALLOC_WORKSPACE_BYTES);
     rc = B.create_external(dev, dev_bytes, host, host_bytes);
     if (rc != STAG_OK)
         return rc;

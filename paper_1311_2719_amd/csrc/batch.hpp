@@ -6,6 +6,7 @@
 #include <vector>
 
 #include "cg_launch.hpp"
+#include "cg_persist.hpp"
 #include "runtime.hpp"
 
 namespace stag {
@@ -20,10 +21,11 @@ public:
     Batch(const Batch &) = delete;
     Batch &operator=(const Batch &) = delete;
 
-    // Allocate workspace from the arena (own_work: the field's own workspace if
-    // it is free and large enough) and pinned host mirrors.  ENOMEM if the
+    // Allocate workspace from the arena (single: for blocking solves of one
+    // source, which may use the field's own workspace if it is free and large
+    // enough, and run in one launch) and pinned host mirrors.  ENOMEM if the
     // arena cannot hold it.
-    int create(bool own_work = false);
+    int create(bool single = false);
     // Use caller-provided memory instead: `dev` (device, dev_bytes >=
     // workspace_bytes) and `host` (ordinary host memory, host_bytes >=
     // host_bytes_for(slots)).  Nothing is allocated: no arena, pinned memory,
@@ -69,6 +71,11 @@ public:
     // `running` first (per parity), the rest left out.  Stream-ordered: applies
     // to the kernels enqueued after this call.
     int set_running(const std::vector<char> &running);
+    // Whether a solve runs in one launch (cg_persist.hip); solve_in_one_launch
+    // runs the staged systems to their end, or gives up (gave_up: a block waited
+    // too long for another; the solve must start again with the step kernels).
+    bool persistent() const { return persist_; }
+    int solve_in_one_launch(bool &gave_up);
     // Parities the step kernels cover from now on (bit 0 even, bit 1 odd): a
     // solve of one parity launches no blocks for the other.
     void set_parities(int mask) { parities_ = mask; }
@@ -121,12 +128,17 @@ private:
     SysState *st_d_[2] = {nullptr, nullptr};
     int *perm_d_ = nullptr;
     double *partials_ = nullptr;
+    bool single_ = false;   // blocking solves of one source
+    bool persist_ = false;  // solves run in one launch
+    PersistPlan persist_plan_;
+    void *persist_slots_ = nullptr;
     // pinned host memory
     SysState *stage_ = nullptr;   // [nsys] staged initial states
     SysState *snap_ = nullptr;    // [2][nsys] last snapshot of both state buffers
     dbl2 **xhi_h_ = nullptr;
     const dbl2 **b_h_ = nullptr;
     int *perm_h_ = nullptr;
+    int *abort_h_ = nullptr;
     std::vector<int> perm_last_;
     hipEvent_t snap_ev_ = nullptr, stage_ev_ = nullptr;
     std::vector<SysState> tune_st_;  // states a timed shape starts from

@@ -19,7 +19,10 @@ namespace stag {
 // 128 MiB: an FP64 solve of one right-hand side needs about 480 bytes per
 // checkerboard site (a 24^4 lattice, 331 776 sites: 80 MB); FP32 and FP16
 // solves less.
-constexpr size_t kScratchBytes = (size_t)128 << 20;
+// The interface's limit is counted with two search-direction buffers and at
+// most 4096 partial sums per slot (noalloc_bytes); the extra MiB holds the
+// partial sums and exchange words beyond that.
+constexpr size_t kScratchBytes = STAG_NOALLOC_WORKSPACE_BYTES + ((size_t)1 << 20);
 constexpr int kMaxDevices = 64;
 constexpr size_t kHostBytes = 4096;  // host mirror of one solve's state records
 
