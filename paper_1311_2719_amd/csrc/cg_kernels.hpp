@@ -112,19 +112,6 @@ template <class P> __device__ __forceinline__ void *spin_at(void *base, int j, i
     return (char *)base + (size_t)j * Vh * P::spinor_bytes;
 }
 
-template <class P> __device__ __forceinline__ cplx<typename P::real> load_colour(const void *base, int Vh, int s, int c)
-{
-    if constexpr (P::id == 2) {
-        cplx<typename P::real> v[3];
-        P::load_spinor(base, Vh, s, v);
-        return v[c];
-    } else {
-        using v2 = typename vec2_of<typename P::real>::type;
-        v2 t = ((const v2 *)base)[(int64_t)c * Vh + s];
-        return {t.x, t.y};
-    }
-}
-
 // Whether precision P runs the recurrence form (see the top of the file).
 template <class P> constexpr bool kRecurrence = P::id != 2;
 
@@ -449,9 +436,11 @@ template <class P, int R, int LPS> struct OwnSite {
         }
     }
     // K2: p (recurrence form: the last direction; direct form: p'), x and r of systems r0 .. r0 + G - 1 at the own site.
-    // x is read and written once per step, at its own site only: non-temporal
-    // accesses keep it from evicting the gathered vectors (32^4 solves: FP16
-    // +6%, FP32 +2%, FP64 unchanged; 16^4 within 1%).
+    // x, and in the recurrence form p, are read and written once per step, at
+    // their own site only: non-temporal accesses keep them from evicting the
+    // gathered vectors (32^4 step, x and p instead of x alone: FP32 118.8 -> 114.2 us,
+    // FP64 275 -> 271; 24^4 within 1%; batched K2 of 24 systems at 24^4, neither ->
+    // x -> both: FP32 188 -> 179 -> 160 us, FP16 155 -> 141).
     template <class Args>
     __device__ __forceinline__ void load_k2(const Args &a, const int *js, const bool *cg, const int *pn, int s,
                                             int sub, int r0)
@@ -472,8 +461,10 @@ template <class P, int R, int LPS> struct OwnSite {
                 if (!owns_colour<LPS>(sub, c))
                     continue;
                 const int64_t o = (int64_t)c * Vh + s;
-                if constexpr (P::id != 2)
-                    ps_[q][c] = load_colour<P>(pb, Vh, s, c);
+                if constexpr (P::id != 2) {
+                    const v2 t = __builtin_nontemporal_load((const v2 *)pb + o);
+                    ps_[q][c] = {t.x, t.y};
+                }
                 if constexpr (P::id == 0)
                     xx_[q][c] = __builtin_nontemporal_load(&a.xhi[j][o]);
                 else
@@ -985,7 +976,7 @@ __device__ __forceinline__ void step2_recurrence(const CgArgs &a, int ver)
                     // beta = 0 starts from p = 0, whatever the buffer holds
                     const v2 po = v2{own.ps_[q][c].re, own.ps_[q][c].im};
                     const v2 pn = beta[r] != real(0) ? v2{fma(beta[r], po.x, rr.x), fma(beta[r], po.y, rr.y)} : rr;
-                    pv[o] = pn;
+                    __builtin_nontemporal_store(pn, &pv[o]);
                     const auto xv = own.xx_[q][c];
                     if constexpr (P::id == 0)
                         __builtin_nontemporal_store(dbl2{fma(alpha[r], pn.x, xv.x), fma(alpha[r], pn.y, xv.y)},

@@ -545,10 +545,17 @@ __global__ void __launch_bounds__(64 * W, kSharedMinWaves) k_cg_shared2(CgArgs a
                     if (!cg[q])
                         continue;
                     const int j = js[q];
-                    P::load_spinor(spin_at<P>(a.p[pn_buf[q]], j, Vh), Vh, s, pv[q]);
+                    // x and p (FP32) non-temporally, as in the register tiles
+                    const void *pb = spin_at<P>(a.p[pn_buf[q]], j, Vh);
+                    if constexpr (!kRecurrence<P>)
+                        P::load_spinor(pb, Vh, s, pv[q]);
 #pragma unroll
                     for (int c = 0; c < 3; ++c) {
-                        xv[q][c] = a.xlo[(size_t)j * 3 * Vh + (int64_t)c * Vh + s];
+                        if constexpr (kRecurrence<P>) {
+                            const v2 t = __builtin_nontemporal_load((const v2 *)pb + (int64_t)c * Vh + s);
+                            pv[q][c] = {t.x, t.y};
+                        }
+                        xv[q][c] = __builtin_nontemporal_load(&a.xlo[(size_t)j * 3 * Vh + (int64_t)c * Vh + s]);
                         ro[q][c] = ((const v2 *)a.r)[(size_t)j * 3 * Vh + (int64_t)c * Vh + s];
                     }
                 }
@@ -580,7 +587,8 @@ __global__ void __launch_bounds__(64 * W, kSharedMinWaves) k_cg_shared2(CgArgs a
                         pv[q][c].re = be[q] != 0.f ? fmaf(be[q], pv[q][c].re, ro[q][c].x) : ro[q][c].x;
                         pv[q][c].im = be[q] != 0.f ? fmaf(be[q], pv[q][c].im, ro[q][c].y) : ro[q][c].y;
                     }
-                    xl[o] = flt2{fmaf(al[q], pv[q][c].re, xv[q][c].x), fmaf(al[q], pv[q][c].im, xv[q][c].y)};
+                    __builtin_nontemporal_store(
+                        flt2{fmaf(al[q], pv[q][c].re, xv[q][c].x), fmaf(al[q], pv[q][c].im, xv[q][c].y)}, &xl[o]);
                     const real apr = m2r[q] * pv[q][c].re - acc[q][c].re;
                     const real api = m2r[q] * pv[q][c].im - acc[q][c].im;
                     v2 rn = ro[q][c];
@@ -588,11 +596,11 @@ __global__ void __launch_bounds__(64 * W, kSharedMinWaves) k_cg_shared2(CgArgs a
                     rn.y = fma(-al[q], api, rn.y);
                     rv[o] = rn;
                     nrm[q] += (double)rn.x * rn.x + (double)rn.y * rn.y;
-                    if constexpr (kRecurrence<P>)
+                    if constexpr (kRecurrence<P>) {
                         nrp[q] += (double)rn.x * pv[q][c].re + (double)rn.y * pv[q][c].im;
+                        __builtin_nontemporal_store(v2{pv[q][c].re, pv[q][c].im}, (v2 *)spin_at<P>(a.p[0], j, Vh) + o);
+                    }
                 }
-                if constexpr (kRecurrence<P>)
-                    P::store_spinor(spin_at<P>(a.p[0], j, Vh), Vh, s, pv[q]);
             }
         }
     }
