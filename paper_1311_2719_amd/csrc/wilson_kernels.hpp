@@ -207,22 +207,57 @@ __device__ __forceinline__ void wilson_hop(const Geom &g, const dbl2 *__restrict
     }
 }
 
-// Component k = 3 * spin + colour of the site is handled by lane k mod LPS.
-template <int LPS> __device__ __forceinline__ bool owns_component(int sub, int sp, int col)
+// Component k = 3 * spin + colour of a site is handled by lane k mod LPS: lane
+// sub has components sub, sub + LPS, ... (kOwn of them, the last one past the
+// 12th for some lanes if LPS = 8).
+template <int LPS> constexpr int kOwn = (12 + LPS - 1) / LPS;
+
+// o[j] = component j LPS + sub of acc, by selects
+template <int LPS>
+__device__ __forceinline__ void own_components(const cplx<double> (&acc)[4][3], int sub, cplx<double> (&o)[kOwn<LPS>])
 {
-    return ((sp * 3 + col) % LPS) == sub;
+#pragma unroll
+    for (int j = 0; j < kOwn<LPS>; ++j) {
+        o[j] = acc[j * LPS / 3][j * LPS % 3];
+#pragma unroll
+        for (int t = 1; t < LPS; ++t) {
+            const int k = j * LPS + t;
+            if (k < 12) {
+                const cplx<double> z = acc[k / 3][k % 3];
+                o[j] = {sub == t ? z.re : o[j].re, sub == t ? z.im : o[j].im};
+            }
+        }
+    }
 }
 
-// Component (spin, colour) of a 12-plane parity vector at site n.
+// fn(j, k) for each component k of this lane, without branches between them
+// (a branch per component made every load of an update wait for the one before)
+template <int LPS, class Fn> __device__ __forceinline__ void each_own(int sub, Fn fn)
+{
+#pragma unroll
+    for (int j = 0; j < kOwn<LPS>; ++j) {
+        const int k = j * LPS + sub;
+        if (12 % LPS == 0 || k < 12)
+            fn(j, k);
+    }
+}
+
+// Component k, or (spin, colour), of a 12-plane parity vector at site n.
+__device__ __forceinline__ cplx<double> comp(const dbl2 *v, int Vh, int n, int k)
+{
+    const dbl2 t = v[(int64_t)k * Vh + n];
+    return {t.x, t.y};
+}
+
 __device__ __forceinline__ cplx<double> comp(const dbl2 *v, int Vh, int n, int sp, int col)
 {
     const dbl2 t = v[(int64_t)(sp * 3 + col) * Vh + n];
     return {t.x, t.y};
 }
 
-__device__ __forceinline__ void put(dbl2 *v, int Vh, int n, int sp, int col, const cplx<double> &z)
+__device__ __forceinline__ void put(dbl2 *v, int Vh, int n, int k, const cplx<double> &z)
 {
-    v[(int64_t)(sp * 3 + col) * Vh + n] = dbl2{z.re, z.im};
+    v[(int64_t)k * Vh + n] = dbl2{z.re, z.im};
 }
 
 // Site and lane-within-site of this thread (LPS lanes per site, sub-major
@@ -254,13 +289,10 @@ k_wilson_dslash(Geom g, const dbl2 *__restrict__ links, const dbl2 *__restrict__
     const int64_t lp = link_parity_entries(ROWS, Vh);
     wilson_hop<ROWS, LPS, LP>(g, links + lp * p, links + lp * (1 - p), p, s, sub, acc,
                           [&](int n, int sp, int col) { return comp(src, Vh, n, sp, col); });
+    cplx<double> h[kOwn<LPS>];
+    own_components<LPS>(acc, sub, h);
     dbl2 *o = out + (size_t)p * 12 * Vh;
-#pragma unroll
-    for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-            if (owns_component<LPS>(sub, sp, a))
-                put(o, Vh, s, sp, a, acc[sp][a]);
+    each_own<LPS>(sub, [&](int j, int k) { put(o, Vh, s, k, h[j]); });
 }
 
 // ---- even-odd CG ------------------------------------------------------------------
@@ -382,14 +414,12 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
     cplx<double> acc[4][3];
     wilson_hop<ROWS, LPS, LP>(a.g, a.links[0], a.links[1], 0, s, sub, acc,
                           [&](int n, int sp, int col) { return comp(bo, Vh, n, sp, col); });
-#pragma unroll
-    for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-            if (owns_component<LPS>(sub, sp, c)) {
-                const cplx<double> be = comp(a.b, Vh, s, sp, c);
-                put(a.bh, Vh, s, sp, c, {be.re + a.kappa * acc[sp][c].re, be.im + a.kappa * acc[sp][c].im});
-            }
+    cplx<double> h[kOwn<LPS>];
+    own_components<LPS>(acc, sub, h);
+    each_own<LPS>(sub, [&](int j, int k) {
+        const cplx<double> be = comp(a.b, Vh, s, k);
+        put(a.bh, Vh, s, k, {be.re + a.kappa * h[j].re, be.im + a.kappa * h[j].im});
+    });
 }
 
 // odd outputs: t = H_oe (gamma_5 src).  With a state (K3 of a step) it runs
@@ -408,12 +438,9 @@ __global__ void __launch_bounds__(128) k_wil_odd_g5(WArgs a, const dbl2 *__restr
         const cplx<double> z = comp(src, Vh, n, sp, col);
         return sp < 2 ? z : cplx<double>{-z.re, -z.im};
     });
-#pragma unroll
-    for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-            if (owns_component<LPS>(sub, sp, c))
-                put(a.t, Vh, s, sp, c, acc[sp][c]);
+    cplx<double> h[kOwn<LPS>];
+    own_components<LPS>(acc, sub, h);
+    each_own<LPS>(sub, [&](int j, int k) { put(a.t, Vh, s, k, h[j]); });
 }
 
 // init 3 (even outputs): r = bh - kappa^2 gamma_5 (H t)_e = Mhat^dagger bh;
@@ -428,20 +455,17 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
         cplx<double> acc[4][3];
         wilson_hop<ROWS, LPS, LP>(a.g, a.links[0], a.links[1], 0, s, sub, acc,
                               [&](int n, int sp, int col) { return comp(a.t, Vh, n, sp, col); });
+        cplx<double> h[kOwn<LPS>];
+        own_components<LPS>(acc, sub, h);
         const double k2 = a.kappa * a.kappa;
-#pragma unroll
-        for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                if (!owns_component<LPS>(sub, sp, c))
-                    continue;
-                const double g5 = sp < 2 ? k2 : -k2;
-                const cplx<double> bh = comp(a.bh, Vh, s, sp, c);
-                const cplx<double> r = {bh.re - g5 * acc[sp][c].re, bh.im - g5 * acc[sp][c].im};
-                put(a.r, Vh, s, sp, c, r);
-                put(a.x, Vh, s, sp, c, czero<double>());
-                nrm += r.re * r.re + r.im * r.im;
-            }
+        each_own<LPS>(sub, [&](int j, int k) {
+            const double g5 = k < 6 ? k2 : -k2;
+            const cplx<double> bh = comp(a.bh, Vh, s, k);
+            const cplx<double> r = {bh.re - g5 * h[j].re, bh.im - g5 * h[j].im};
+            put(a.r, Vh, s, k, r);
+            put(a.x, Vh, s, k, czero<double>());
+            nrm += r.re * r.re + r.im * r.im;
+        });
     }
     wpartial(a, 0, 1, nrm, lds);
 }
@@ -454,7 +478,10 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
 //   K4  alpha, then p' = r + beta p, x += alpha p', r -= alpha Mhat^dagger ap'
 //       (= ap' - kappa^2 gamma_5 H_eo t) and <r,r>.
 // The direct form gathered r and p at every neighbour in K1 (3 KB a site
-// instead of 1.5), and its prologue ran before K1's hop.
+// instead of 1.5), and its prologue ran before K1's hop.  K2 and K4 sum the
+// partials after their hop: at 16^4 a block needs 10 us for a hop from the
+// Infinity Cache and L2, and with the totals before it and a branch per
+// component of the update K2 took 19.2 us and K4 20.9, now 12.2 and 14.5.
 
 // K1 (odd outputs): t = H_oe r while the system iterates (or has not begun)
 template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_wil_step1(WArgs a, int ver)
@@ -469,12 +496,9 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
     cplx<double> acc[4][3];
     wilson_hop<ROWS, LPS, LP>(a.g, a.links[1], a.links[0], 1, s, sub, acc,
                               [&](int n, int sp, int col) { return comp(a.r, Vh, n, sp, col); });
-#pragma unroll
-    for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-            if (owns_component<LPS>(sub, sp, c))
-                put(a.t, Vh, s, sp, c, acc[sp][c]);
+    cplx<double> h[kOwn<LPS>];
+    own_components<LPS>(acc, sub, h);
+    each_own<LPS>(sub, [&](int j, int k) { put(a.t, Vh, s, k, h[j]); });
 }
 
 // K2 (even outputs): advance the state over the previous step, then
@@ -492,6 +516,23 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
     }
     if (threadIdx.x < sizeof(WState) / 16)
         ((uint4 *)&sst)[threadIdx.x] = ((const uint4 *)a.st[ver])[threadIdx.x];
+    // the hop and the site's own vectors need no scalar: they come before the
+    // totals, so that the waits for the two overlap
+    int s, sub;
+    const bool site = wsite<LPS>(Vh, a.remap, s, sub);
+    cplx<double> h[kOwn<LPS>], o[kOwn<LPS>];
+    if (site) {
+        cplx<double> acc[4][3];
+        wilson_hop<ROWS, LPS, LP>(a.g, a.links[0], a.links[1], 0, s, sub, acc,
+                                  [&](int n, int sp, int col) { return comp(a.t, Vh, n, sp, col); });
+        own_components<LPS>(acc, sub, h);
+        const double k2 = a.kappa * a.kappa;
+        each_own<LPS>(sub, [&](int j, int k) {
+            const cplx<double> r = comp(a.r, Vh, s, k);
+            o[j] = comp(a.ap, Vh, s, k);
+            h[j] = {r.re - k2 * h[j].re, r.im - k2 * h[j].im};
+        });
+    }
     double tot[2];
     wtotals<2>(a, ver, nblk, lds, tot);  // its barriers also publish sst
     if (threadIdx.x == 0) {
@@ -543,28 +584,14 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
     if (wuniform(sst.mode) != W_CG)
         return;
     const double beta = wuniform(sst.beta);
-    int s, sub;
     double nrm = 0.0;
-    if (wsite<LPS>(Vh, a.remap, s, sub)) {
-        cplx<double> acc[4][3];
-        wilson_hop<ROWS, LPS, LP>(a.g, a.links[0], a.links[1], 0, s, sub, acc,
-                                  [&](int n, int sp, int col) { return comp(a.t, Vh, n, sp, col); });
-        const double k2 = a.kappa * a.kappa;
-#pragma unroll
-        for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                if (!owns_component<LPS>(sub, sp, c))
-                    continue;
-                const cplx<double> r = comp(a.r, Vh, s, sp, c);
-                cplx<double> v = {r.re - k2 * acc[sp][c].re, r.im - k2 * acc[sp][c].im};
-                if (beta != 0.0) {  // beta = 0 starts from ap = 0, whatever the buffer holds
-                    const cplx<double> o = comp(a.ap, Vh, s, sp, c);
-                    v = {fma(beta, o.re, v.re), fma(beta, o.im, v.im)};
-                }
-                put(a.ap, Vh, s, sp, c, v);
-                nrm += v.re * v.re + v.im * v.im;
-            }
+    if (site) {
+        each_own<LPS>(sub, [&](int j, int k) {
+            if (beta != 0.0)  // beta = 0 starts from ap = 0, whatever the buffer holds
+                h[j] = {fma(beta, o[j].re, h[j].re), fma(beta, o[j].im, h[j].im)};
+            put(a.ap, Vh, s, k, h[j]);
+            nrm += h[j].re * h[j].re + h[j].im * h[j].im;
+        });
     }
     wpartial(a, ver ^ 1, 0, nrm, lds);
 }
@@ -580,39 +607,39 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
         return;
     const int cur = ver ^ 1;
     const double rr = wuniform(st->rr), beta = wuniform(st->beta);
+    const int Vh = a.g.Vh;
+    int s, sub;
+    const bool site = wsite<LPS>(Vh, a.remap, s, sub);
+    cplx<double> h[kOwn<LPS>], r[kOwn<LPS>], p[kOwn<LPS>], x[kOwn<LPS>];
+    if (site) {  // before the totals, as in K2
+        cplx<double> acc[4][3];
+        wilson_hop<ROWS, LPS, LP>(a.g, a.links[0], a.links[1], 0, s, sub, acc,
+                                  [&](int n, int sp, int col) { return comp(a.t, Vh, n, sp, col); });
+        own_components<LPS>(acc, sub, h);
+        const double k2 = a.kappa * a.kappa;
+        each_own<LPS>(sub, [&](int j, int k) {
+            const double g5 = k < 6 ? k2 : -k2;
+            const cplx<double> ap = comp(a.ap, Vh, s, k), o = comp(a.p, Vh, s, k);
+            r[j] = comp(a.r, Vh, s, k);
+            x[j] = comp(a.x, Vh, s, k);
+            h[j] = {ap.re - g5 * h[j].re, ap.im - g5 * h[j].im};
+            p[j] = r[j];
+            if (beta != 0.0)  // beta = 0 starts from p = 0
+                p[j] = {fma(beta, o.re, r[j].re), fma(beta, o.im, r[j].im)};
+        });
+    }
     double tot[1];
     wtotals<1>(a, cur, gridDim.x, lds, tot);
     const double alpha = wfinite_pos(tot[0]) ? rr / tot[0] : 0.0;
-    const int Vh = a.g.Vh;
-    int s, sub;
     double nrm = 0.0;
-    if (wsite<LPS>(Vh, a.remap, s, sub)) {
-        cplx<double> acc[4][3];
-        wilson_hop<ROWS, LPS, LP>(a.g, a.links[0], a.links[1], 0, s, sub, acc,
-                              [&](int n, int sp, int col) { return comp(a.t, Vh, n, sp, col); });
-        const double k2 = a.kappa * a.kappa;
-#pragma unroll
-        for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                if (!owns_component<LPS>(sub, sp, c))
-                    continue;
-                const double g5 = sp < 2 ? k2 : -k2;
-                const cplx<double> ap = comp(a.ap, Vh, s, sp, c);
-                const cplx<double> atap = {ap.re - g5 * acc[sp][c].re, ap.im - g5 * acc[sp][c].im};
-                cplx<double> r = comp(a.r, Vh, s, sp, c);
-                cplx<double> p = r;
-                if (beta != 0.0) {
-                    const cplx<double> o = comp(a.p, Vh, s, sp, c);
-                    p = {fma(beta, o.re, r.re), fma(beta, o.im, r.im)};
-                }
-                put(a.p, Vh, s, sp, c, p);
-                const cplx<double> x = comp(a.x, Vh, s, sp, c);
-                put(a.x, Vh, s, sp, c, {fma(alpha, p.re, x.re), fma(alpha, p.im, x.im)});
-                r = {fma(-alpha, atap.re, r.re), fma(-alpha, atap.im, r.im)};
-                put(a.r, Vh, s, sp, c, r);
-                nrm += r.re * r.re + r.im * r.im;
-            }
+    if (site) {
+        each_own<LPS>(sub, [&](int j, int k) {
+            put(a.p, Vh, s, k, p[j]);
+            put(a.x, Vh, s, k, {fma(alpha, p[j].re, x[j].re), fma(alpha, p[j].im, x[j].im)});
+            const cplx<double> rn = {fma(-alpha, h[j].re, r[j].re), fma(-alpha, h[j].im, r[j].im)};
+            put(a.r, Vh, s, k, rn);
+            nrm += rn.re * rn.re + rn.im * rn.im;
+        });
     }
     wpartial(a, cur, 1, nrm, lds);
 }
@@ -629,14 +656,12 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
                           [&](int n, int sp, int col) { return comp(a.x, Vh, n, sp, col); });
     const dbl2 *bo = a.b + (size_t)12 * Vh;
     dbl2 *xo = a.x + (size_t)12 * Vh;
-#pragma unroll
-    for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-            if (owns_component<LPS>(sub, sp, c)) {
-                const cplx<double> b = comp(bo, Vh, s, sp, c);
-                put(xo, Vh, s, sp, c, {b.re + a.kappa * acc[sp][c].re, b.im + a.kappa * acc[sp][c].im});
-            }
+    cplx<double> h[kOwn<LPS>];
+    own_components<LPS>(acc, sub, h);
+    each_own<LPS>(sub, [&](int j, int k) {
+        const cplx<double> b = comp(bo, Vh, s, k);
+        put(xo, Vh, s, k, {b.re + a.kappa * h[j].re, b.im + a.kappa * h[j].im});
+    });
 }
 
 // |b - M x|^2 on the sites of parity `par`, per block into slot `par` of
@@ -654,17 +679,14 @@ template <int ROWS, int LPS, class LP> __global__ void __launch_bounds__(128) k_
                               [&](int n, int sp, int col) { return comp(xin, Vh, n, sp, col); });
         const dbl2 *bp = a.b + (size_t)par * 12 * Vh;
         const dbl2 *xp = a.x + (size_t)par * 12 * Vh;
-#pragma unroll
-        for (int sp = 0; sp < 4; ++sp)
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                if (!owns_component<LPS>(sub, sp, c))
-                    continue;
-                const cplx<double> b = comp(bp, Vh, s, sp, c), x = comp(xp, Vh, s, sp, c);
-                const double re = b.re - x.re + a.kappa * acc[sp][c].re;
-                const double im = b.im - x.im + a.kappa * acc[sp][c].im;
-                nrm += re * re + im * im;
-            }
+        cplx<double> h[kOwn<LPS>];
+        own_components<LPS>(acc, sub, h);
+        each_own<LPS>(sub, [&](int j, int k) {
+            const cplx<double> b = comp(bp, Vh, s, k), x = comp(xp, Vh, s, k);
+            const double re = b.re - x.re + a.kappa * h[j].re;
+            const double im = b.im - x.im + a.kappa * h[j].im;
+            nrm += re * re + im * im;
+        });
     }
     wpartial(a, 0, par, nrm, lds);
 }
