@@ -111,11 +111,21 @@ struct Lex {
     }
 };
 
-// force (+)= coeff * (-beta/6) TA[U_mu(x) Sigma_mu(x)]; one thread per link
-__global__ void __launch_bounds__(256)
+// force (+)= coeff * (-beta/6) TA[U_mu(x) Sigma_mu(x)]; one thread per link.
+// 19 matrices are read per link, most of them by the sites around as well: each
+// XCD takes one contiguous range of sites, so that it finds them in its L2, and
+// blocks of one wavefront reach every CU on small lattices.  With blocks of 256
+// dealt to the XCDs in turn: 8^4 20.4 -> 18.1 us, 12^3 16 45 -> 38, 16^4 85 -> 80,
+// 24^4 481 -> 465 (these with the fermion force, 17 of the 80).  What remains is
+// the address unit, 64 lines a load, and latency at three waves a SIMD: loads by
+// quads of lanes that transpose in registers (a third of the lines) took as long,
+// a transposition through LDS longer.
+constexpr int kGaugeForceBlock = 64;
+
+__global__ void __launch_bounds__(kGaugeForceBlock)
 k_gauge_force(Lex g, int64_t V, const dbl2 *__restrict__ U, dbl2 *__restrict__ force, double scale, int accumulate)
 {
-    const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t gid = (int64_t)logical_block(blockIdx.x, gridDim.x, 1) * blockDim.x + threadIdx.x;
     if (gid >= V * 4)
         return;
     const int x = (int)(gid >> 2);
@@ -323,8 +333,8 @@ int gauge_force(const int32_t dims[4], const double *U, double *force, double be
     Lex g;
     memcpy(g.L, dims, sizeof(g.L));
     const int64_t V = (int64_t)dims[0] * dims[1] * dims[2] * dims[3];
-    const dim3 grid((unsigned)((V * 4 + 255) / 256));
-    hipLaunchKernelGGL(k_gauge_force, grid, dim3(256), 0, s, g, V, (const dbl2 *)U, (dbl2 *)force,
+    const dim3 grid((unsigned)((V * 4 + kGaugeForceBlock - 1) / kGaugeForceBlock));
+    hipLaunchKernelGGL(k_gauge_force, grid, dim3(kGaugeForceBlock), 0, s, g, V, (const dbl2 *)U, (dbl2 *)force,
                        -coeff * beta / 6.0, accumulate);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess)
