@@ -18,9 +18,10 @@ The same line reports:
   roofline      the FP64 D_slash kernel on the same 32^4 field (working set
                 0.9 GB, far beyond the 256 MB Infinity Cache): 100
                 full-lattice applications per run, HIP events on the library's
-                stream; achieved = algorithmic bytes per output site (8 links
-                + 1 gathered input vector + 1 output vector: 864 B with two
-                stored link rows, 1248 B with three) x V / mean duration;
+                stream; achieved = algorithmic bytes per site (its 4 stored links,
+                each read once for both its ends, + 1 gathered input vector
+                + 1 output vector: 480 B with two stored link rows, 672 B
+                with three) x V / mean duration;
   cg_iteration  the solve's bytes per CG iteration over its time per iteration;
   c2_16         the 16^4 workload (eps 0.3, m 0.05): FP64 solves/s and the
                 D_slash, cache-resident and cold (8 fields cycled);
@@ -55,18 +56,20 @@ METRIC = "CG solves/s to 1e-10 (mixed vs FP64) + D_slash HBM GB/s % of peak; p99
 HBM_PEAK_GBS = 8000.0
 
 
-def dslash_bytes_per_site(rows: int) -> int:
-    """FP64 D_slash algorithmic bytes per output site: 8 links of 3 x rows
-    complex entries, one gathered input vector and one output vector."""
-    return 8 * 3 * rows * 16 + 48 + 48
+def dslash_bytes_per_site(rows: int, one_parity: bool = False) -> int:
+    """FP64 D_slash algorithmic bytes per output site: links of 3 x rows
+    complex entries (a site's 4 forward ones, which the outputs of both
+    parities share; with outputs of one parity each serves one output, 8 a
+    site), one gathered input vector and one output vector."""
+    return (8 if one_parity else 4) * 3 * rows * 16 + 48 + 48
 
 
 def cg_bytes_per_half_site(rows: int) -> int:
-    """FP64 CG iteration, algorithmic bytes per site of one parity system:
-    K1 (links, r and p gathered, ap and p' stored) + K2 (links, ap gathered,
-    p' read, x and r read and written)."""
-    links = 8 * 3 * rows * 16
-    return (links + 96 + 48 + 48) + (links + 48 + 48 + 96 + 96)
+    """FP64 CG iteration of both parity systems, algorithmic bytes per site of
+    one system: K1 (links, r gathered, u read and written) + K2 (links, u
+    gathered; p, x and r read and written)."""
+    links = 4 * 3 * rows * 16
+    return (links + 48 + 96) + (links + 48 + 96 + 96 + 96)
 
 
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "dslash_f64_32x32x32x32_traffic.txt")
@@ -371,7 +374,7 @@ def run_default(args):
     d, smean = dslash_timing(ctx, f3, b3, 50, out_parity=binding.ODD, offset=0, count=n_share)
     shard = {"lattice": list(c3_dims), "out_parity": "odd", "sites": n_share, "mean_us": smean * 1e6,
              "p99_us": float(np.percentile(d, 99) * 1e6),
-             "gbs": dslash_bytes_per_site(rows3) * n_share / smean / 1e9}
+             "gbs": dslash_bytes_per_site(rows3, one_parity=True) * n_share / smean / 1e9}
 
     cpu = None
     if not args.no_cpu:
@@ -491,7 +494,8 @@ def run_default(args):
                    "lattice": list(c3_dims), "mass": c3_m, "tol": tol, "precision": "fp64", "parity": "all"},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": read_traffic(V3),
-                     "kernel": "k_dslash<PrecF64NT> (full lattice, FP64 with non-temporal link loads, 32^4 on the same field)",
+                     "kernel": "k_dslash<PrecF64NT> (full lattice, FP64, non-temporal loads of the backward neighbours' links, 32^4 "
+                               "on the same field)",
                      "algorithmic_bytes_per_launch": algo_bytes, "bytes_per_site": dslash_bytes_per_site(rows3),
                      "link_rows": rows3, "mean_us": mean * 1e6, "p50_us": float(np.percentile(durs, 50) * 1e6),
                      "p99_us": float(np.percentile(durs, 99) * 1e6), "config": tune,
@@ -821,9 +825,10 @@ def run_serve(args):
 
 
 def wilson_bytes_per_site(rows: int) -> int:
-    """Wilson hop algorithmic bytes per output site (FP64): 8 links of
-    3 x rows complex entries, one gathered and one written spin-colour vector."""
-    return 8 * 3 * rows * 16 + 192 + 192
+    """Wilson hop of both parities, algorithmic bytes per site (FP64): its 4
+    links of 3 x rows complex entries, one gathered and one written spin-colour
+    vector."""
+    return 4 * 3 * rows * 16 + 192 + 192
 
 
 def run_wilson(args):

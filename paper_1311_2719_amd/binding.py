@@ -13,6 +13,7 @@ even-odd layout, shape (2, 3, V/2): [parity][colour][checkerboard site].
 from __future__ import annotations
 
 import ctypes
+import math
 import os
 import threading
 from dataclasses import dataclass
@@ -204,7 +205,7 @@ class Field:
 
     @property
     def volume(self):
-        return int(np.prod(self.dims))
+        return int(math.prod(self.dims))
 
 
 class Context:

@@ -161,8 +161,11 @@ int dslash_with(const KernelCfg &cfg, GaugeField *f, int prec, int out_parity, i
     hipError_t e;
     switch (prec) {
     case 0:
-        e = f->nt_links ? launch_dslash_p<PrecF64NT>(cfg, f, par_fixed, nparity, off, cnt, in, out, accumulate, s)
-                        : launch_dslash_p<PrecF64>(cfg, f, par_fixed, nparity, off, cnt, in, out, accumulate, s);
+        e = f->nt_once && nparity == 1
+                ? launch_dslash_p<PrecF64NTOnce>(cfg, f, par_fixed, nparity, off, cnt, in, out, accumulate, s)
+            : f->nt_links
+                ? launch_dslash_p<PrecF64NT>(cfg, f, par_fixed, nparity, off, cnt, in, out, accumulate, s)
+                : launch_dslash_p<PrecF64>(cfg, f, par_fixed, nparity, off, cnt, in, out, accumulate, s);
         break;
     case 1: e = launch_dslash_p<PrecF32>(cfg, f, par_fixed, nparity, off, cnt, in, out, accumulate, s); break;
     case 2: e = launch_dslash_p<PrecF16>(cfg, f, par_fixed, nparity, off, cnt, in, out, accumulate, s); break;

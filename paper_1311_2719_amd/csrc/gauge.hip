@@ -121,13 +121,19 @@ k_pack(Geom g, dbl2 *__restrict__ lex, dbl2 *__restrict__ eo, int to_eo)
 
 }  // namespace
 
-int nt_links_for(const GaugeField &f)
+void choose_link_loads(GaugeField &f)
 {
     if (const char *e = getenv("STAG_NT_LINKS"))
-        if (e[0] == '0' || e[0] == '1')
-            return e[0] == '1';
+        if (e[0] == '0' || e[0] == '1') {
+            f.nt_links = f.nt_once = e[0] == '1';
+            return;
+        }
     const size_t fp64_link_bytes = (size_t)2 * link_parity_entries(f.rows, f.g.Vh) * link_entry_bytes_of(0);
-    return fp64_link_bytes > ((size_t)256 << 20);
+    f.nt_links = fp64_link_bytes > ((size_t)256 << 20);
+    // between 128 and 256 MiB: a hop of one parity on one field after another
+    // 53.4 us with plain loads, 49.7 without keeping the lines (28^4; the one
+    // field repeated 42 and 49); both parities and the solves keep plain ones
+    f.nt_once = fp64_link_bytes > ((size_t)128 << 20);
 }
 
 int gauge_check(Ctx *ctx, const Geom &g, const double *links_dev, hipStream_t s, bool &two_rows)

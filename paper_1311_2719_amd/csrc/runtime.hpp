@@ -79,6 +79,7 @@ struct GaugeField {
     Geom g{};
     int32_t rows = 3;                                // link rows stored (2: third row rebuilt)
     int32_t nt_links = 0;                            // 1: FP64 kernels read the backward neighbours' links non-temporally
+    int32_t nt_once = 0;                             // 1: a hop of one parity alone reads all links non-temporally
     void *links[3] = {nullptr, nullptr, nullptr};  // per precision id, layout in stag_types.hpp
     int32_t *nbr = nullptr;                          // [2][8][Vh]
     // Kept with the field for the workspace of stag_cg_solve (as many bytes as
@@ -150,9 +151,9 @@ constexpr double kTwoRowTolerance = 1e-14;
 // Check the lexicographic links on the device: ENONFINITE for NaN/Inf;
 // two_rows = whether every folded link admits the two-row form.
 int gauge_check(Ctx *ctx, const Geom &g, const double *links_dev, hipStream_t s, bool &two_rows);
-// Whether the FP64 kernels of field f read links of backward neighbours
-// non-temporally: when its FP64 links do not fit the Infinity Cache (STAG_NT_LINKS=0/1 forces it).
-int nt_links_for(const GaugeField &f);
+// Sets nt_links and nt_once of field f: non-temporal loads where its FP64 links
+// do not fit the Infinity Cache beside the vectors (STAG_NT_LINKS=0/1 forces both).
+void choose_link_loads(GaugeField &f);
 // Fill f->links (f->rows rows, every precision) and f->nbr from the links.
 int gauge_prepare(GaugeField *f, const double *links_dev, hipStream_t s);
 

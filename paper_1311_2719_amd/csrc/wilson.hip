@@ -7,6 +7,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "runtime.hpp"
@@ -147,7 +148,7 @@ int wilson_prepare(Ctx *ctx, GaugeField *f, const double *links_dev, hipStream_t
     if (!f->links[0])
         return set_error(STAG_ENOMEM, "arena exhausted (%zu bytes of Wilson links)", lb);
     f->bytes = lb;
-    f->nt_links = nt_links_for(*f);
+    choose_link_loads(*f);
     if (f->rows == 2)
         hipLaunchKernelGGL((k_wprepare_links<2>), grid, block, 0, s, g, links_dev, (dbl2 *)f->links[0]);
     else
@@ -175,16 +176,25 @@ int launch_pack_spinor(const Geom &g, const double *lex, double *eo, int to_eo, 
 namespace {
 
 // The launches of the hop and of one solve, for one link format and one
-// number of lanes per site.
-template <int ROWS, int LPS, class LP> struct WLaunch {
+// number of lanes per site: LPA reads the links of the hop of both parities, LP
+// those of the solve's kernels, which use every link once.
+template <int ROWS, int LPS, class LPA> struct WLaunch {
+    using LP = std::conditional_t<std::is_same_v<LPA, PrecF64NT>, PrecF64NTOnce, LPA>;
     static dim3 grid(int Vh, int tiles = 1)
     {
         return dim3((unsigned)(((int64_t)Vh * LPS + kWBlock - 1) / kWBlock) * (unsigned)tiles);
     }
     static void hop(const GaugeField *f, int pf, const double *in, double *out, int remap, hipStream_t s)
     {
-        hipLaunchKernelGGL((wil::k_wilson_dslash<ROWS, LPS, LP>), grid(f->g.Vh, pf < 0 ? 2 : 1), dim3(kWBlock), 0, s, f->g,
-                           (const dbl2 *)f->links[0], (const dbl2 *)in, (dbl2 *)out, pf, remap);
+        if (pf < 0)
+            hipLaunchKernelGGL((wil::k_wilson_dslash<ROWS, LPS, LPA>), grid(f->g.Vh, 2), dim3(kWBlock), 0, s, f->g,
+                               (const dbl2 *)f->links[0], (const dbl2 *)in, (dbl2 *)out, pf, remap);
+        else if (f->nt_once)
+            hipLaunchKernelGGL((wil::k_wilson_dslash<ROWS, LPS, PrecF64NTOnce>), grid(f->g.Vh), dim3(kWBlock), 0, s, f->g,
+                               (const dbl2 *)f->links[0], (const dbl2 *)in, (dbl2 *)out, pf, remap);
+        else
+            hipLaunchKernelGGL((wil::k_wilson_dslash<ROWS, LPS, PrecF64>), grid(f->g.Vh), dim3(kWBlock), 0, s, f->g,
+                               (const dbl2 *)f->links[0], (const dbl2 *)in, (dbl2 *)out, pf, remap);
     }
     static void init(const wil::WArgs &a, hipStream_t s)
     {

@@ -68,3 +68,28 @@ def test_cg_block_orders_and_scalars_kernel(gpu_ctx, monkeypatch, dims, order, p
         finally:
             gpu_ctx.free_gauge(f)
     assert np.linalg.norm(got["1"] - got["0"]) <= 2 * BOUND * np.linalg.norm(got["0"])
+
+
+@pytest.mark.parametrize("dims", [(4, 4, 4, 6), (8, 8, 8, 8)])
+@pytest.mark.parametrize("rows", ["2", "3"])
+@pytest.mark.parametrize("parity", [binding.EVEN, binding.ODD])
+def test_one_parity_with_nontemporal_links_gives_the_same_bits(gpu_ctx, monkeypatch, dims, rows, parity):
+    monkeypatch.setenv("STAG_LINK_ROWS", rows)
+    monkeypatch.setenv("STAG_WILSON_LPS", "4")  # a timed choice of lanes would change the order of a sum
+    U = inputs.haar_su3(dims, 531)
+    chi, psi = inputs.gaussian_source(dims, 532), inputs.gaussian_spinor(dims, 533)
+    got = {}
+    for nt in "01":
+        monkeypatch.setenv("STAG_NT_LINKS", nt)
+        f, w = gpu_ctx.set_gauge(dims, U), gpu_ctx.set_gauge_wilson(dims, U)
+        try:
+            b, out = gpu_ctx.pack(f, chi), gpu_ctx.new_fermion(f)
+            gpu_ctx.dslash(f, b, out, out_parity=parity)
+            s, hop = gpu_ctx.pack_spinor(w, psi), gpu_ctx.new_spinor(w)
+            gpu_ctx.wilson_dslash(w, s, hop, out_parity=parity)
+            got[nt] = gpu_ctx.unpack(f, out).cpu(), gpu_ctx.unpack_spinor(w, hop).cpu()
+        finally:
+            gpu_ctx.free_gauge(f)
+            gpu_ctx.free_gauge(w)
+    assert float(got["0"][0].abs().max()) > 0 and float(got["0"][1].abs().max()) > 0
+    assert torch.equal(got["0"][0], got["1"][0]) and torch.equal(got["0"][1], got["1"][1])
