@@ -503,6 +503,25 @@ static KernelCfg shared_shape(int code, int reduce)
     return c;
 }
 
+// The shape "lps,block,rtile,tables,remap[,shared]" at `text`; false if this
+// batch cannot run it.
+bool Batch::parse_shape(const char *text, const CgLaunchTable &t, KernelCfg &c) const
+{
+    const int n = sscanf(text, "%d,%d,%d,%d,%d,%d", &c.lps, &c.block, &c.rtile, &c.tables, &c.remap, &c.shared);
+    if (n < 5 || c.rtile <= 0 || S_ % c.rtile)
+        return false;
+    if (n == 6 && c.shared) {
+        bool have = false;
+        const int W = c.block / 64;
+        for (int i = 0; i < t.n_stiles; ++i)
+            have |= c.block % 64 == 0 && W > 0 && c.rtile % W == 0 && t.stiles[i] == shared_code(W, c.rtile / W);
+        return have && c.lps == 1;
+    }
+    c.shared = 0;
+    return (c.lps == 1 || c.lps == 2 || c.lps == 4 || c.lps == 8) && c.block >= 64 && c.block <= 256 &&
+           c.block % 64 == 0;
+}
+
 KernelCfg Batch::tune_cg()
 {
     KernelCfg best = default_cg_cfg();
@@ -510,23 +529,15 @@ KernelCfg Batch::tune_cg()
     const char *env = getenv("STAG_KERNEL_CFG");
     if (env && *env) {
         KernelCfg c;
-        const int n = sscanf(env, "%d,%d,%d,%d,%d,%d", &c.lps, &c.block, &c.rtile, &c.tables, &c.remap, &c.shared);
-        if (n < 5 || c.rtile <= 0 || S_ % c.rtile)
+        if (!parse_shape(env, t, c))
             return best;
-        if (n == 6 && c.shared) {
-            bool have = false;
-            const int W = c.block / 64;
-            for (int i = 0; i < t.n_stiles; ++i)
-                have |= c.block % 64 == 0 && W > 0 && c.rtile % W == 0 && t.stiles[i] == shared_code(W, c.rtile / W);
-            if (have && c.lps == 1)
-                return c;
-            return best;
-        }
-        c.shared = 0;
-        if ((c.lps == 1 || c.lps == 2 || c.lps == 4 || c.lps == 8) && c.block >= 64 && c.block <= 256 &&
-            c.block % 64 == 0)
-            return c;
-        return best;
+        // further shapes: the smaller tiles, by size
+        small_.clear();
+        KernelCfg sb;
+        for (const char *q = strchr(env, ';'); q; q = strchr(q + 1, ';'))
+            if (parse_shape(q + 1, t, sb) && sb.rtile < c.rtile && (small_.empty() || sb.rtile > small_.back().rtile))
+                small_.push_back(sb);
+        return c;
     }
     const char *tenv = getenv("STAG_TUNE");
     if (tenv && tenv[0] == '0')

@@ -96,6 +96,7 @@ private:
     hipError_t launch_scalars(hipStream_t st, const CgArgs &a, int ver, int kind, int nblk) const;
     // Tune the tile shape on this workspace; also fills small_.
     KernelCfg tune_cg();
+    bool parse_shape(const char *text, const CgLaunchTable &t, KernelCfg &c) const;
     KernelCfg default_cg_cfg() const;
     double time_cg_config(const KernelCfg &c, int nblk, bool reduce);
     CgArgs args() const;

@@ -53,7 +53,10 @@ __device__ __forceinline__ int chunk_link_index(int k, int d, int i) { return (k
 // sites are consecutive but for the x direction's and the boundaries' steps).
 // Two parts, so that the step's prologue runs while the first loads are in
 // flight: load() starts the loads of a wavefront's first kPre hops, store()
-// writes them to LDS and does the rest.
+// writes them to LDS and does the rest.  A smaller tile runs at the tuned
+// shape's block count, which may exceed the chunks: a block without a chunk
+// (chunk_start() = -1) loads the first sites' links, never stores them, and
+// writes partial sums of zero.
 template <class P, int ROWS, int W> struct ChunkLinks {
     static constexpr int kPre = (8 + W - 1) / W <= 2 ? (8 + W - 1) / W : 1;
     SiteCoord c;
@@ -72,7 +75,7 @@ template <class P, int ROWS, int W> struct ChunkLinks {
     __device__ __forceinline__ void load(const Geom &g, const typename P::link_t *lout, const typename P::link_t *lin,
                                          int p_out, int s0)
     {
-        s = s0 + (threadIdx.x & 63);
+        s = (s0 < 0 ? 0 : s0) + (threadIdx.x & 63);
         s = s < g.Vh ? s : g.Vh - 1;  // past the end: staged, never used
         c = decode_site(g, p_out, s);
 #pragma unroll
@@ -210,7 +213,7 @@ __global__ void __launch_bounds__(64 * W, kSharedMinWaves) k_cg_shared1(CgArgs a
         return;
     const auto *lout = (const typename P::link_t *)a.links[pout], *lin = (const typename P::link_t *)a.links[1 - pout];
     ChunkLinks<P, ROWS, W> cl;
-    cl.load(a.g, lout, lin, pout, chunk_start(0, Vh, tl));  // every block has a first chunk
+    cl.load(a.g, lout, lin, pout, chunk_start(0, Vh, tl));
     // prologue: this wavefront advances its own systems over the previous step
     int js[RR];
     bool cg[RR], ru[RR];
@@ -446,7 +449,7 @@ __global__ void __launch_bounds__(64 * W, kSharedMinWaves) k_cg_shared2(CgArgs a
         return;
     const auto *lout = (const typename P::link_t *)a.links[par], *lin = (const typename P::link_t *)a.links[1 - par];
     ChunkLinks<P, ROWS, W> cl;
-    cl.load(a.g, lout, lin, par, chunk_start(0, Vh, tl));  // every block has a first chunk
+    cl.load(a.g, lout, lin, par, chunk_start(0, Vh, tl));
     // alpha from K1's partial sums (slot 0; FP16: slots 0 and 1)
     constexpr int NS = kRecurrence<P> ? 1 : 2;
     int js[RR], pn_buf[RR];
