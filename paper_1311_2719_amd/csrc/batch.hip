@@ -106,11 +106,18 @@ bool cg_uses_reduction(const Geom &g, const KernelCfg &c)
 
 bool Batch::uses_reduction(const KernelCfg &c) const { return cg_uses_reduction(f_->g, c); }
 
+// Keys of GaugeField::tuned for the step kernels of (precision, slots): the
+// timed shape, and the default shape noted for a workspace whose solves run in
+// one launch.  Only the timed one is taken over by other workspaces.
+static uint64_t timed_key(int prec, int slots) { return ((uint64_t)1 << 40) | ((uint64_t)prec << 32) | (uint32_t)slots; }
+static uint64_t untimed_key(int prec, int slots) { return ((uint64_t)4 << 40) | ((uint64_t)prec << 32) | (uint32_t)slots; }
+
 bool cg_tuned_shape(Ctx *ctx, const GaugeField *f, int prec, int slots, KernelCfg &out, bool &reduce)
 {
-    const uint64_t key = ((uint64_t)1 << 40) | ((uint64_t)prec << 32) | (uint32_t)slots;
     std::lock_guard<std::mutex> lk(ctx->mu);
-    auto it = f->tuned.find(key);
+    auto it = f->tuned.find(timed_key(prec, slots));
+    if (it == f->tuned.end())
+        it = f->tuned.find(untimed_key(prec, slots));
     if (it == f->tuned.end())
         return false;
     out = it->second;
@@ -334,7 +341,7 @@ int Batch::finish_create()
     persist_ = S_ == 1 && single_ && !(forced && *forced) &&
                cg_persist_plan(ctx_->num_cus, f_->g, prec_, f_->rows, persist_plan_);
     // kernel shape for this (field, precision, slots): tuned on this workspace
-    const uint64_t key = ((uint64_t)1 << 40) | ((uint64_t)prec_ << 32) | (uint32_t)S_;
+    const uint64_t key = timed_key(prec_, S_);
     bool have = false;
     {
         std::lock_guard<std::mutex> lk(ctx_->mu);
@@ -359,7 +366,7 @@ int Batch::finish_create()
     } else if (persist_) {
         cfg_ = default_cg_cfg();  // the step kernels only step in if the one launch gives up: not timed
         std::lock_guard<std::mutex> lk(ctx_->mu);
-        f_->tuned[key] = cfg_;
+        f_->tuned[untimed_key(prec_, S_)] = cfg_;
     } else {
         cfg_ = tune_cg();  // also fills small_
         std::lock_guard<std::mutex> lk(ctx_->mu);
