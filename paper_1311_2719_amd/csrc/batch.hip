@@ -913,6 +913,17 @@ int Batch::wait_snapshot()
 // threads' solves get their turn.
 constexpr int kPersistSteps = 1024;
 
+int Batch::one_launch(const CgArgs &a, uint32_t seq)
+{
+    const hipError_t e = cg_persist_launch(persist_plan_, prec_, f_->rows, a, persist_slots_, seq, kPersistSteps, s_);
+    if (e != hipSuccess)
+        return set_error(STAG_EHIP, "CG launch failed: %s", hipGetErrorString(e));
+    STAG_HIP_CHECK(hipMemcpyAsync(abort_h_, (char *)persist_slots_ + cg_persist_abort_offset(), sizeof(int),
+                                  hipMemcpyDeviceToHost, s_));
+    const int rc = enqueue_snapshot();
+    return rc != STAG_OK ? rc : wait_snapshot();
+}
+
 int Batch::solve_in_one_launch(bool &gave_up)
 {
     const CgArgs a = args();
@@ -920,19 +931,15 @@ int Batch::solve_in_one_launch(bool &gave_up)
     STAG_HIP_CHECK(hipMemsetAsync(persist_slots_, 0, cg_persist_bytes(), s_));
     uint32_t seq = 0;
     for (;;) {
-        {
-            std::lock_guard<std::mutex> lk(persist_lock(ctx_->device));
-            const hipError_t e = cg_persist_launch(persist_plan_, prec_, f_->rows, a, persist_slots_, seq, kPersistSteps, s_);
-            if (e != hipSuccess)
-                return set_error(STAG_EHIP, "CG launch failed: %s", hipGetErrorString(e));
-            STAG_HIP_CHECK(hipMemcpyAsync(abort_h_, (char *)persist_slots_ + cg_persist_abort_offset(), sizeof(int),
-                                          hipMemcpyDeviceToHost, s_));
-            int rc = enqueue_snapshot();
-            if (rc == STAG_OK)
-                rc = wait_snapshot();
-            if (rc != STAG_OK)
-                return rc;
-        }
+        const int rc = [&]() -> int {
+            const LaunchPass pass(persist_gate(ctx_->device), persist_share(persist_plan_.nblk), ctx_->num_cus);
+            const int e = one_launch(a, seq);
+            if (e != STAG_OK)
+                (void)hipStreamSynchronize(s_);  // the CUs are free before the pass goes back
+            return e;
+        }();
+        if (rc != STAG_OK)
+            return rc;
         if (*abort_h_) {
             gave_up = true;
             persist_ = false;  // this workspace keeps to the step kernels
@@ -1131,6 +1138,12 @@ static int run_solve(Ctx *ctx, Batch &B, const std::shared_ptr<GaugeField> &f, i
         hipStream_t s;
         ~SyncOnExit() { (void)hipStreamSynchronize(s); }
     } drain{s};
+    // the caller's earlier work on the stream ends before a one-launch solve asks
+    // for its CUs, so that no other thread's solve waits for that work
+    if (B.persistent() && hipStreamQuery(s) == hipErrorNotReady) {
+        (void)hipGetLastError();  // not an error of a later launch
+        STAG_HIP_CHECK(hipStreamSynchronize(s));
+    }
     const size_t half = (size_t)3 * f->g.Vh * 2;  // doubles per parity half
     std::vector<int> systems;
     std::vector<char> running(B.nsys(), 0);

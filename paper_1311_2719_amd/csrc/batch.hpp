@@ -87,6 +87,7 @@ private:
     int launch_step(int ver, hipStream_t st, const KernelCfg &c);
     int finish_create();              // common tail of create / create_external
     void carve(void *base);           // device views into the workspace at base
+    int one_launch(const CgArgs &a, uint32_t seq);  // launched, and its outcome read back
     int mark_stage();                 // the staged host data are being copied
     void wait_stage();                // ... and may be overwritten after this
     int grid_x(const KernelCfg &c) const;

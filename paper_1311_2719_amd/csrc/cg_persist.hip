@@ -27,9 +27,9 @@
 //
 // Every wait is bounded: a block that waits longer than kWaitTicks raises the
 // abort word and leaves, the others follow, and the host repeats the solve with
-// the step kernels.  The grid has at most one block per CU, and the host runs
-// one such kernel at a time per device and process, so the blocks become
-// resident together once other kernels' blocks have ended.
+// the step kernels.  The grids that the host lets run at a time on a device (of
+// this process) have at most one block per CU together, so their blocks become
+// resident once other kernels' blocks have ended.
 //
 // A step takes 7 us on one block (4^4), 9 at 8^4, 13 at 12^3 16 and 18 at 16^4
 // in FP64: two chains of a gather, a block sum, a store that has to complete
@@ -38,7 +38,6 @@
 // 16^4 3.31 -> 2.44; FP32 1.30 -> 0.87, 1.41 -> 0.91, 2.24 -> 1.52, 2.64 -> 1.71.
 #include <algorithm>
 #include <cstdlib>
-#include <mutex>
 
 #include "batch.hpp"
 #include "cg_kernels.hpp"
@@ -515,10 +514,10 @@ int blocks_for_lps(const Geom &g, int lps)
 
 }  // namespace
 
-std::mutex &persist_lock(int device)
+LaunchGate &persist_gate(int device)
 {
-    static std::mutex mu[64];
-    return mu[device & 63];
+    static LaunchGate gate[64];
+    return gate[device & 63];
 }
 
 size_t cg_persist_bytes() { return (size_t)(kBlockWords + kGroupWords) * 8 + 256; }

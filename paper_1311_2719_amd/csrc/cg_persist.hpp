@@ -1,9 +1,8 @@
 // The CG loop of one right-hand side in one launch (cg_persist.hip).
 #pragma once
 
-#include <mutex>
-
 #include "cg_kernels.hpp"
+#include "launch_gate.hpp"
 
 namespace stag {
 
@@ -11,9 +10,12 @@ struct PersistPlan {
     int lps = 0, nblk = 0;
 };
 
-// One such kernel at a time per device in this process: held from its launch
-// until it has ended, since two could each hold CUs the other waits for.
-std::mutex &persist_lock(int device);
+// Passed from the launch of such a kernel until it has ended: two that do not
+// fit the CUs together could each hold CUs the other waits for.
+LaunchGate &persist_gate(int device);
+// What a grid counts there against the number of CUs: blocks are dealt to the
+// eight XCDs in turn, and each XCD must hold its share.
+inline int persist_share(int nblk) { return (nblk + 7) / 8 * 8; }
 // Sums a step exchanges between blocks, and the word that says a wait was given up.
 size_t cg_persist_bytes();
 inline size_t cg_persist_abort_offset() { return cg_persist_bytes() - 256; }

@@ -34,3 +34,40 @@ def test_server_of_one_slot_times_its_shape_after_a_one_launch_solve(monkeypatch
         ctx.cg_solve(f, b, again, mass=MASS, tol=TOL, precision=precision)
         torch.cuda.synchronize()
         assert torch.equal(x, again)
+
+
+def test_solves_at_once_on_two_streams_give_the_bits_of_solves_alone(gpu_ctx):
+    import threading
+
+    cases = [((4, 4, 4, 4), 451, binding.FP64), ((8, 8, 10, 14), 452, binding.FP32_RU), ((16, 16, 16, 16), 453, binding.FP64)]
+    links = [inputs.smooth_su3(d, 0.4, n) for d, n, _ in cases]
+    srcs = [inputs.gaussian_source(d, n + 10) for d, n, _ in cases]
+    out, errors = {}, []
+
+    def work(k, passes, key):
+        try:
+            d, _, prec = cases[k]
+            stream = torch.cuda.Stream()
+            with torch.cuda.stream(stream), binding.Context(device=0, arena_bytes=256 << 20, stream=stream) as ctx:
+                f = ctx.set_gauge(d, links[k])
+                b = ctx.pack(f, srcs[k])
+                for _ in range(passes):
+                    x = ctx.new_fermion(f)
+                    ctx.cg_solve(f, b, x, mass=MASS, tol=TOL, precision=prec)
+                    got = ctx.unpack(f, x)
+                    stream.synchronize()
+                    out.setdefault((key, k), []).append(got.cpu())
+        except Exception as e:  # noqa: BLE001
+            errors.append(e)
+
+    for k in range(len(cases)):
+        work(k, 1, "alone")
+    threads = [threading.Thread(target=work, args=(k, 6, "at once")) for k in range(len(cases))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
+    for k in range(len(cases)):
+        assert len(out["at once", k]) == 6
+        assert all(torch.equal(g, out["alone", k][0]) for g in out["at once", k]), cases[k]
