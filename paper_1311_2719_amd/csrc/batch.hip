@@ -323,6 +323,8 @@ int Batch::create_external(void *dev, size_t dev_bytes, void *host, size_t host_
     return finish_create();
 }
 
+static bool one_launch_paused(const Ctx *ctx);
+
 int Batch::finish_create()
 {
     const size_t nsys = 2 * (size_t)S_;
@@ -332,14 +334,22 @@ int Batch::finish_create()
     perm_h_ = (int *)(b_h_ + nsys);
     abort_h_ = perm_h_ + nsys;
     memset(stage_, 0, host_bytes_for(S_));
-    for (size_t j = 0; j < nsys; ++j)
-        perm_h_[j] = (int)j;
-    perm_last_.assign(perm_h_, perm_h_ + nsys);
     // one launch for a whole solve where the field allows it; a forced shape of
     // the step kernels asks for those
     const char *forced = getenv("STAG_KERNEL_CFG");
-    persist_ = S_ == 1 && single_ && !(forced && *forced) &&
+    persist_ = S_ == 1 && single_ && !(forced && *forced) && !one_launch_paused(ctx_) &&
                cg_persist_plan(ctx_->num_cus, f_->g, prec_, f_->rows, persist_plan_);
+    return choose_shape();
+}
+
+int Batch::choose_shape()
+{
+    const size_t nsys = 2 * (size_t)S_;
+    wait_stage();
+    for (size_t j = 0; j < nsys; ++j)
+        perm_h_[j] = (int)j;
+    perm_last_.assign(perm_h_, perm_h_ + nsys);
+    small_.clear();
     // kernel shape for this (field, precision, slots): tuned on this workspace
     const uint64_t key = timed_key(prec_, S_);
     bool have = false;
@@ -364,7 +374,7 @@ int Batch::finish_create()
     } else if (external_) {
         cfg_ = default_cg_cfg();  // no timing runs without events; not cached
     } else if (persist_) {
-        cfg_ = default_cg_cfg();  // the step kernels only step in if the one launch gives up: not timed
+        cfg_ = default_cg_cfg();  // timed only if the one launch gives up
         std::lock_guard<std::mutex> lk(ctx_->mu);
         f_->tuned[untimed_key(prec_, S_)] = cfg_;
     } else {
@@ -913,6 +923,24 @@ int Batch::wait_snapshot()
 // threads' solves get their turn.
 constexpr int kPersistSteps = 1024;
 
+// Something else holds the CUs of a device whose one-launch solve gave up
+// (another process, a long kernel), and a wait given up costs 0.3 s: for this
+// long the context's solves take the step kernels (1% at most is lost).
+constexpr int64_t kOneLaunchPauseNs = 30000000000;
+
+static int64_t steady_ns()
+{
+    return std::chrono::duration_cast<std::chrono::nanoseconds>(std::chrono::steady_clock::now().time_since_epoch()).count();
+}
+static bool one_launch_paused(const Ctx *ctx) { return steady_ns() < ctx->one_launch_from.load(); }
+static void pause_one_launch(Ctx *ctx) { ctx->one_launch_from.store(steady_ns() + kOneLaunchPauseNs); }
+
+int Batch::use_step_kernels()
+{
+    persist_ = false;
+    return choose_shape();
+}
+
 int Batch::one_launch(const CgArgs &a, uint32_t seq)
 {
     const hipError_t e = cg_persist_launch(persist_plan_, prec_, f_->rows, a, persist_slots_, seq, kPersistSteps, s_);
@@ -942,8 +970,10 @@ int Batch::solve_in_one_launch(bool &gave_up)
             return rc;
         if (*abort_h_) {
             gave_up = true;
-            persist_ = false;  // this workspace keeps to the step kernels
-            return STAG_OK;
+            pause_one_launch(ctx_);
+            if (getenv("STAG_EPOCH_VERBOSE"))
+                fprintf(stderr, "[stag epoch] one launch gave up waiting: step kernels\n");
+            return use_step_kernels();
         }
         seq += 3 * kPersistSteps + 1;
         bool done = true;
@@ -1138,6 +1168,8 @@ static int run_solve(Ctx *ctx, Batch &B, const std::shared_ptr<GaugeField> &f, i
         hipStream_t s;
         ~SyncOnExit() { (void)hipStreamSynchronize(s); }
     } drain{s};
+    if (B.persistent() && one_launch_paused(ctx) && (rc = B.use_step_kernels()) != STAG_OK)
+        return rc;
     // the caller's earlier work on the stream ends before a one-launch solve asks
     // for its CUs, so that no other thread's solve waits for that work
     if (B.persistent() && hipStreamQuery(s) == hipErrorNotReady) {
@@ -1172,8 +1204,8 @@ static int run_solve(Ctx *ctx, Batch &B, const std::shared_ptr<GaugeField> &f, i
         if ((rc = B.solve_in_one_launch(gave_up)) != STAG_OK)
             return rc;
         done = !gave_up;
-        if (gave_up && (rc = B.upload_and_init(systems)) != STAG_OK)  // from the start
-            return rc;
+        if (gave_up && ((rc = B.upload_and_init(systems)) != STAG_OK || (rc = B.set_running(running)) != STAG_OK))
+            return rc;  // from the start, with the step kernels
     }
     int E = 8, Emax = kEpochMax;
     const bool fixed_epoch = getenv("STAG_EPOCH") != nullptr;

@@ -76,6 +76,9 @@ public:
     // too long for another; the solve must start again with the step kernels).
     bool persistent() const { return persist_; }
     int solve_in_one_launch(bool &gave_up);
+    // This workspace's solves take the step kernels from now on (their shape is
+    // timed now); systems staged before are to be uploaded again.
+    int use_step_kernels();
     // Parities the step kernels cover from now on (bit 0 even, bit 1 odd): a
     // solve of one parity launches no blocks for the other.
     void set_parities(int mask) { parities_ = mask; }
@@ -87,6 +90,7 @@ private:
     int launch_step(int ver, hipStream_t st, const KernelCfg &c);
     int finish_create();              // common tail of create / create_external
     void carve(void *base);           // device views into the workspace at base
+    int choose_shape();  // the step kernels' shape, idle states, recorded epochs
     int one_launch(const CgArgs &a, uint32_t seq);  // launched, and its outcome read back
     int mark_stage();                 // the staged host data are being copied
     void wait_stage();                // ... and may be overwritten after this

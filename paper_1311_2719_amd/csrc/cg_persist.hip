@@ -164,9 +164,9 @@ struct GridSum {
         if (w < NV) {  // wavefront k receives value k
             const uint64_t t0 = wall_clock64();
             double s = 0.0, q;
-            bool ok = true;
+            bool ok = pa.wait_ticks != 0;  // 0: given up before the first look
             if (nblk <= kFlatBlocks) {
-                if (lane < nblk) {
+                if (ok && lane < nblk) {
                     ok = receive(mine + ((size_t)w * kMaxBlocks + lane) * 2, seq, t0, pa, q);
                     s = ok ? q : 0.0;
                 }
@@ -175,7 +175,7 @@ struct GridSum {
                 unsigned long long *grp = pa.slots + kBlockWords + (size_t)(seq & 1) * (kCopies * 4 * kMaxGroups * 2);
                 if (b % kGroup == 0) {
                     double g = 0.0;
-                    if (lane < kGroup && b + lane < nblk) {
+                    if (ok && lane < kGroup && b + lane < nblk) {
                         ok = receive(mine + ((size_t)w * kMaxBlocks + b + lane) * 2, seq, t0, pa, q);
                         g = ok ? q : 0.0;
                     }
@@ -556,7 +556,7 @@ hipError_t cg_persist_launch(const PersistPlan &plan, int prec, int rows, const 
     pa.seq0 = seq0;
     pa.max_steps = max_steps;
     pa.wait_ticks = kWaitTicks;
-    if (const char *e = getenv("STAG_PERSIST_TICKS"))  // tests: 0 gives up at the first long wait
+    if (const char *e = getenv("STAG_PERSIST_TICKS"))  // tests: 0 gives up at the first sum
         pa.wait_ticks = strtoull(e, nullptr, 10);
 #define STAG_PERSIST_CASE(P, LPS)                                                                          \
     return rows == 2 ? launch<P, LPS, 2>(pa, plan.nblk, s) : launch<P, LPS, 3>(pa, plan.nblk, s)

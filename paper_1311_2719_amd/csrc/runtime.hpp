@@ -120,6 +120,7 @@ struct Ctx {
     int slots_per_field = 16;
     int epoch_iters = 16;
     int queue_capacity = 4096;
+    std::atomic<int64_t> one_launch_from{0};  // steady clock, ns: before it, solves take the step kernels
 
     std::shared_ptr<GaugeField> field(int32_t id);
 };

@@ -71,3 +71,80 @@ def test_solves_at_once_on_two_streams_give_the_bits_of_solves_alone(gpu_ctx):
     for k in range(len(cases)):
         assert len(out["at once", k]) == 6
         assert all(torch.equal(g, out["alone", k][0]) for g in out["at once", k]), cases[k]
+
+
+@pytest.mark.parametrize("dims", [DIMS, (8, 8, 10, 14)])  # 4 blocks; 70 blocks, sums through groups
+@pytest.mark.parametrize("precision,parity", [(binding.FP64, binding.ALL), (binding.FP32_RU, binding.ODD)])
+def test_given_up_launch_hands_over_once(monkeypatch, capfd, dims, precision, parity):
+    # no wait at all: the first sum is given up.  The step kernels repeat the
+    # solve, bit for bit as they run it by themselves (untimed shape on both
+    # sides), and the context's next solves take them at once
+    U, src = inputs.smooth_su3(dims, 0.5, 461), inputs.gaussian_source(dims, 462)
+    monkeypatch.setenv("STAG_TUNE", "0")
+    monkeypatch.setenv("STAG_EPOCH_VERBOSE", "1")
+
+    def solve(ctx, f, noalloc=False):
+        b, x = ctx.pack(f, src), ctx.new_fermion(f)
+        call = ctx.cg_solve_noalloc if noalloc else ctx.cg_solve
+        info = call(f, b, x, mass=MASS, tol=TOL, precision=precision, parity=parity)
+        torch.cuda.synchronize()
+        assert info["status"] == 0 and info["true_rel_resid"] <= TOL
+        return x.cpu(), capfd.readouterr().err.count("gave up")
+
+    monkeypatch.setenv("STAG_PERSIST", "0")
+    with binding.Context(device=0, arena_bytes=256 << 20) as ctx:
+        want, n = solve(ctx, ctx.set_gauge(dims, U))
+        assert n == 0
+    monkeypatch.setenv("STAG_PERSIST", "4")
+    for noalloc in (False, True):
+        monkeypatch.setenv("STAG_PERSIST_TICKS", "0")
+        with binding.Context(device=0, arena_bytes=256 << 20) as ctx:
+            f, g = ctx.set_gauge(dims, U), ctx.set_gauge(dims, U)
+            first, n = solve(ctx, f, noalloc)
+            assert n == 1 and torch.equal(first, want)
+            monkeypatch.delenv("STAG_PERSIST_TICKS")
+            for field in (f, g):
+                again, n = solve(ctx, field, noalloc)
+                assert n == 0 and torch.equal(again, want)
+
+
+def test_given_up_launch_times_the_step_shape(monkeypatch, capfd):
+    U, src = inputs.smooth_su3(DIMS, 0.5, 471), inputs.gaussian_source(DIMS, 472)
+    monkeypatch.setenv("STAG_PERSIST", "4")
+    monkeypatch.setenv("STAG_PERSIST_TICKS", "0")
+    monkeypatch.setenv("STAG_TUNE_VERBOSE", "1")
+    with binding.Context(device=0, arena_bytes=256 << 20) as ctx:
+        f = ctx.set_gauge(DIMS, U)
+        b, x = ctx.pack(f, src), ctx.new_fermion(f)
+        ctx.cg_solve(f, b, x, mass=MASS, tol=TOL)
+        assert "[stag tune cg]" in capfd.readouterr().err
+        assert oracle.true_residual(DIMS, U, MASS, src, ctx.unpack(f, x).cpu().numpy()) <= TOL
+        # a lane of one slot on the field takes the timed shape over
+        ctx.serve_config(slots_per_field=1)
+        t = ctx.submit(f, b, x, mass=MASS, tol=TOL)
+        assert ctx.wait(t)["rc"] == 0
+        ctx.release(t)
+        assert "[stag tune cg]" not in capfd.readouterr().err
+
+
+@pytest.mark.parametrize("precision,parity", [(binding.FP64, binding.ALL), (binding.FP32_RU, binding.ALL),
+                                              (binding.FP64, binding.ODD)])
+def test_solves_of_several_launches(monkeypatch, precision, parity):
+    # more than 1024 steps: r, p, x and u go through memory between two launches
+    dims, mass = (8, 8, 8, 8), 0.01
+    U, src = inputs.haar_su3(dims, 481), inputs.gaussian_source(dims, 482)
+    got = {}
+    for mode in ("4", "0"):
+        monkeypatch.setenv("STAG_PERSIST", mode)
+        with binding.Context(device=0, arena_bytes=256 << 20) as ctx:
+            f = ctx.set_gauge(dims, U)
+            b, x = ctx.pack(f, src), ctx.new_fermion(f)
+            info = ctx.cg_solve(f, b, x, mass=mass, tol=TOL, precision=precision, parity=parity, maxiter=40000)
+            assert info["iters"] > 1024 + 64 and info["true_rel_resid"] <= TOL, info
+            got[mode] = info, ctx.unpack(f, x).cpu().numpy()
+    if parity == binding.ALL:
+        assert oracle.true_residual(dims, U, mass, src, got["4"][1]) <= TOL
+    # a state lost between launches would cost a restart: hundreds of steps.
+    # The two forms round differently; their counts agree to a few percent
+    a, b = got["4"][0]["iters"], got["0"][0]["iters"]
+    assert abs(a - b) <= 0.1 * b, (a, b)
