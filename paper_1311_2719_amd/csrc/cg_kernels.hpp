@@ -410,10 +410,9 @@ template <class P, int R, int LPS> struct OwnSite {
                     pr_[q][c] = uv[(int64_t)c * Vh + s];
         }
     }
-    // K1, direct form: p (current buffer) and r of systems r0 .. r0 + G - 1 at the partner site
+    // K1, direct form (FP16): p (current buffer) and r of systems r0 .. r0 + G - 1 at the partner site
     template <class Args>
-    __device__ __forceinline__ void load_k1(const Args &a, const int *js, const bool *cg, const int *pc, int s,
-                                            int sub, int r0)
+    __device__ __forceinline__ void load_k1(const Args &a, const int *js, const bool *cg, const int *pc, int s, int r0)
     {
         const int Vh = a.g.Vh;
 #pragma unroll
@@ -422,20 +421,14 @@ template <class P, int R, int LPS> struct OwnSite {
             if (r >= R || !cg[r])
                 continue;
             const v2 *rv = (const v2 *)a.r + (size_t)js[r] * 3 * Vh;
-            const void *pold = spin_at<P>(a.p[pc[r]], js[r], Vh);
-            if constexpr (P::id == 2)
-                P::load_spinor(pold, Vh, s, ps_[q]);
+            P::load_spinor(spin_at<P>(a.p[pc[r]], js[r], Vh), Vh, s, ps_[q]);
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                if (P::id != 2 && !owns_colour<LPS>(sub, c))
-                    continue;
+            for (int c = 0; c < 3; ++c)
                 rr_[q][c] = rv[(int64_t)c * Vh + s];
-                if constexpr (P::id != 2)
-                    pr_[q][c] = ((const v2 *)pold)[(int64_t)c * Vh + s];
-            }
         }
     }
-    // K2: p (recurrence form: the last direction; direct form: p'), x and r of systems r0 .. r0 + G - 1 at the own site.
+    // K2: p (recurrence form: the last direction, pn unused; direct form: p' in buffer pn[r]), x and r of systems
+    // r0 .. r0 + G - 1 at the own site.
     // x, and in the recurrence form p, are read and written once per step, at
     // their own site only: non-temporal accesses keep them from evicting the
     // gathered vectors (32^4 step, x and p instead of x alone: FP32 118.8 -> 114.2 us,
@@ -452,7 +445,7 @@ template <class P, int R, int LPS> struct OwnSite {
             if (r >= R || !cg[r])
                 continue;
             const int j = js[r];
-            const void *pb = spin_at<P>(a.p[pn[r]], j, Vh);
+            const void *pb = spin_at<P>(kRecurrence<P> ? a.p[0] : a.p[pn[r]], j, Vh);
             const v2 *rv = (const v2 *)a.r + (size_t)j * 3 * Vh;
             if constexpr (P::id == 2)
                 P::load_spinor(pb, Vh, s, ps_[q]);
@@ -781,14 +774,14 @@ __device__ __forceinline__ void step1_direct(const CgArgs &a, int ver)
             using Own = OwnSite<P, R, LPS>;
             Own own;
             if constexpr (Own::kBeforeHop)
-                own.load_k1(a, js, cg, pc, s, sub, 0);
+                own.load_k1(a, js, cg, pc, s, 0);
             hop_accumulate<P, LPS, R, decltype(load), false, ROWS>(a.g, (const typename P::link_t *)a.links[pout],
                                                                    (const typename P::link_t *)a.links[1 - pout],
                                                                    a.nbr[pout], pout, s, sub, acc, load);
 #pragma unroll
             for (int g = 0; g < R; g += Own::G) {
                 if constexpr (!Own::kBeforeHop)
-                    own.load_k1(a, js, cg, pc, s, sub, g);
+                    own.load_k1(a, js, cg, pc, s, g);
 #pragma unroll
                 for (int q = 0; q < Own::G; ++q) {
                     const int r = g + q;
@@ -877,7 +870,6 @@ __device__ __forceinline__ void step2_recurrence(const CgArgs &a, int ver)
         return;
     bool cg[R], ru[R], anycg = false, anyru = false;
     real alpha[R], beta[R], m2[R];
-    int p0[R];
     if (a.nread == 0) {
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -920,7 +912,6 @@ __device__ __forceinline__ void step2_recurrence(const CgArgs &a, int ver)
     }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        p0[r] = 0;  // p is updated in place
         anycg |= cg[r];
         anyru |= ru[r];
     }
@@ -951,14 +942,14 @@ __device__ __forceinline__ void step2_recurrence(const CgArgs &a, int ver)
         // this site's p, x and r
         Own own;
         if constexpr (Own::kBeforeHop)
-            own.load_k2(a, js, cg, p0, s, sub, 0);
+            own.load_k2(a, js, cg, nullptr, s, sub, 0);
         hop_accumulate<P, LPS, R, decltype(load), false, ROWS>(
             a.g, (const typename P::link_t *)a.links[par], (const typename P::link_t *)a.links[1 - par], a.nbr[par],
             par, s, sub, acc, load);
 #pragma unroll
         for (int g = 0; g < R; g += Own::G) {
             if constexpr (!Own::kBeforeHop)
-                own.load_k2(a, js, cg, p0, s, sub, g);
+                own.load_k2(a, js, cg, nullptr, s, sub, g);
 #pragma unroll
             for (int q = 0; q < Own::G; ++q) {
                 const int r = g + q;
