@@ -811,6 +811,13 @@ CgArgs Batch::args() const
     a.pstride = pstride_;
     a.remap = remap_for(cfg_, nblk_);
     a.nread = reduce_ ? 0 : nblk_;
+    // what a step reads and writes of the links, and of each system's r, x, u and p
+    const size_t nsys = (size_t)a.npar * S_, links = 2 * link_parity_entries(f_->rows, f_->g.Vh) * link_entry_bytes_of(prec_);
+    const size_t per_site = 2 * (prec_ == 0 ? 48 : 24) + spinor_bytes_of(prec_) * (prec_ == STAG_FP16_RU ? 3 : 2);
+    a.nt_vectors = streams_vectors(prec_, links + nsys * f_->g.Vh * per_site);
+    if (const char *e = getenv("STAG_NT_VECTORS"))
+        if (prec_ != STAG_FP64 && (e[0] == '0' || e[0] == '1'))
+            a.nt_vectors = e[0] == '1';
     return a;
 }
 

@@ -45,6 +45,8 @@
 // compaction never changes results.
 #pragma once
 
+#include <type_traits>
+
 #include "hop.hpp"
 
 namespace stag {
@@ -101,6 +103,7 @@ struct CgArgs {
     // per-block partials that a prologue sums per slot; 0: k_cg_scalars has
     // summed them, st[ver ^ 1] holds the state of the step and alpha
     int nread;
+    int nt_vectors;            // FP32, FP16: x and p of K2 are accessed non-temporally (streams_vectors)
 };
 
 template <typename T> struct vec2_of;
@@ -374,6 +377,49 @@ __device__ __forceinline__ int64_t round_base(int it, int chunk, int nchunks)
     return ((int64_t)it * nchunks + chunk) * blockDim.x + threadIdx.x;
 }
 
+// x, and in the recurrence form p, are read and written once per step, at their
+// own site only.  Where a step's links and vectors exceed the Infinity Cache,
+// non-temporal accesses keep them from evicting the gathered vectors (32^4
+// step, x and p instead of x alone: FP32 118.8 -> 114.2 us, FP64 275 -> 271;
+// batched K2 of 24 systems at 24^4, neither -> x -> both: FP32 188 -> 179 ->
+// 160 us, FP16 155 -> 141).  Where they fit it the next step finds x and p
+// there: FP32 and FP16 solves with plain accesses gain 0.5% (8^4) to 3.5% (12^4
+// of 24 systems, 20^4 of 6), nothing at 177 to 255 MB, and lose 3% (24^4 of 24
+// systems, 446 MB) to 10% (32^4, 302 MB).  FP64, whose links take most of a
+// step's bytes, loses up to 5% without them at every size but one (12^4 of 4
+// systems, 1%), so it always has them.
+inline bool streams_vectors(int prec, size_t step_bytes) { return prec == 0 || step_bytes > ((size_t)256 << 20); }
+
+// fn(true_type): non-temporal accesses, fn(false_type): plain ones.  The empty
+// statements keep the compiler from merging the accesses of the two branches,
+// which would make all of them plain.
+template <class Fn> __device__ __forceinline__ void by_access(int nt, Fn fn)
+{
+    if (nt) {
+        asm volatile("");
+        fn(std::true_type{});
+        asm volatile("");
+    } else {
+        fn(std::false_type{});
+    }
+}
+
+template <bool NT, class T> __device__ __forceinline__ T load_own(const T *p)
+{
+    if constexpr (NT)
+        return __builtin_nontemporal_load(p);
+    else
+        return *p;
+}
+
+template <bool NT, class T> __device__ __forceinline__ void store_own(const T &v, T *p)
+{
+    if constexpr (NT)
+        __builtin_nontemporal_store(v, p);
+    else
+        *p = v;
+}
+
 // ---- own-site values of a step ------------------------------------------------------
 // The values a step kernel reads at its own site (not gathered) are loaded
 // in groups of G = 2 systems, all loads of a group before any use, so that a
@@ -429,12 +475,7 @@ template <class P, int R, int LPS> struct OwnSite {
     }
     // K2: p (recurrence form: the last direction, pn unused; direct form: p' in buffer pn[r]), x and r of systems
     // r0 .. r0 + G - 1 at the own site.
-    // x, and in the recurrence form p, are read and written once per step, at
-    // their own site only: non-temporal accesses keep them from evicting the
-    // gathered vectors (32^4 step, x and p instead of x alone: FP32 118.8 -> 114.2 us,
-    // FP64 275 -> 271; 24^4 within 1%; batched K2 of 24 systems at 24^4, neither ->
-    // x -> both: FP32 188 -> 179 -> 160 us, FP16 155 -> 141).
-    template <class Args>
+    template <bool NT, class Args>
     __device__ __forceinline__ void load_k2(const Args &a, const int *js, const bool *cg, const int *pn, int s,
                                             int sub, int r0)
     {
@@ -455,16 +496,40 @@ template <class P, int R, int LPS> struct OwnSite {
                     continue;
                 const int64_t o = (int64_t)c * Vh + s;
                 if constexpr (P::id != 2) {
-                    const v2 t = __builtin_nontemporal_load((const v2 *)pb + o);
+                    const v2 t = load_own<NT>((const v2 *)pb + o);
                     ps_[q][c] = {t.x, t.y};
                 }
                 if constexpr (P::id == 0)
-                    xx_[q][c] = __builtin_nontemporal_load(&a.xhi[j][o]);
+                    xx_[q][c] = load_own<NT>(&a.xhi[j][o]);
                 else
-                    xx_[q][c] = __builtin_nontemporal_load(&a.xlo[(size_t)j * 3 * Vh + o]);
+                    xx_[q][c] = load_own<NT>(&a.xlo[(size_t)j * 3 * Vh + o]);
                 rr_[q][c] = rv[o];
             }
         }
+    }
+    template <class Args>
+    __device__ __forceinline__ void load_k2_any(const Args &a, const int *js, const bool *cg, const int *pn, int s,
+                                                int sub, int r0)
+    {
+        by_access(a.nt_vectors, [&](auto nt) { load_k2<decltype(nt)::value>(a, js, cg, pn, s, sub, r0); });
+    }
+    // FP32, FP16, K2: x, and in the recurrence form p, of system j at its own site
+    template <class Args>
+    __device__ __forceinline__ void store_k2(const Args &a, int j, int s, int sub, const v2 (&pn)[3],
+                                             const xv_t (&xn)[3]) const
+    {
+        by_access(a.nt_vectors, [&](auto nt) {
+            constexpr bool NT = decltype(nt)::value;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                if (!owns_colour<LPS>(sub, c))
+                    continue;
+                const int64_t o = (int64_t)c * a.g.Vh + s;
+                if constexpr (kRecurrence<P>)
+                    store_own<NT>(pn[c], (v2 *)spin_at<P>(a.p[0], j, a.g.Vh) + o);
+                store_own<NT>(xn[c], &a.xlo[(size_t)j * 3 * a.g.Vh + o]);
+            }
+        });
     }
 };
 
@@ -941,15 +1006,23 @@ __device__ __forceinline__ void step2_recurrence(const CgArgs &a, int ver)
         };
         // this site's p, x and r
         Own own;
-        if constexpr (Own::kBeforeHop)
-            own.load_k2(a, js, cg, nullptr, s, sub, 0);
+        if constexpr (Own::kBeforeHop) {
+            // FP64 directly: through one more function the schedule waits half as
+            // often, and a 24^4 solve takes 1.8% longer
+            if constexpr (P::id == 0)
+                own.template load_k2<true>(a, js, cg, nullptr, s, sub, 0);
+            else
+                own.load_k2_any(a, js, cg, nullptr, s, sub, 0);
+        }
         hop_accumulate<P, LPS, R, decltype(load), false, ROWS>(
             a.g, (const typename P::link_t *)a.links[par], (const typename P::link_t *)a.links[1 - par], a.nbr[par],
             par, s, sub, acc, load);
 #pragma unroll
         for (int g = 0; g < R; g += Own::G) {
-            if constexpr (!Own::kBeforeHop)
-                own.load_k2(a, js, cg, nullptr, s, sub, g);
+            if constexpr (!Own::kBeforeHop && P::id == 0)
+                own.template load_k2<true>(a, js, cg, nullptr, s, sub, g);
+            if constexpr (!Own::kBeforeHop && P::id != 0)
+                own.load_k2_any(a, js, cg, nullptr, s, sub, g);
 #pragma unroll
             for (int q = 0; q < Own::G; ++q) {
                 const int r = g + q;
@@ -958,6 +1031,8 @@ __device__ __forceinline__ void step2_recurrence(const CgArgs &a, int ver)
                 const int j = js[r];
                 v2 *rv = (v2 *)a.r + (size_t)j * 3 * Vh;
                 v2 *pv = (v2 *)spin_at<P>(a.p[0], j, Vh);
+                v2 p_new[3];
+                typename Own::xv_t x_new[3];
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
                     if (!owns_colour<LPS>(sub, c))
@@ -967,14 +1042,15 @@ __device__ __forceinline__ void step2_recurrence(const CgArgs &a, int ver)
                     // beta = 0 starts from p = 0, whatever the buffer holds
                     const v2 po = v2{own.ps_[q][c].re, own.ps_[q][c].im};
                     const v2 pn = beta[r] != real(0) ? v2{fma(beta[r], po.x, rr.x), fma(beta[r], po.y, rr.y)} : rr;
-                    __builtin_nontemporal_store(pn, &pv[o]);
                     const auto xv = own.xx_[q][c];
-                    if constexpr (P::id == 0)
+                    if constexpr (P::id == 0) {  // one kind of access: each store as soon as it can go
+                        __builtin_nontemporal_store(pn, &pv[o]);
                         __builtin_nontemporal_store(dbl2{fma(alpha[r], pn.x, xv.x), fma(alpha[r], pn.y, xv.y)},
                                                     &a.xhi[j][o]);
-                    else
-                        __builtin_nontemporal_store(flt2{fmaf(alpha[r], pn.x, xv.x), fmaf(alpha[r], pn.y, xv.y)},
-                                                    &a.xlo[(size_t)j * 3 * Vh + o]);
+                    } else {
+                        p_new[c] = pn;
+                        x_new[c] = {fmaf(alpha[r], pn.x, xv.x), fmaf(alpha[r], pn.y, xv.y)};
+                    }
                     const real apr = m2[r] * pn.x - acc[r][c].re;
                     const real api = m2[r] * pn.y - acc[r][c].im;
                     rr.x = fma(-alpha[r], apr, rr.x);
@@ -983,6 +1059,8 @@ __device__ __forceinline__ void step2_recurrence(const CgArgs &a, int ver)
                     nrm[r] += (double)rr.x * rr.x + (double)rr.y * rr.y;
                     nrm[R + r] += (double)rr.x * pn.x + (double)rr.y * pn.y;
                 }
+                if constexpr (P::id != 0)
+                    own.store_k2(a, j, s, sub, p_new, x_new);
             }
         }
     }
@@ -1094,14 +1172,14 @@ __device__ __forceinline__ void step2_direct(const CgArgs &a, int ver)
             using Own = OwnSite<P, R, LPS>;
             Own own;
             if constexpr (Own::kBeforeHop)
-                own.load_k2(a, js, cg, pnew, s, sub, 0);
+                own.load_k2_any(a, js, cg, pnew, s, sub, 0);
             hop_accumulate<P, LPS, R, decltype(load), false, ROWS>(a.g, (const typename P::link_t *)a.links[par],
                                                                    (const typename P::link_t *)a.links[1 - par],
                                                                    a.nbr[par], par, s, sub, acc, load);
 #pragma unroll
             for (int g = 0; g < R; g += Own::G) {
                 if constexpr (!Own::kBeforeHop)
-                    own.load_k2(a, js, cg, pnew, s, sub, g);
+                    own.load_k2_any(a, js, cg, pnew, s, sub, g);
 #pragma unroll
                 for (int q = 0; q < Own::G; ++q) {
                     const int r = g + q;
@@ -1109,23 +1187,24 @@ __device__ __forceinline__ void step2_direct(const CgArgs &a, int ver)
                         continue;
                     const int j = js[r];
                     v2 *rv = (v2 *)a.r + (size_t)j * 3 * Vh;
+                    v2 pn[3];  // stored by K1
+                    flt2 xn[3];
 #pragma unroll
                     for (int c = 0; c < 3; ++c) {
                         if (!owns_colour<LPS>(sub, c))
                             continue;
                         const cplx<real> pv = own.ps_[q][c];
-                        const int64_t o = (int64_t)c * Vh + s;
                         const flt2 xv = own.xx_[q][c];
-                        __builtin_nontemporal_store(flt2{fmaf(alpha[r], pv.re, xv.x), fmaf(alpha[r], pv.im, xv.y)},
-                                                    &a.xlo[(size_t)j * 3 * Vh + o]);
+                        xn[c] = flt2{fmaf(alpha[r], pv.re, xv.x), fmaf(alpha[r], pv.im, xv.y)};
                         const real apr = m2[r] * pv.re - acc[r][c].re;
                         const real api = m2[r] * pv.im - acc[r][c].im;
                         v2 rr = own.rr_[q][c];
                         rr.x = fma(-alpha[r], apr, rr.x);
                         rr.y = fma(-alpha[r], api, rr.y);
-                        rv[o] = rr;
+                        rv[(int64_t)c * Vh + s] = rr;
                         nrm[r] += (double)rr.x * rr.x + (double)rr.y * rr.y;
                     }
+                    own.store_k2(a, j, s, sub, pn, xn);
                 }
             }
         }

@@ -542,27 +542,28 @@ __global__ void __launch_bounds__(64 * W, kSharedMinWaves) k_cg_shared2(CgArgs a
             cplx<real> pv[RR][3];
             flt2 xv[RR][3];
             v2 ro[RR][3];
-            auto own = [&]() {
+            auto own_as = [&](auto nt) {
+                constexpr bool NT = decltype(nt)::value;
 #pragma unroll
                 for (int q = 0; q < RR; ++q) {
                     if (!cg[q])
                         continue;
                     const int j = js[q];
-                    // x and p (FP32) non-temporally, as in the register tiles
                     const void *pb = spin_at<P>(a.p[pn_buf[q]], j, Vh);
                     if constexpr (!kRecurrence<P>)
                         P::load_spinor(pb, Vh, s, pv[q]);
 #pragma unroll
                     for (int c = 0; c < 3; ++c) {
                         if constexpr (kRecurrence<P>) {
-                            const v2 t = __builtin_nontemporal_load((const v2 *)pb + (int64_t)c * Vh + s);
+                            const v2 t = load_own<NT>((const v2 *)pb + (int64_t)c * Vh + s);
                             pv[q][c] = {t.x, t.y};
                         }
-                        xv[q][c] = __builtin_nontemporal_load(&a.xlo[(size_t)j * 3 * Vh + (int64_t)c * Vh + s]);
+                        xv[q][c] = load_own<NT>(&a.xlo[(size_t)j * 3 * Vh + (int64_t)c * Vh + s]);
                         ro[q][c] = ((const v2 *)a.r)[(size_t)j * 3 * Vh + (int64_t)c * Vh + s];
                     }
                 }
             };
+            auto own = [&]() { by_access(a.nt_vectors, own_as); };
             if constexpr (RR == 1)
                 own();
             cplx<float> acc[RR][3];
@@ -590,8 +591,7 @@ __global__ void __launch_bounds__(64 * W, kSharedMinWaves) k_cg_shared2(CgArgs a
                         pv[q][c].re = be[q] != 0.f ? fmaf(be[q], pv[q][c].re, ro[q][c].x) : ro[q][c].x;
                         pv[q][c].im = be[q] != 0.f ? fmaf(be[q], pv[q][c].im, ro[q][c].y) : ro[q][c].y;
                     }
-                    __builtin_nontemporal_store(
-                        flt2{fmaf(al[q], pv[q][c].re, xv[q][c].x), fmaf(al[q], pv[q][c].im, xv[q][c].y)}, &xl[o]);
+                    xv[q][c] = flt2{fmaf(al[q], pv[q][c].re, xv[q][c].x), fmaf(al[q], pv[q][c].im, xv[q][c].y)};
                     const real apr = m2r[q] * pv[q][c].re - acc[q][c].re;
                     const real api = m2r[q] * pv[q][c].im - acc[q][c].im;
                     v2 rn = ro[q][c];
@@ -599,11 +599,19 @@ __global__ void __launch_bounds__(64 * W, kSharedMinWaves) k_cg_shared2(CgArgs a
                     rn.y = fma(-al[q], api, rn.y);
                     rv[o] = rn;
                     nrm[q] += (double)rn.x * rn.x + (double)rn.y * rn.y;
-                    if constexpr (kRecurrence<P>) {
+                    if constexpr (kRecurrence<P>)
                         nrp[q] += (double)rn.x * pv[q][c].re + (double)rn.y * pv[q][c].im;
-                        __builtin_nontemporal_store(v2{pv[q][c].re, pv[q][c].im}, (v2 *)spin_at<P>(a.p[0], j, Vh) + o);
-                    }
                 }
+                by_access(a.nt_vectors, [&](auto nt) {
+                    constexpr bool NT = decltype(nt)::value;
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        const int64_t o = (int64_t)c * Vh + s;
+                        store_own<NT>(xv[q][c], &xl[o]);
+                        if constexpr (kRecurrence<P>)
+                            store_own<NT>(v2{pv[q][c].re, pv[q][c].im}, (v2 *)spin_at<P>(a.p[0], j, Vh) + o);
+                    }
+                });
             }
         }
     }
