@@ -128,7 +128,7 @@ bool cg_tuned_shape(Ctx *ctx, const GaugeField *f, int prec, int slots, KernelCf
 namespace {
 
 // What k_cg_scalars does with the sums of system blockIdx.x.
-enum ScalarsKind : int { kAfterK1 = 0, kAfterK2 = 1, kAfterInit = 2, kSumOnly = 3 };
+enum ScalarsKind : int { kAfterK1 = 0, kAfterK2 = 1, kAfterInit = 2 };
 
 // The scalars of one step, once per system instead of in every block of the
 // next kernel: totals of the partials [0, nblk) of the slots the last kernel
@@ -136,8 +136,7 @@ enum ScalarsKind : int { kAfterK1 = 0, kAfterK2 = 1, kAfterInit = 2, kSumOnly = 
 // in that state with <u',u'> (FP16: and <p',p'>); after K2 the state of the
 // next step, from buffer cur into buffer ver; after the initialisation the
 // first step's state, from buffer 0 into 1, for systems still in M_INIT.
-// kSumOnly forms the sums and leaves the states alone (timing runs).  Running it again
-// over unchanged partials and states gives the same result.  A block reads
+// Running it again over unchanged partials and states gives the same result.  A block reads
 // up to 8192 partials per slot, 8 per thread and slot in flight.
 template <bool REC>
 __global__ void __launch_bounds__(1024) k_cg_scalars(CgArgs a, int ver, int kind, int nblk)
@@ -200,11 +199,25 @@ __global__ void __launch_bounds__(1024) k_cg_scalars(CgArgs a, int ver, int kind
             advance<REC>(st, s);
         }
         a.st[ver][j] = st;
-    } else if (kind == kAfterInit) {
+    } else {
         advance<REC>(st, t);
         a.st[1][j] = st;
-    } else if (t[0] == -1.0) {  // never (a sum of squares): keeps the sums alive
-        a.st[cur][j].apap = t[0];
+    }
+}
+
+// A source for timed solves: values in [-1, 1) that no field's D maps to few
+// of its eigenvectors.
+__global__ void __launch_bounds__(256) k_timing_source(dbl2 *v, int64_t n)
+{
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        uint32_t h[2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {  // a mixing of the index (odd multipliers and shifts)
+            uint32_t z = (uint32_t)(2 * i + k) * 2654435769u + 12345u;
+            z = (z ^ z >> 15) * 2246822519u;
+            h[k] = z ^ z >> 13;
+        }
+        v[i] = dbl2{h[0] * 0x1p-31 - 1.0, h[1] * 0x1p-31 - 1.0};
     }
 }
 
@@ -434,51 +447,38 @@ int Batch::set_running(const std::vector<char> &running)
     return mark_stage();
 }
 
-// Time K1 + K2 of one step with every system in a CG step on filled vectors.
-double Batch::time_cg_config(const KernelCfg &c, int nblk, bool reduce)
+// Time a step of a solve of the first `running` systems of each parity with
+// shape c on nblk blocks: the fastest of `runs` runs of `reps` steps, from a fresh
+// source and the states in tune_st_.  recompute: the first system recomputes
+// its residual in every other step.
+double Batch::time_cg_config(const KernelCfg &c, int nblk, bool reduce, int running, int reps, int runs, bool recompute)
 {
     if (nblk < 1 || nblk > pstride_)  // partial sums are indexed by block: never past a slot
         return 1e30;
-    const CgLaunchTable &t = cg_table(prec_, f_->rows, f_->nt_links);
-    CgArgs a = args();
-    for (int par = 0; par < 2; ++par)
-        a.nbr[par] = c.tables ? f_->nbr_for(par) : nullptr;
-    a.remap = remap_for(c, nblk);
-    a.nread = reduce ? 0 : nblk;
-    if (c.shared && !t.shared1)
-        return 1e30;
-    a.npar = 2;
-    a.par0 = 0;
-    dim3 grid((unsigned)nblk * (unsigned)(nsys() / c.rtile)), blk(c.block);
-    // every shape starts from the same states, vectors and partials
-    const size_t ns = (size_t)nsys(), sb = ns * sizeof(SysState);
-    if (hipMemcpyAsync(st_d_[0], tune_st_.data(), sb, hipMemcpyHostToDevice, s_) != hipSuccess ||
+    cfg_ = c;
+    nblk_ = nblk;
+    reduce_ = reduce;
+    tune_st_[0].delta2 = recompute ? 1e30 : 0.0;
+    std::vector<int> places((size_t)nsys(), -1);
+    for (int j = 0; j < running; ++j) {
+        places[j] = j;
+        places[S_ + j] = S_ + j;
+    }
+    const int64_t n = (int64_t)nsys() * 3 * f_->g.Vh;
+    hipLaunchKernelGGL(k_timing_source, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 2048)), dim3(256), 0, s_, tmp_, n);
+    const size_t sb = (size_t)nsys() * sizeof(SysState);
+    if (hipGetLastError() != hipSuccess ||
+        hipMemcpyAsync(perm_d_, places.data(), places.size() * sizeof(int), hipMemcpyHostToDevice, s_) != hipSuccess ||
+        hipMemcpyAsync(st_d_[0], tune_st_.data(), sb, hipMemcpyHostToDevice, s_) != hipSuccess ||
         hipMemcpyAsync(st_d_[1], tune_st_.data(), sb, hipMemcpyHostToDevice, s_) != hipSuccess ||
-        hipMemsetAsync(p_[0], 0x3f, (char *)tmp_ - (char *)p_[0] + ns * 3 * f_->g.Vh * 16, s_) != hipSuccess ||
-        hipMemsetAsync(partials_, 0x3f, 2 * ns * 3 * (size_t)pstride_ * sizeof(double), s_) != hipSuccess)
+        launch_init() != STAG_OK || launch_step(0, s_, c) != STAG_OK)
         return 1e30;
-    auto step = [&]() {
-        hipError_t e = c.shared ? t.shared1(c.rtile, c.block / 64, grid, s_, a, 0)
-                                 : t.step1(c.lps, c.rtile, grid, blk, s_, a, 0);
-        if (e == hipSuccess && reduce)
-            e = launch_scalars(s_, a, 0, kSumOnly, nblk);
-        if (e == hipSuccess)
-            e = c.shared ? t.shared2(c.rtile, c.block / 64, grid, s_, a, 0)
-                         : t.step2(c.lps, c.rtile, grid, blk, s_, a, 0);
-        if (e == hipSuccess && reduce)
-            e = launch_scalars(s_, a, 0, kSumOnly, nblk);
-        return e;
-    };
-    if (step() != hipSuccess)
-        return 1e30;
-    // the faster of two runs of 5 steps: single short runs vary by more than
-    // the differences between the leading shapes
-    const int reps = 5;
     double best = 1e30;
-    for (int run = 0; run < 2; ++run) {
+    int step = 1;
+    for (int run = 0; run < runs; ++run) {
         (void)hipEventRecord(tune_ev_[0], s_);
         for (int i = 0; i < reps; ++i)
-            (void)step();
+            (void)launch_step(step++ & 1, s_, c);
         (void)hipEventRecord(tune_ev_[1], s_);
         if (hipEventSynchronize(tune_ev_[1]) != hipSuccess)
             return 1e30;
@@ -559,34 +559,68 @@ KernelCfg Batch::tune_cg()
     const char *tenv = getenv("STAG_TUNE");
     if (tenv && tenv[0] == '0')
         return best;
-    // Every system in a CG step; vectors and the partial sums the first
-    // prologue reads filled with a small positive pattern (bytes 0x3f) before
-    // each shape's run, so the state stays in CG steps and every kernel does its
-    // full work.  x points at
-    // the FP64 work vector.
+    // Each shape runs the first steps of a solve of every system, as the solve
+    // driver launches them (steps from one fixed state, which do not alternate
+    // the FP16 directions, put other shapes first than solves do).  The FP64 work
+    // vector holds what the solve does not own: in mixed precision the first
+    // system's part the source of all, the second's x (CG steps touch neither),
+    // so that the first can recompute its residual; in FP64 each system's part its
+    // source, which x = 0 overwrites as the initialisation reads it.
     const size_t nsys = 2 * (size_t)S_, Vh = f_->g.Vh;
     tune_st_.resize(nsys);
     memset(tune_st_.data(), 0, nsys * sizeof(SysState));
     for (auto &x : tune_st_) {
-        x.mode = M_CG;
+        x.mode = M_INIT;
         x.mass2 = 1e-4;
-        x.rr = 1.0;
-        x.alpha = 1e-30;
         x.maxiter = 1 << 30;
         x.mixed = prec_ != STAG_FP64;
     }
-    std::vector<dbl2 *> xs(nsys);
-    for (size_t j = 0; j < nsys; ++j)
-        xs[j] = tmp_ + j * 3 * Vh;
+    const bool mixed = prec_ != STAG_FP64;
+    std::vector<dbl2 *> xs(nsys), bs(nsys);
+    for (size_t j = 0; j < nsys; ++j) {
+        xs[j] = tmp_ + (mixed ? 1 : j) * 3 * Vh;
+        bs[j] = tmp_ + (mixed ? 0 : j) * 3 * Vh;
+    }
+    struct Restore {  // what the timed solves run with is not this workspace's choice
+        int &p, v;
+        ~Restore() { p = v; }
+    } restore{parities_, parities_};
+    parities_ = 3;
     const bool verbose = getenv("STAG_TUNE_VERBOSE") != nullptr;
     if (hipMemcpyAsync(xhi_d_, xs.data(), nsys * sizeof(void *), hipMemcpyHostToDevice, s_) != hipSuccess ||
-        hipMemcpyAsync(perm_d_, perm_h_, nsys * sizeof(int), hipMemcpyHostToDevice, s_) != hipSuccess ||
+        hipMemcpyAsync(b_d_, bs.data(), nsys * sizeof(void *), hipMemcpyHostToDevice, s_) != hipSuccess ||
         hipEventCreate(&tune_ev_[0]) != hipSuccess || hipEventCreate(&tune_ev_[1]) != hipSuccess) {
         (void)hipStreamSynchronize(s_);
         return best;
     }
     double best_t = 1e30;
     const int lps_c[4] = {1, 2, 4, 8}, blk_c[3] = {64, 128, 256};
+    struct Timed {
+        KernelCfg c;
+        double t;             // all systems running; in the end the time to choose by
+        double half = 1e30;   // half of them running
+    };
+    std::vector<Timed> seen;
+    auto timed = [&](const KernelCfg &c, int running, int reps, bool recompute) {
+        const double ms = time_cg_config(c, grid_x(c), uses_reduction(c), running, reps, 1, recompute);
+        if (verbose)
+            fprintf(stderr, "[stag tune cg] V=%d prec=%d slots=%d lps=%d block=%d rtile=%d shared=%d reduce=%d "
+                            "tables=%d remap=%d running=%d%s: %.2f us\n", 2 * f_->g.Vh, prec_, S_, c.lps, c.block, c.rtile,
+                    c.shared, uses_reduction(c) ? 1 : 0, c.tables, c.remap, running, recompute ? " recompute" : "", ms * 1e3);
+        return ms;
+    };
+    auto sweep = [&](const KernelCfg &c) {
+        // few partials are summed sooner by the next prologue than by a kernel of
+        // its own (two launches, 9 us a step)
+        if (c.reduce == 1 && (int64_t)blocks_needed(f_->g, c) * c.rtile < 256)
+            return;
+        seen.push_back({c, timed(c, S_, 5, false)});
+        best_t = std::min(best_t, seen.back().t);
+    };
+    // a first look at every shape, in the block order that most often suits its
+    // tiles: one system's two parities side by side, several systems' tiles one
+    // after the other (with the first order, FP16 16^4 took the wrong block size:
+    // 5.19 ms a solve of two systems instead of 4.54)
     for (int i = 0; i < t.n_rtiles; ++i) {
         const int R = t.rtiles[i];
         if (S_ % R)
@@ -599,18 +633,11 @@ KernelCfg Batch::tune_cg()
                     c.block = B;
                     c.rtile = R;
                     c.tables = 0;
-                    c.remap = 1;
+                    c.remap = S_ == 1 ? 1 : 2;
                     c.reduce = D;
                     if (D == 1 && uses_reduction(c) == uses_reduction(KernelCfg{L, B, R, 0, 1, 0}))
                         continue;  // the mode is forced from the environment
-                    const double ms = time_cg_config(c, grid_x(c), uses_reduction(c));
-                    if (verbose)
-                        fprintf(stderr, "[stag tune cg] V=%d prec=%d slots=%d lps=%d block=%d rtile=%d reduce=%d: "
-                                        "%.2f us\n", 2 * f_->g.Vh, prec_, S_, L, B, R, D, ms * 1e3);
-                    if (ms < best_t * 0.99) {
-                        best_t = ms;
-                        best = c;
-                    }
+                    sweep(c);
                 }
     }
     // shared-link tiles: one shape per tile size (one lane per site, a wavefront per system)
@@ -622,36 +649,72 @@ KernelCfg Batch::tune_cg()
             const KernelCfg c = shared_shape(code, D);
             if (D == 1 && uses_reduction(c) == uses_reduction(shared_shape(code, 0)))
                 continue;  // the mode is forced from the environment
-            const double ms = time_cg_config(c, grid_x(c), uses_reduction(c));
-            if (verbose)
-                fprintf(stderr, "[stag tune cg] V=%d prec=%d slots=%d shared rtile=%d waves=%d reduce=%d: %.2f us\n",
-                        2 * f_->g.Vh, prec_, S_, c.rtile, c.block / 64, D, ms * 1e3);
-            if (ms < best_t * 0.99) {
-                best_t = ms;
-                best = c;
-            }
+            sweep(c);
         }
     }
-    for (int T = 0; T < 2; ++T)
-        for (int X = 0; X < 4; ++X) {
-            KernelCfg c = best;
-            c.tables = T;
+    // the leading shapes again in every block order, in turn and the fastest of
+    // three runs each (short runs vary by more than these differ; one run for
+    // shapes far behind), with all systems and with half of them: a batch's
+    // systems end one after another, and a server's slots are seldom all taken
+    std::stable_sort(seen.begin(), seen.end(), [](const Timed &x, const Timed &y) { return x.t < y.t; });
+    std::vector<Timed> last;
+    for (size_t i = 0; i < seen.size() && i < (S_ < 4 ? 3 : 6) && seen[i].t < best_t * 1.15; ++i)
+        for (int X : {2, 1, 3, 0}) {
+            KernelCfg c = seen[i].c;
             c.remap = X;
-            if (remap_for(c, grid_x(c)) != X)
-                continue;
-            const double ms = time_cg_config(c, grid_x(c), uses_reduction(c));
-            if (verbose)
-                fprintf(stderr, "[stag tune cg] V=%d prec=%d slots=%d lps=%d block=%d rtile=%d tables=%d remap=%d: "
-                                "%.2f us\n", 2 * f_->g.Vh, prec_, S_, c.lps, c.block, c.rtile, T, X, ms * 1e3);
-            if (ms < best_t * 0.99) {
-                best_t = ms;
-                best = c;
-            }
+            if (remap_for(c, grid_x(c)) == X)
+                last.push_back({c, 1e30});
         }
+    const int half = (S_ + 1) / 2;
+    auto in_turn = [&](std::vector<Timed> &v) {
+        double t_best = 1e30;
+        for (int run = 0; run < 3; ++run)
+            for (Timed &x : v) {
+                if (run > 0 && x.t + x.half > t_best * 1.1)
+                    continue;
+                x.t = std::min(x.t, timed(x.c, S_, 5, false));
+                x.half = half == S_ ? x.t : std::min(x.half, timed(x.c, half, 5, false));
+                t_best = std::min(t_best, x.t + x.half);
+            }
+    };
+    auto keep_fastest = [&](const std::vector<Timed> &v) {
+        double t_best = 1e30;
+        for (const Timed &x : v)
+            if (x.t + x.half < t_best * 0.99) {
+                t_best = x.t + x.half;
+                best = x.c;
+            }
+    };
+    in_turn(last);
+    if (mixed) {
+        // What the residual recomputations add differs between shapes that are
+        // close otherwise.  One a decade of the residual in FP16 and one every two in
+        // FP32 are about one in 18 and in 40 steps of each system; the runs below
+        // have one system's in half their steps.
+        std::stable_sort(last.begin(), last.end(),
+                         [](const Timed &x, const Timed &y) { return x.t + x.half < y.t + y.half; });
+        const double share = std::min(1.0, 2.0 * S_ / (prec_ == STAG_FP16_RU ? 18 : 40));
+        size_t n = 1;
+        while (n < last.size() && n < 4 && last[n].t + last[n].half < (last[0].t + last[0].half) * 1.06)
+            ++n;
+        last.resize(std::min(n, last.size()));
+        std::vector<double> with(last.size(), 1e30);
+        for (int run = 0; run < 2; ++run)
+            for (size_t i = 0; i < last.size(); ++i)
+                with[i] = std::min(with[i], timed(last[i].c, S_, 4, true));
+        for (size_t i = 0; i < last.size(); ++i)
+            last[i].t += 2.0 * share * (with[i] - last[i].t);
+    }
+    keep_fastest(last);
+    last.assign(2, {best, 1e30});
+    last[1].c.tables = 1;
+    in_turn(last);
+    keep_fastest(last);
     // Smaller tiles, for when fewer systems run than the tuned tile takes: a
     // tile's empty places still gather (they read the first system's values),
-    // so a lone system in a large tile pays for the whole tile.  Each is tuned
-    // at the tuned shape's block count, which every kernel of the batch keeps.
+    // so a lone system in a large tile pays for the whole tile.  Each is timed
+    // with as many systems as it holds, at the tuned shape's block count, which
+    // every kernel of the batch keeps.
     const int nblk = grid_x(best);
     const bool reduce = uses_reduction(best);
     small_.clear();
@@ -676,7 +739,7 @@ KernelCfg Batch::tune_cg()
                 c.lps = L;
                 c.block = B;
                 c.rtile = R;
-                const double ms = time_cg_config(c, nblk, reduce);
+                const double ms = time_cg_config(c, nblk, reduce, R, 5, 2, false);
                 if (verbose)
                     fprintf(stderr, "[stag tune cg] small tile: V=%d prec=%d slots=%d lps=%d block=%d rtile=%d "
                                     "blocks=%d: %.2f us\n", 2 * f_->g.Vh, prec_, S_, L, B, R, nblk, ms * 1e3);
@@ -691,7 +754,7 @@ KernelCfg Batch::tune_cg()
                 continue;
             c.tables = best.tables;
             c.remap = best.remap;
-            const double ms = time_cg_config(c, nblk, reduce);
+            const double ms = time_cg_config(c, nblk, reduce, R, 5, 2, false);
             if (verbose)
                 fprintf(stderr, "[stag tune cg] small tile: V=%d prec=%d slots=%d shared rtile=%d waves=%d blocks=%d: "
                                 "%.2f us\n", 2 * f_->g.Vh, prec_, S_, R, c.block / 64, nblk, ms * 1e3);
@@ -763,6 +826,11 @@ int Batch::upload_and_init(const std::vector<int> &systems)
     int rc = mark_stage();
     if (rc != STAG_OK || persist_)  // the one launch initialises by itself
         return rc;
+    return launch_init();
+}
+
+int Batch::launch_init()
+{
     const CgArgs a = args();
     const CgLaunchTable &t = cg_table(prec_, f_->rows, f_->nt_links);
     dim3 grid((unsigned)nblk_, (unsigned)nsys());

@@ -90,6 +90,7 @@ private:
     int launch_step(int ver, hipStream_t st, const KernelCfg &c);
     int finish_create();              // common tail of create / create_external
     void carve(void *base);           // device views into the workspace at base
+    int launch_init();
     int choose_shape();  // the step kernels' shape, idle states, recorded epochs
     int one_launch(const CgArgs &a, uint32_t seq);  // launched, and its outcome read back
     int mark_stage();                 // the staged host data are being copied
@@ -103,7 +104,8 @@ private:
     KernelCfg tune_cg();
     bool parse_shape(const char *text, const CgLaunchTable &t, KernelCfg &c) const;
     KernelCfg default_cg_cfg() const;
-    double time_cg_config(const KernelCfg &c, int nblk, bool reduce);
+    double time_cg_config(const KernelCfg &c, int nblk, bool reduce, int running, int reps, int runs,
+                          bool recompute);
     CgArgs args() const;
 
     Ctx *ctx_;
