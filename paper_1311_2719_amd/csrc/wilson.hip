@@ -184,12 +184,13 @@ template <int ROWS, int LPS, class LPA> struct WLaunch {
     {
         return dim3((unsigned)(((int64_t)Vh * LPS + kWBlock - 1) / kWBlock) * (unsigned)tiles);
     }
-    static void hop(const GaugeField *f, int pf, const double *in, double *out, int remap, hipStream_t s)
+    // outputs of parity pf (once: every link read non-temporally), or of both (pf < 0)
+    static void hop(const GaugeField *f, int pf, bool once, const double *in, double *out, int remap, hipStream_t s)
     {
         if (pf < 0)
             hipLaunchKernelGGL((wil::k_wilson_dslash<ROWS, LPS, LPA>), grid(f->g.Vh, 2), dim3(kWBlock), 0, s, f->g,
                                (const dbl2 *)f->links[0], (const dbl2 *)in, (dbl2 *)out, pf, remap);
-        else if (f->nt_once)
+        else if (once)
             hipLaunchKernelGGL((wil::k_wilson_dslash<ROWS, LPS, PrecF64NTOnce>), grid(f->g.Vh), dim3(kWBlock), 0, s, f->g,
                                (const dbl2 *)f->links[0], (const dbl2 *)in, (dbl2 *)out, pf, remap);
         else
@@ -221,7 +222,7 @@ template <int ROWS, int LPS, class LPA> struct WLaunch {
 };
 
 struct WTable {
-    void (*hop)(const GaugeField *, int, const double *, double *, int, hipStream_t);
+    void (*hop)(const GaugeField *, int, bool, const double *, double *, int, hipStream_t);
     void (*init)(const wil::WArgs &, hipStream_t);
     void (*step)(const wil::WArgs &, hipStream_t, int);
     void (*finish)(const wil::WArgs &, hipStream_t);
@@ -249,14 +250,30 @@ const WTable &wilson_table(const GaugeField *f, int lps)
     return f->nt_links ? wilson_table_of<PrecF64NT>(f->rows, lps) : wilson_table_of<PrecF64>(f->rows, lps);
 }
 
-// Lanes per site and block order (XCD-contiguous or not) for the Wilson
-// kernels of a field: STAG_WILSON_LPS fixes the lanes, else the fastest hop
-// on two full-field vectors of scratch (`in`, `out`, each [2][12][Vh]), timed
-// once per field (by its first solve or first standalone hop); 4 lanes and
-// the XCD order when no scratch is given.
-KernelCfg wilson_cfg(Ctx *ctx, GaugeField *f, const double *in, double *out, hipStream_t s)
+// What a shape is chosen for.  Each use is timed on the kernel it runs: the
+// hop of both parities shares links between them, the hop of one parity and
+// the solve's kernels use each link once, and read it with the loads the field
+// has for them.
+enum class WUse { kBoth, kOne, kSolve };
+
+bool reads_once(const GaugeField *f, WUse use) { return use == WUse::kSolve ? f->nt_links != 0 : f->nt_once != 0; }
+
+// Key of the shape in GaugeField::tuned (one entry for the two uses of one
+// parity where their link loads are the same).
+uint64_t wilson_key(const GaugeField *f, WUse use)
 {
-    const uint64_t key = (uint64_t)3 << 40;
+    return ((uint64_t)3 << 40) | (use == WUse::kBoth ? 0u : reads_once(f, use) ? 1u : 2u);
+}
+
+// Lanes per site and block order (XCD-contiguous or not) for a use of a field:
+// STAG_WILSON_LPS fixes the lanes, else the fastest hop on two full-field
+// vectors of scratch (`in`, `out`, each [2][12][Vh]), timed once per field and
+// use (by its first solve or first standalone hop); 4 lanes and the XCD order
+// when no scratch is given.  With one shape for all, from the hop of one
+// parity, see the figures at wilson_dslash.
+KernelCfg wilson_cfg(Ctx *ctx, GaugeField *f, WUse use, const double *in, double *out, hipStream_t s)
+{
+    const uint64_t key = wilson_key(f, use);
     int lps_env = 0;
     if (const char *e = getenv("STAG_WILSON_LPS")) {
         const int v = atoi(e);
@@ -280,9 +297,8 @@ KernelCfg wilson_cfg(Ctx *ctx, GaugeField *f, const double *in, double *out, hip
             (void)hipEventDestroy(e0);
         return best;
     }
-    // timed on one parity (half the sites), the work of each CG kernel: a
-    // count that fills the GPU for the whole lattice can leave it half idle
-    // there
+    const int pf = use == WUse::kBoth ? -1 : 0;
+    const bool once = reads_once(f, use);
     float best_ms = 1e30f;
     const int reps = 5;
     for (int L : kWLps) {
@@ -290,10 +306,10 @@ KernelCfg wilson_cfg(Ctx *ctx, GaugeField *f, const double *in, double *out, hip
             continue;
         for (int remap = 1; remap >= 0; --remap) {
             const WTable &t = wilson_table(f, L);
-            t.hop(f, 0, in, out, remap, s);
+            t.hop(f, pf, once, in, out, remap, s);
             (void)hipEventRecord(e0, s);
             for (int i = 0; i < reps; ++i)
-                t.hop(f, 0, in, out, remap, s);
+                t.hop(f, pf, once, in, out, remap, s);
             (void)hipEventRecord(e1, s);
             float ms = 0.f;
             if (hipEventSynchronize(e1) == hipSuccess && hipEventElapsedTime(&ms, e0, e1) == hipSuccess &&
@@ -303,8 +319,8 @@ KernelCfg wilson_cfg(Ctx *ctx, GaugeField *f, const double *in, double *out, hip
                 best.remap = remap;
             }
             if (getenv("STAG_TUNE_VERBOSE"))
-                fprintf(stderr, "[stag tune wilson] V=%d lps=%d remap=%d: %.2f us per parity\n", 2 * f->g.Vh, L,
-                        remap, ms * 1e3 / reps);
+                fprintf(stderr, "[stag tune wilson] V=%d %s once=%d lps=%d remap=%d: %.2f us\n", 2 * f->g.Vh,
+                        pf < 0 ? "both parities" : "one parity", once, L, remap, ms * 1e3 / reps);
         }
     }
     (void)hipEventDestroy(e0);
@@ -318,12 +334,13 @@ KernelCfg wilson_cfg(Ctx *ctx, GaugeField *f, const double *in, double *out, hip
 
 int wilson_dslash(Ctx *ctx, GaugeField *f, int out_parity, const double *in, double *out, hipStream_t s)
 {
+    const WUse use = out_parity == STAG_ALL ? WUse::kBoth : WUse::kOne;
     bool tuned;
     {
         std::lock_guard<std::mutex> lk(ctx->mu);
-        tuned = f->tuned.count((uint64_t)3 << 40) != 0;
+        tuned = f->tuned.count(wilson_key(f, use)) != 0;
     }
-    KernelCfg c = wilson_cfg(ctx, f, nullptr, nullptr, s);
+    KernelCfg c = wilson_cfg(ctx, f, use, nullptr, nullptr, s);
     if (!tuned) {
         // the first hop of a field times the shapes on two scratch vectors
         // from the arena (as the first solve does on its workspace); without
@@ -332,12 +349,12 @@ int wilson_dslash(Ctx *ctx, GaugeField *f, int out_parity, const double *in, dou
         char *scratch = (char *)ctx->arena.alloc(2 * full);
         if (scratch) {
             if (hipMemsetAsync(scratch, 0, full, s) == hipSuccess)
-                c = wilson_cfg(ctx, f, (const double *)scratch, (double *)(scratch + full), s);
+                c = wilson_cfg(ctx, f, use, (const double *)scratch, (double *)(scratch + full), s);
             (void)hipStreamSynchronize(s);
             ctx->arena.release(scratch);
         }
     }
-    wilson_table(f, c.lps).hop(f, out_parity == STAG_ALL ? -1 : out_parity, in, out, c.remap, s);
+    wilson_table(f, c.lps).hop(f, out_parity == STAG_ALL ? -1 : out_parity, reads_once(f, use), in, out, c.remap, s);
     STAG_HIP_CHECK(hipGetLastError());
     return STAG_OK;
 }
@@ -408,7 +425,7 @@ int wilson_cg_solve(Ctx *ctx, GaugeField *f, double kappa, double tol, int maxit
 
     // lanes per site: tuned on this workspace (bh|r and p|ap are two full-field
     // vectors) before the solve uses it
-    const KernelCfg cfg = wilson_cfg(ctx, f, (const double *)a.bh, (double *)a.p, s);
+    const KernelCfg cfg = wilson_cfg(ctx, f, WUse::kSolve, (const double *)a.bh, (double *)a.p, s);
     const int lps = cfg.lps;
     a.remap = cfg.remap;
     const WTable &tab = wilson_table(f, lps);

@@ -1,13 +1,42 @@
-"""What the tuners time: the leading shapes of the CG step more than once."""
+"""What the tuners time: the kernels that are then run, and the leading shapes
+of the CG step more than once."""
 
 import re
 
+import numpy as np
 import pytest
 
+import oracle
 from paper_1311_2719_amd import binding, inputs
 
 pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("nt", ["0", "1"])
+def test_wilson_shapes_are_timed_on_the_kernels_that_run(monkeypatch, capfd, nt):
+    dims = (4, 4, 6, 8)
+    monkeypatch.setenv("STAG_TUNE_VERBOSE", "1")
+    monkeypatch.setenv("STAG_NT_LINKS", nt)
+    U, psi = inputs.haar_su3(dims, 541), inputs.gaussian_spinor(dims, 542)
+    ref = oracle.wilson_hop(dims, U, psi)
+    scale = np.sqrt(np.mean(np.sum(np.abs(ref) ** 2, axis=(1, 2))))
+    timed = lambda: set(re.findall(r"(both parities|one parity) once=(\d)", capfd.readouterr().err))  # noqa: E731
+    with binding.Context(device=0, arena_bytes=64 << 20) as ctx:
+        f = ctx.set_gauge_wilson(dims, U)
+        b, out = ctx.pack_spinor(f, psi), ctx.new_spinor(f)
+        capfd.readouterr()
+        ctx.wilson_dslash(f, b, out)
+        assert {k for k, _ in timed()} == {"both parities"}
+        # sums of 8 hops of 3 products on 4 spins in FP64
+        assert np.max(np.abs(ctx.unpack_spinor(f, out).cpu().numpy() - ref)) <= 1e-13 * scale
+        one = ctx.new_spinor(f)
+        ctx.wilson_dslash(f, b, one, out_parity=binding.ODD)
+        assert timed() == {("one parity", nt)}
+        assert float((one[1] - out[1]).abs().max()) <= 1e-13 * scale and float(one[0].abs().max()) == 0
+        ctx.wilson_dslash(f, b, out)
+        ctx.wilson_solve(f, b, out, 0.11)  # the loads of the hop of one parity: nothing new to time
+        assert timed() == set()
 
 
 @pytest.mark.parametrize("slots,precision", [(1, binding.FP16_RU), (4, binding.FP32_RU)])
