@@ -1347,7 +1347,7 @@ static int run_solve(Ctx *ctx, Batch &B, const std::shared_ptr<GaugeField> &f, i
         if (y && y[i]) {
             const int par = params[i].parity;
             const int out_par = par == STAG_ALL ? STAG_ALL : 1 - par;
-            rc = fixed_mem ? dslash_with(cached_config(ctx, f.get(), 0, 1), f.get(), 0, out_par, 0, f->g.Vh, x[i],
+            rc = fixed_mem ? dslash_with(cached_config(ctx, f.get(), 0, 1, out_par != STAG_ALL), f.get(), 0, out_par, 0, f->g.Vh, x[i],
                                          y[i], 0, s)
                            : dslash_f64(ctx, f.get(), out_par, 0, f->g.Vh, x[i], y[i], 0, s);
             if (rc != STAG_OK)

@@ -716,7 +716,7 @@ int stag_tune_info(stag_ctx *ctx, int32_t gauge_id, int32_t precision, int32_t n
     if (f->kind != FIELD_STAGGERED)
         return set_error(STAG_EINVAL, "gauge id %d holds Wilson-fermion links", gauge_id);
     DeviceGuard dg(c->device);
-    KernelCfg k = tune_config(c, f.get(), precision, nrhs, c->stream);
+    KernelCfg k = tune_config(c, f.get(), precision, nrhs, false, c->stream);
     if (lanes_per_site)
         *lanes_per_site = k.lps;
     if (block)

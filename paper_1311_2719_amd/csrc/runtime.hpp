@@ -193,9 +193,10 @@ int md_trajectory(Ctx *ctx, const int32_t dims[4], double *U, double *Q, const d
                   hipStream_t s, stag_md_info *info);
 // full-lattice fermion field from one storage precision to another
 int convert_fermion(const Geom &g, int prec_in, const void *in, int prec_out, void *out, hipStream_t s);
-KernelCfg tune_config(Ctx *ctx, GaugeField *f, int prec, int nrhs, hipStream_t s);
-// the tuned shape if (prec, nrhs) has been tuned on f, else the default; never tunes
-KernelCfg cached_config(Ctx *ctx, GaugeField *f, int prec, int nrhs);
+// one_parity: for outputs of one parity (nrhs 1)
+KernelCfg tune_config(Ctx *ctx, GaugeField *f, int prec, int nrhs, bool one_parity, hipStream_t s);
+// the tuned shape if (prec, nrhs, one_parity) has been tuned on f, else the default; never tunes
+KernelCfg cached_config(Ctx *ctx, GaugeField *f, int prec, int nrhs, bool one_parity);
 // CG step shape tuned for (field, precision, slots), if a solve with that many
 // slots has run; reduce: whether a reduction kernel runs between the steps.
 bool cg_tuned_shape(Ctx *ctx, const GaugeField *f, int prec, int slots, KernelCfg &out, bool &reduce);

@@ -57,3 +57,26 @@ def test_leading_cg_shapes_are_timed_again_in_every_block_order(monkeypatch, cap
     taken = (shape["lanes_per_site"], shape["block"], shape["rhs_tile"], shape["shared_links"], shape["reduction_kernel"])
     times = [lines.count(taken + (order,)) for order in (0, 1, 2)]
     assert min(times) >= 1 and max(times) >= 3, (taken, times)
+
+
+@pytest.mark.parametrize("precision", [0, 1, 2])
+def test_dslash_of_one_parity_is_timed_by_itself(monkeypatch, capfd, precision):
+    dims = (16, 8, 8, 4)
+    monkeypatch.setenv("STAG_TUNE_VERBOSE", "1")
+    U, chi = inputs.haar_su3(dims, 581), inputs.gaussian_source(dims, 582)
+    timed = lambda: set(re.findall(r"stag tune\].* (both parities|one parity) ", capfd.readouterr().err))  # noqa: E731
+    with binding.Context(device=0, arena_bytes=256 << 20) as ctx:
+        f = ctx.set_gauge(dims, U)
+        b = ctx.pack(f, chi)
+        if precision:
+            b = ctx.convert(f, b, ctx.new_fermion(f, precision), binding.F64, precision)
+        out, one = ctx.new_fermion(f, precision), ctx.new_fermion(f, precision)
+        capfd.readouterr()
+        ctx.dslash(f, b, out, precision=precision)
+        assert timed() == {"both parities"}
+        ctx.dslash(f, b, one, out_parity=binding.ODD, precision=precision)
+        assert timed() == {"one parity"}
+        ctx.dslash(f, b, one, out_parity=binding.EVEN, precision=precision)
+        assert timed() == set()
+        torch.cuda.synchronize()
+        assert torch.equal(one, out)  # block size and order do not change a site's sum
