@@ -445,8 +445,10 @@ int stag_tune_info(stag_ctx *ctx, int32_t gauge_id, int32_t precision,
  * systems per tile, neighbour tables read (1) or computed (0), and whether a
  * reduction kernel sums each step kernel's partial sums (1) or every block of
  * the next kernel does (0).  Where one launch runs the whole solve (one
- * source, FP64 or FP32, up to 65536 sites), the shape is that of the step
- * kernels which would take over, by rule and not timed.  While fewer systems run than a tile takes, the
+ * source in FP64 or FP32, on lattices that fit one block of 512 threads per CU,
+ * at most 256: up to 65536 sites at two lanes per site, up to 32768 at four,
+ * which FP64 takes with three stored link rows), the shape is that of the step
+ * kernels which would take over: by rule, and timed once they have.  While fewer systems run than a tile takes, the
  * solve may use smaller tiles tuned alongside.  shared_links = 1: the FP32 /
  * FP16 tiles that stage each block's links in LDS for all systems of the tile
  * (one wavefront per system, block = 64 x rhs_tile threads, one lane per
