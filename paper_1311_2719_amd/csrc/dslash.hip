@@ -319,7 +319,7 @@ KernelCfg tune_config(Ctx *ctx, GaugeField *f, int prec, int nrhs, bool one_pari
                 ok = false;
                 return 1e30;
             }
-            const int reps = 4;
+            const int reps = tune_reps(f->g);
             (void)hipEventRecord(e0, s);
             for (int i = 0; i < reps; ++i)
                 (void)run();

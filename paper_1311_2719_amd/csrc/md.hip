@@ -115,8 +115,9 @@ struct Lex {
 // 19 matrices are read per link, most of them by the sites around as well: each
 // XCD takes one contiguous range of sites, so that it finds them in its L2, and
 // blocks of one wavefront reach every CU on small lattices.  With blocks of 256
-// dealt to the XCDs in turn: 8^4 20.4 -> 18.1 us, 12^3 16 45 -> 38, 16^4 85 -> 80,
-// 24^4 481 -> 465 (these with the fermion force, 17 of the 80).  What remains is
+// dealt to the XCDs in turn: 8^4 19.9 -> 17.1 us, 12^3 16 44.5 -> 36.8, 16^4 84.0 ->
+// 80.1, 24^4 483 -> 471 (these with the fermion force, 17 of the 80, a hundred calls
+// on one field; with inputs in turn 16^4 86.0 -> 82.8).  What remains is
 // the address unit, 64 lines a load, and latency at three waves a SIMD: loads by
 // quads of lanes that transpose in registers (a third of the lines) took as long,
 // a transposition through LDS longer.

@@ -193,6 +193,10 @@ int md_trajectory(Ctx *ctx, const int32_t dims[4], double *U, double *Q, const d
                   hipStream_t s, stag_md_info *info);
 // full-lattice fermion field from one storage precision to another
 int convert_fermion(const Geom &g, int prec_in, const void *in, int prec_out, void *out, hipStream_t s);
+// Launches in one timing of a hop's shape: from 24^4 on, where one takes 30 us and
+// more, two say as much as five (32^4, first hop of both parities: 11.1 -> 6.8 ms
+// staggered, 13.4 -> 6.9 ms Wilson).
+inline int tune_reps(const Geom &g) { return g.Vh >= 165888 ? 2 : 5; }
 // one_parity: for outputs of one parity (nrhs 1)
 KernelCfg tune_config(Ctx *ctx, GaugeField *f, int prec, int nrhs, bool one_parity, hipStream_t s);
 // the tuned shape if (prec, nrhs, one_parity) has been tuned on f, else the default; never tunes
