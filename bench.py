@@ -16,7 +16,7 @@ The same line reports:
   mixed         FP32 and FP16 reliable-update solves/s of the same system and
                 their ratio to FP64;
   roofline      the FP64 D_slash kernel on the same 32^4 field (working set
-                0.9 GB, far beyond the 256 MB Infinity Cache): 100
+                0.5 GB, twice the 256 MB Infinity Cache): 100
                 full-lattice applications per run, HIP events on the library's
                 stream; achieved = algorithmic bytes per site (its 4 stored links,
                 each read once for both its ends, + 1 gathered input vector
